@@ -325,7 +325,7 @@ def main():
             if i:
                 times.append(ev.elapsed_ms(0, 1))
         ms = sum(times) / len(times)
-        moved = rows * cols * 4.0 * r * (2 * it + 3)           # per rank: 2 it + 2 reads and one write of the matrix
+        moved = rows * cols * 4.0 * (r * (it + 1) + 2)         # it + 1 reads of the matrix per rank; the residual read and written once
         print(json.dumps({"sketch": {"rows": rows, "cols": cols, "rank": r, "power_iterations": it, "ms": round(ms, 3),
                                      "ms_per_rank": round(ms / r, 3),
                                      "roofline": {"bound": "hbm", "achieved": round(moved / ms / 1e6, 1), "peak": 8000.0,

@@ -47,7 +47,7 @@ tq_status tqi_device_state(const TqDeviceState** out)
             void* sp = nullptr;
             if (hipGetSymbolAddress(&sp, HIP_SYMBOL(scratch)) != hipSuccess || !sp) return TQ_ERR_HIP;
             g_dev_state[dev].scratch = sp;
-            if (tqi_setup_mfma() != TQ_OK || tqi_setup_skinny() != TQ_OK) return TQ_ERR_HIP;
+            if (tqi_setup_mfma() != TQ_OK || tqi_setup_skinny() != TQ_OK || tqi_setup_sketch() != TQ_OK) return TQ_ERR_HIP;
             g_dev_ready[dev].store(1, std::memory_order_release);
         }
     }

@@ -402,6 +402,7 @@ tq_status tqi_device_state(const TqDeviceState** out);
 // each translation unit raises the dynamic-LDS limit of its own kernel instantiations (current device)
 tq_status tqi_setup_mfma();
 tq_status tqi_setup_skinny();
+tq_status tqi_setup_sketch();
 
 // profiling aid: stage-boundary events registered through tq_set_profile_events (nullptr when off)
 void tqi_record_stage(int stage, hipStream_t stream);

@@ -1,13 +1,18 @@
 // Offline helper: rank-r approximation of a dense fp32 matrix by r Gaussian-sketch rank-1 deflations (Section 3.1,
 // "Plug-in", Eq. 13), the replacement for the SVD of the tiled matrix W_big of Eq. 11.  Per rank, with sketch vector s:
 //   Q = (W W^T)^it W s,   U = Q / |Q|,   Sigma = |Q^T W| / |Q|,   V = Q^T W / |Q^T W|,   W <- W - U Sigma V.
-// Everything is a matrix-vector product or a rank-1 update over a matrix that does not fit any cache, so every kernel
-// is a coalesced stream over W (HBM-bound): products along the rows by one wave per row, products along the columns
-// by column strips with the rows cut into slabs (partial sums added in a fixed order), and the deflation fused into the
-// first product of the next rank, so that a rank costs 2 it + 2 reads and one write of W.
+// The matrix fits no cache, so what counts is how often it is streamed.  A product along the rows followed by one along
+// the columns, q = W x and z = W^T q, needs ONE read: row i of W adds q_i W_i to z, and q_i = W_i x depends on that row
+// alone, so a workgroup that holds a whole row in registers forms q_i and adds the row to its own z before it lets the
+// row go (sk_pass_kernel).  A rank is it + 1 such passes.  The deflation is applied to the rows as they are read, with
+// the same subtraction per element and in the same order as a stored update, and the matrix is written back only when
+// no more pending u p^T fit in LDS.  Matrices of more than 32768 columns (a row does not fit a workgroup) take one
+// stream per product instead, with the deflation stored once per rank.
 // Q is renormalised after every power iteration (U, Sigma and V do not depend on the length of Q; the raw powers leave
 // the fp32 range after a few iterations).  All sums have a fixed order: results are run-to-run identical.
-#include "tq_common.h"
+#include "tq_device.h"
+
+#include <algorithm>
 
 namespace {
 
@@ -119,10 +124,247 @@ __global__ void __launch_bounds__(256) sk_scale_kernel(const float* __restrict__
     if (sigma_out && i == 0) *sigma_out = nv;
 }
 
+// One stream over W: rows are read (with the npend pending deflations w -= u_k[i] p_k applied, and stored back with
+// WRITE); with DOT, q[i] = w_i . x, partial[workgroup][j] = sum of q[i] w_ij over the workgroup's rows and
+// ssq[workgroup] = sum of its q[i]^2.
+// Bound by the HBM stream.  A thread owns NC float4 columns of every row, so x and the column sums stay in registers for
+// the whole pass, and R rows are in work while the next R are in flight; one barrier per R rows (the dot products'
+// reduction over the waves).  The workgroup is as wide as the row needs (256 to 1024 threads, 1024 threads per CU in all):
+// registers hold at most 32768 columns (there x moves to LDS and the pending vector is read through the L2).
+// Measured on 16384 x 12672 (831 MB): 130-136 us a pass = 6.1-6.4 TB/s with up to three pending deflations (295 us where it
+// also stores), against 119 us for the product along the rows, 135 + 6 us for the one along the columns and 319 us for
+// the stored deflation as passes of their own: rank 16 with two power iterations went from 16.6 to 7.8 ms.
+template <int NT, int NC, int R, bool XLDS, bool DOT, bool WRITE>
+__global__ void __launch_bounds__(NT, 4) sk_pass_kernel(float* __restrict__ W, int64_t rows, int64_t cols,
+                                                     const float* __restrict__ x, const float* __restrict__ U0,
+                                                     const float* __restrict__ P0, int npend, float* __restrict__ q,
+                                                     float* __restrict__ partial, float* __restrict__ ssq)
+{
+    constexpr int NW = NT / 64;
+    extern __shared__ __attribute__((aligned(16))) float sm[];      // red [2][R][NW] | x [cols] (XLDS) or p [npend][cols]
+    float* red = sm;
+    float* vec = sm + 2 * R * NW;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t G = gridDim.x, b = blockIdx.x;
+    const int nsteps = (int)((rows - b * R + G * R - 1) / (G * R));      // groups of R rows: b, b + G, ...
+    // columns past the end repeat the last four: they meet x = 0 and are never stored
+    // (byte offsets next to a scalar row pointer, recomputed at each use: held or hoisted they would not fit the 128
+    // registers that 1024 threads per CU leave)
+    const uint32_t end = (uint32_t)cols * 4u;
+    auto lane_off = [&]() {
+        uint32_t o = (uint32_t)tid * 16u;
+        asm volatile("" : "+v"(o));
+        return o;
+    };
+    auto at = [&](uint32_t o, int c) { return min(o + (uint32_t)(c * NT * 16), end - 16u); };
+    auto live = [&](uint32_t o, int c) { return o + (uint32_t)(c * NT * 16) < end; };
+    auto f4 = [](const float* p, uint32_t o) { return reinterpret_cast<const f32x4*>(reinterpret_cast<const uint8_t*>(p) + o); };
+    f32x4 xr[XLDS ? 1 : NC], acc[NC];
+    if (DOT) {
+        const uint32_t o = lane_off();
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (!XLDS) xr[c] = live(o, c) ? *f4(x, at(o, c)) : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    if (XLDS ? DOT : npend > 0) {
+        const float* src = XLDS ? x : P0;
+        const int64_t n = XLDS ? cols : npend * cols, n_pad = XLDS ? (int64_t)NC * NT * 4 : n;      // x is padded with zeros
+        for (int64_t i = (int64_t)tid * 4; i < n_pad; i += NT * 4)
+            *reinterpret_cast<f32x4*>(vec + i) = i < n ? *reinterpret_cast<const f32x4*>(src + i) : f32x4{0.f, 0.f, 0.f, 0.f};
+        __syncthreads();
+    }
+    float sq = 0.f;
+    auto row_of = [&](int s, int r) { return ((int64_t)s * G + b) * R + r; };
+    auto load = [&](f32x4 (&w)[R][NC], int s) {      // rows past the end repeat the last one: they count with q = 0
+        const uint32_t o = lane_off();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int64_t i = row_of(s, r);
+            const float* wr = W + (i < rows ? i : rows - 1) * cols;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) w[r][c] = WRITE ? *f4(wr, at(o, c)) : __builtin_nontemporal_load(f4(wr, at(o, c)));
+        }
+    };
+    auto work = [&](f32x4 (&w)[R][NC], int s) {
+        const uint32_t o = lane_off();
+        for (int k = 0; k < npend; ++k) {
+            float ui[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) ui[r] = U0[k * rows + (row_of(s, r) < rows ? row_of(s, r) : rows - 1)];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const f32x4 p4 = *f4((XLDS ? P0 : vec) + k * cols, at(o, c));
+#pragma unroll
+                for (int r = 0; r < R; ++r) w[r][c] -= ui[r] * p4;
+            }
+        }
+        if (WRITE) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (row_of(s, r) < rows) {
+#pragma unroll
+                    for (int c = 0; c < NC; ++c)
+                        if (live(o, c)) *const_cast<f32x4*>(f4(W + row_of(s, r) * cols, at(o, c))) = w[r][c];
+                }
+        }
+        if constexpr (DOT) {
+            float* rd = red + (s & 1) * (R * NW);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                float d = 0.f;
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    f32x4 x4;
+                    if constexpr (XLDS) x4 = *f4(vec, o + (uint32_t)(c * NT * 16));
+                    else x4 = xr[c];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) d = fmaf(w[r][c][i], x4[i], d);
+                }
+                d = wave_sum(d);
+                if (lane == 0) rd[r * NW + wave] = d;
+            }
+            tqdev::lds_barrier();
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                float qv = 0.f;
+#pragma unroll
+                for (int i = 0; i < NW; i += 4) {
+                    const f32x4 t = *reinterpret_cast<const f32x4*>(rd + r * NW + i);
+                    qv += (t[0] + t[1]) + (t[2] + t[3]);
+                }
+                const bool in = row_of(s, r) < rows;
+                if (tid == 0 && in) q[row_of(s, r)] = qv;
+                qv = in ? qv : 0.f;
+                sq = fmaf(qv, qv, sq);
+#pragma unroll
+                for (int c = 0; c < NC; ++c) acc[c] += qv * w[r][c];
+            }
+        }
+    };
+    f32x4 wa[R][NC], wb[R][NC];
+    load(wa, 0);
+    load(wb, 1);
+    for (int s = 0; s < nsteps; s += 2) {
+        work(wa, s);
+        load(wa, s + 2);
+        if (s + 1 < nsteps) work(wb, s + 1);
+        load(wb, s + 3);
+    }
+    if (DOT) {
+        const uint32_t o = lane_off();
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            if (live(o, c)) *const_cast<f32x4*>(f4(partial + b * cols, at(o, c))) = acc[c];
+        if (tid == 0) ssq[b] = sq;
+    }
+}
+
+// Ends a pass: z[j] = inv * sum of the G partial sums of column j, inv = 1 / |q| from the G partial sums of squares
+// (0 if that is zero: the matrix has run out of rank); with u, u[i] = q[i] * inv as well.  Latency-bound: 64 columns per
+// workgroup, the partial sums in 16 groups side by side.
+__global__ void __launch_bounds__(256) sk_finish_kernel(const float* __restrict__ partial, int G, int64_t cols,
+                                                        const float* __restrict__ ssq, float* __restrict__ z,
+                                                        const float* __restrict__ q, int64_t rows, float* __restrict__ u)
+{
+    __shared__ f32x4 red[16][16];
+    __shared__ float sred[256];
+    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+    const int64_t j = ((int64_t)blockIdx.x * 16 + tx) * 4;
+    float sq = 0.f;
+    for (int g = tid; g < G; g += 256) sq += ssq[g];
+    sred[tid] = sq;
+    f32x4 a = {0.f, 0.f, 0.f, 0.f};
+    if (j < cols) {
+        const int per = (G + 15) / 16, g1 = min(G, (ty + 1) * per);
+        int g = ty * per;
+        for (; g + 8 <= g1; g += 8) {
+            f32x4 v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = *reinterpret_cast<const f32x4*>(partial + (int64_t)(g + i) * cols + j);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) a += v[i];
+        }
+        for (; g < g1; ++g) a += *reinterpret_cast<const f32x4*>(partial + (int64_t)g * cols + j);
+    }
+    red[ty][tx] = a;
+    __syncthreads();
+    for (int s = 128; s >= 1; s >>= 1) {
+        if (tid < s) sred[tid] += sred[tid + s];
+        __syncthreads();
+    }
+    const float n = sqrtf(sred[0]), inv = n > 0.f ? 1.f / n : 0.f;
+    if (ty == 0 && j < cols) {
+        for (int i = 1; i < 16; ++i) a += red[i][tx];
+        *reinterpret_cast<f32x4*>(z + j) = a * inv;
+    }
+    if (u)
+        for (int64_t i = (int64_t)blockIdx.x * 256 + tid; i < rows; i += (int64_t)gridDim.x * 256) u[i] = q[i] * inv;
+}
+
+// V[rho] (p = Sigma V on entry) becomes a unit vector, its length goes to sigma[rho]; one workgroup per rank
+__global__ void __launch_bounds__(1024) sk_unit_kernel(float* __restrict__ V, int64_t cols, float* __restrict__ sigma)
+{
+    __shared__ float red[1024];
+    float* v = V + (int64_t)blockIdx.x * cols;
+    float acc = 0.f;
+    for (int64_t i = threadIdx.x; i < cols; i += 1024) acc = fmaf(v[i], v[i], acc);
+    red[threadIdx.x] = acc;
+    __syncthreads();
+    for (int s = 512; s >= 1; s >>= 1) {
+        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+        __syncthreads();
+    }
+    const float n = sqrtf(red[0]), inv = n > 0.f ? 1.f / n : 0.f;
+    for (int64_t i = threadIdx.x; i < cols; i += 1024) v[i] *= inv;
+    if (threadIdx.x == 0) sigma[blockIdx.x] = n;
+}
+
+// Shape of the fused pass for a row length: threads, float4 columns per thread, rows in work at a time; workgroups and
+// pending deflations that 156 KB of LDS per CU hold.  1024 threads per CU whatever the width.
+struct SketchShape {
+    int nt, nc, rr, wg, maxpend;
+    bool xlds;
+};
+bool sketch_shape(int64_t rows, int64_t cols, SketchShape* s)
+{
+    if (cols > 32768) return false;
+    s->xlds = cols > 16384;
+    s->nt = cols <= 4096 ? 256 : cols <= 8192 ? 512 : 1024;
+    s->nc = cols <= 1024 ? 1 : cols <= 2048 ? 2 : cols <= 16384 ? 4 : 8;
+    s->rr = s->xlds ? 1 : 8 / s->nc;
+    const int per_cu = 1024 / s->nt;
+    s->wg = (int)std::min<int64_t>(256 * per_cu, (rows + s->rr - 1) / s->rr);
+    s->maxpend = s->xlds ? 1 : (int)std::min<int64_t>(4, 156 * 1024 / per_cu / (cols * 4));
+    return true;
+}
+
+template <bool DOT, bool WRITE>
+tq_status launch_pass(const SketchShape& s, float* W, int64_t rows, int64_t cols, const float* x, const float* U0,
+                      const float* P0, int npend, float* q, float* partial, float* ssq, hipStream_t st)
+{
+    const size_t smem = ((size_t)2 * s.rr * (s.nt / 64) + (s.xlds ? (size_t)(DOT ? s.nc * s.nt * 4 : 0) : (size_t)npend * cols)) * 4;
+#define TQ_SKP(NT, NC, R, XL)                                                                                            \
+    hipLaunchKernelGGL((sk_pass_kernel<NT, NC, R, XL, DOT, WRITE>), dim3(s.wg), dim3(NT), smem, st, W, rows, cols, x, U0, P0, npend, \
+                       q, partial, ssq)
+    if (s.xlds) TQ_SKP(1024, 8, 1, true);
+    else if (s.nc == 1) TQ_SKP(256, 1, 8, false);
+    else if (s.nc == 2) TQ_SKP(256, 2, 4, false);
+    else if (s.nt == 256) TQ_SKP(256, 4, 2, false);
+    else if (s.nt == 512) TQ_SKP(512, 4, 2, false);
+    else TQ_SKP(1024, 4, 2, false);
+#undef TQ_SKP
+    TQ_CHECK_LAUNCH();
+    return TQ_OK;
+}
+
 struct SketchPlan {
     int slabs;
     int64_t rows_per_slab;
     size_t q, z, p, partial, norms, total;
+    bool fused;
+    SketchShape shape;
 };
 
 bool make_plan(int64_t rows, int64_t cols, SketchPlan* P)
@@ -140,13 +382,28 @@ bool make_plan(int64_t rows, int64_t cols, SketchPlan* P)
     P->q = take((size_t)rows * 4);
     P->z = take((size_t)cols * 4);
     P->p = take((size_t)cols * 4);
-    P->partial = take((size_t)P->slabs * cols * 4);
-    P->norms = take(256);
+    P->fused = sketch_shape(rows, cols, &P->shape);
+    P->partial = take((size_t)(P->fused ? P->shape.wg : P->slabs) * cols * 4);
+    P->norms = take(1024 * 4);          // fused pass: one sum of squares per workgroup
     P->total = off;
     return true;
 }
 
 }  // namespace
+
+tq_status tqi_setup_sketch()
+{
+    bool ok = true;
+#define TQ_ATTR1(NT, NC, R, XL, D, WR)                                                                                   \
+    ok = ok && hipFuncSetAttribute((const void*)sk_pass_kernel<NT, NC, R, XL, D, WR>,                                    \
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess
+#define TQ_ATTR(NT, NC, R, XL) TQ_ATTR1(NT, NC, R, XL, true, false); TQ_ATTR1(NT, NC, R, XL, true, true); TQ_ATTR1(NT, NC, R, XL, false, true)
+    TQ_ATTR(1024, 8, 1, true);
+    TQ_ATTR(512, 4, 2, false); TQ_ATTR(1024, 4, 2, false);
+#undef TQ_ATTR
+#undef TQ_ATTR1
+    return ok ? TQ_OK : TQ_ERR_HIP;
+}
 
 extern "C" size_t tq_sketch_workspace_size(int64_t rows, int64_t cols)
 {
@@ -170,7 +427,38 @@ extern "C" tq_status tq_sketch_lowrank(float* W, int64_t rows, int64_t cols, int
     float* z = (float*)(ws + P.z);
     float* p = (float*)(ws + P.p);
     float* partial = (float*)(ws + P.partial);
-    float* norms = (float*)(ws + P.norms);        // [0] |q|, [1] |p|
+    float* norms = (float*)(ws + P.norms);        // [0] |q|, [1] |p|; fused pass: sums of squares per workgroup
+    if (P.fused) {
+        const TqDeviceState* ds = nullptr;
+        if (tqi_device_state(&ds) != TQ_OK) return TQ_ERR_HIP;      // (raised dynamic-LDS limits)
+        const SketchShape& sh = P.shape;
+        const unsigned fin = (unsigned)((cols + 63) / 64);
+        int npend = 0;                 // the last npend deflations are not in W yet: u_k in U, p_k in V
+        for (int rho = 0; rho < r; ++rho) {
+            const float* x = sketch + (size_t)rho * cols;
+            for (int i = 0; i <= it; ++i) {
+                const float *U0 = U + (size_t)(rho - npend) * rows, *P0 = V + (size_t)(rho - npend) * cols;
+                const bool write = i == 0 && npend == sh.maxpend;
+                const tq_status rc = write ? launch_pass<true, true>(sh, W, rows, cols, x, U0, P0, npend, q, partial, norms, st)
+                                           : launch_pass<true, false>(sh, W, rows, cols, x, U0, P0, npend, q, partial, norms, st);
+                if (rc != TQ_OK) return rc;
+                if (write) npend = 0;
+                const bool last = i == it;      // p = W^T U = Sigma V, kept in V until sk_unit_kernel
+                hipLaunchKernelGGL(sk_finish_kernel, dim3(fin), dim3(256), 0, st, (const float*)partial, sh.wg, cols, (const float*)norms,
+                                   last ? V + (size_t)rho * cols : z, (const float*)q, rows, last ? U + (size_t)rho * rows : (float*)nullptr);
+                x = z;
+            }
+            TQ_CHECK_LAUNCH();
+            ++npend;
+        }
+        // the pending deflations: W holds the residual on return
+        const tq_status rc = launch_pass<false, true>(sh, W, rows, cols, nullptr, U + (size_t)(r - npend) * rows,
+                                                      V + (size_t)(r - npend) * cols, npend, nullptr, nullptr, nullptr, st);
+        if (rc != TQ_OK) return rc;
+        hipLaunchKernelGGL(sk_unit_kernel, dim3(r), dim3(1024), 0, st, V, cols, sigma);
+        TQ_CHECK_LAUNCH();
+        return TQ_OK;
+    }
     const unsigned row_blocks = (unsigned)((rows + 3) / 4 < 8192 ? (rows + 3) / 4 : 8192);
     const dim3 col_grid((unsigned)((cols / 4 + 255) / 256), (unsigned)P.slabs);
     const unsigned col_blocks = (unsigned)((cols + 255) / 256), rowv_blocks = (unsigned)((rows + 255) / 256);
