@@ -243,15 +243,17 @@ tq_status forward_impl(const tq_layer_desc* desc, const void* packed, const void
         if (rr != TQ_OK) return rr;
         route = nullptr;
     }
+    // the row tilings that kernels of this batch read: 16 rows on the decode kernels; 32 (pre-pass, 32-row kernel) and
+    // the large tiles on the tiled ones; none on the fp32 path
+    const int tilings = desc->act_dtype == TQ_ACT_FP32 ? 0 : tqi_bf16_takes_skinny(L, W, desc->flags) ? 1 << 2
+                        : 1 << 0 | 1 << (L.g == 256 ? 1 : 3);
     tq_status rc = tqi_launch_permute(topk_idx, topk_w, T, L.E, L.S, L.k, (int32_t*)(ws + W.offsets),
                                       (int32_t*)(ws + W.slot_of), L.k + L.S, (int32_t*)(ws + W.row_src),
                                       (int32_t*)(ws + W.row_token), (float*)(ws + W.row_w),
                                       (int32_t*)(ws + W.tile_e), (int32_t*)(ws + W.tile_row0), W.rt_max, ctrl,
                                       ctrl, (int32_t*)(ws + W.hist), W.nblk, packed, &L,
                                       (int32_t*)(ws + W.sk_cnt), W.sk_cnt_n, st, with_pre ? &pre : nullptr,
-                                      // the single-wave permutation of decode batches builds only the 16-row tiling
-                                      desc->act_dtype == TQ_ACT_BF16 && tqi_bf16_takes_skinny(L, W, desc->flags)
-                                          ? (1 << 2) : (1 << TQ_N_TILINGS) - 1,
+                                      tilings,
                                       route);
     if (rc != TQ_OK) return rc;
     tqi_record_stage(1, st);

@@ -79,6 +79,86 @@ __global__ void __launch_bounds__(256) route_kernel(const float* __restrict__ lo
     if (lane < k) topk_w[(size_t)t * k + lane] = my_p / denom;
 }
 
+// Layers of at most 256 experts and 16 selections: a row of 16 lanes per token, lane l of it holding experts l, l + 16,
+// ... (PL of them), so that a wave routes four tokens and every step of the arg-max stays inside a row, where lanes
+// exchange values by DPP.  With a wave per token (route_kernel) each round is twelve exchanges through the LDS crossbar,
+// which is what that kernel is bound by: 8192 tokens of 128 experts, top-8, 15.4 us there and 5.6 us here (4 MB of scores: the rest is latency of the rounds).
+// A score is held as an integer that orders the same way, so a round is a maximum, then the lowest expert that has it:
+// the order of route_kernel (score desc, index asc; -0 counts as +0), and its arithmetic on the scores.  NaN orders below
+// every number, an expert already chosen (or past E) below that.
+constexpr int32_t ROUTE_TAKEN = (int32_t)0x80000000, ROUTE_NAN = ROUTE_TAKEN + 1;
+__device__ inline int32_t route_key(float s)
+{
+    const int32_t b = __float_as_int(s + 0.0f);          // -0 + 0 = +0
+    const int32_t key = b < 0 ? b ^ 0x7FFFFFFF : b;
+    return s != s ? ROUTE_NAN : key;
+}
+__device__ inline float route_score(int32_t key) { return __int_as_float(key < 0 ? key ^ 0x7FFFFFFF : key); }
+
+template <int CTRL>
+__device__ inline int row_dpp(int v) { return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false); }
+__device__ inline int row_max(int v)          // rotations by 8, 4, 2, 1: every lane of the row ends with the maximum
+{
+    v = max(v, row_dpp<0x128>(v));
+    v = max(v, row_dpp<0x124>(v));
+    v = max(v, row_dpp<0x122>(v));
+    return max(v, row_dpp<0x121>(v));
+}
+__device__ inline int row_min(int v)
+{
+    v = min(v, row_dpp<0x128>(v));
+    v = min(v, row_dpp<0x124>(v));
+    v = min(v, row_dpp<0x122>(v));
+    return min(v, row_dpp<0x121>(v));
+}
+
+template <int PL>
+__global__ void __launch_bounds__(256) route_row_kernel(const float* __restrict__ logits, const float* __restrict__ bias,
+                                                        int T, int E, int k, int32_t* __restrict__ topk_idx,
+                                                        float* __restrict__ topk_w)
+{
+    const int sub = threadIdx.x & 15;
+    const int t_raw = blockIdx.x * 16 + (threadIdx.x >> 4);
+    const int t = min(t_raw, T - 1);          // a row past the end repeats the last token and stores nothing
+    const float* row = logits + (size_t)t * E;
+    float v[PL], b[PL];
+#pragma unroll
+    for (int i = 0; i < PL; ++i) {            // all loads are issued together, from addresses that exist
+        const int e = min(sub + 16 * i, E - 1);
+        v[i] = row[e];
+        b[i] = bias ? bias[e] : 0.f;
+    }
+    int32_t key[PL];
+#pragma unroll
+    for (int i = 0; i < PL; ++i) {
+        const float s = bias ? v[i] + b[i] : v[i];
+        key[i] = sub + 16 * i < E ? route_key(s) : ROUTE_TAKEN;
+    }
+    float first = 0.f, denom = 0.f, my_p = 0.f;
+    int my_e = 0;
+    for (int j = 0; j < k; ++j) {             // k <= E: there is an expert left in every round
+        int m = key[0];
+#pragma unroll
+        for (int i = 1; i < PL; ++i) m = max(m, key[i]);
+        m = row_max(m);
+        int be = 0x7FFFFFFF;
+#pragma unroll
+        for (int i = PL - 1; i >= 0; --i) be = key[i] == m ? sub + 16 * i : be;
+        be = row_min(be);
+#pragma unroll
+        for (int i = 0; i < PL; ++i) key[i] = be == sub + 16 * i ? ROUTE_TAKEN : key[i];
+        const float bv = route_score(m);
+        if (j == 0) first = bv;
+        const float p = expf(bv - first);     // the same value in every lane of the row
+        denom += p;
+        if (sub == j) { my_p = p; my_e = be; }
+    }
+    if (t_raw < T && sub < k) {
+        topk_idx[(size_t)t * k + sub] = my_e;
+        topk_w[(size_t)t * k + sub] = my_p / denom;
+    }
+}
+
 // The routing of a decode batch inside the permutation's launch (at most 64 tokens and 16 experts): one LANE per
 // token scans its scores serially, the same order (score desc, index asc) and the same arithmetic as route_kernel,
 // so the results are identical bit for bit.  Scores are staged in LDS (row stride E + 1: conflict-free); the results
@@ -150,11 +230,10 @@ __device__ inline int route_expert_of(const TqRouteIn& R, int t, int j, int E, i
 }
 
 // ---------------------------------------------------------------------------------------------
-// Permutation.  Assignments are cut into chunks of TQ_PERM_CHUNK; one wavefront per chunk.
-//   hist_kernel:    per-chunk histogram over experts (also validates the blob header)
-//   scan_kernel:    per expert, exclusive scan over chunks; offsets; row-tile tables
-//   scatter_kernel: stable placement, chunk by chunk, 64 assignments per round in order
-// permute_small_kernel does all of it in one wavefront when there is a single chunk (decode batches).
+// Permutation.
+//   permute_small_kernel: the whole of it in one wavefront, up to TQ_PERM_CHUNK assignments (decode batches)
+//   permute_place_kernel: larger batches, a workgroup per TQ_PLACE_CHUNK assignments; past TQ_PLACE_COUNT_SELF of them
+//                         after a launch of permute_hist_kernel
 //
 // Row-tile tables: for each tiling (32, 128, 16, 64 rows) the list of (expert, first slot) of every tile,
 // expert-major; their lengths go to ctrl[1], ctrl[2], ctrl[4], ctrl[5]; ctrl[3] = number of rows in total.
@@ -196,37 +275,53 @@ __device__ inline bool blob_header_ok(const TqBlobHeader* hdr, const TqBlobHeade
            hdr->expert_stride == expect.expert_stride;
 }
 
-__global__ void __launch_bounds__(64) hist_kernel(const int32_t* __restrict__ idx, int64_t n_assign, int E,
-                                                  int32_t* __restrict__ hist, int32_t* __restrict__ err_flag,
-                                                  const TqBlobHeader* __restrict__ hdr, TqBlobHeader expect,
-                                                  int check_blob)
+constexpr int TQ_PLACE_THREADS = 512, TQ_PLACE_WAVES = TQ_PLACE_THREADS / 64;
+constexpr int TQ_PLACE_CHUNK = 1024;                                   // assignments of one workgroup
+constexpr int TQ_PLACE_ROUNDS = TQ_PLACE_CHUNK / TQ_PLACE_THREADS;     // 64-wide rounds of one wave
+// Up to this many assignments every workgroup of permute_place_kernel counts all of them itself (at most eight loads
+// per thread, one launch); beyond, permute_hist_kernel counts each chunk once and the workgroups add up the counts.
+constexpr int TQ_PLACE_COUNT_SELF = 4096;
+
+// hist[b][e] = assignments of expert e in chunk b; hist[gridDim.x * E + b] = whether the chunk holds an invalid index
+__global__ void __launch_bounds__(TQ_PLACE_THREADS) permute_hist_kernel(const int32_t* __restrict__ idx, int64_t n_assign,
+                                                                        int E, int32_t* __restrict__ hist)
 {
-    extern __shared__ int32_t cnt[];
-    const int lane = threadIdx.x;
-    for (int e = lane; e < E; e += 64) cnt[e] = 0;
+    extern __shared__ int32_t cnt[];       // [E] | flag
+    const int tid = threadIdx.x, b = blockIdx.x;
+    int ev[TQ_PLACE_ROUNDS];
+#pragma unroll
+    for (int r = 0; r < TQ_PLACE_ROUNDS; ++r) {
+        const int64_t a = (int64_t)b * TQ_PLACE_CHUNK + r * TQ_PLACE_THREADS + tid;
+        ev[r] = a < n_assign ? idx[a] : E;
+    }
+    for (int e = tid; e <= E; e += TQ_PLACE_THREADS) cnt[e] = 0;
     __syncthreads();
-    const int64_t a0 = (int64_t)blockIdx.x * TQ_PERM_CHUNK;
-    bool bad = false;
-    for (int i = lane; i < TQ_PERM_CHUNK; i += 64) {
-        int64_t a = a0 + i;
-        if (a < n_assign) {
-            int e = idx[a];
-            if (e >= 0 && e < E) atomicAdd(&cnt[e], 1); else bad = true;
-        }
+#pragma unroll
+    for (int r = 0; r < TQ_PLACE_ROUNDS; ++r) {
+        const int64_t a = (int64_t)b * TQ_PLACE_CHUNK + r * TQ_PLACE_THREADS + tid;
+        if (ev[r] >= 0 && ev[r] < E) atomicAdd(&cnt[ev[r]], 1);
+        else if (a < n_assign) atomicOr(&cnt[E], 1);
     }
     __syncthreads();
-    for (int e = lane; e < E; e += 64) hist[(size_t)blockIdx.x * E + e] = cnt[e];
-    if (bad && err_flag) atomicOr(err_flag, TQ_FLAG_BIT_RANGE);
-    if (check_blob && blockIdx.x == 0 && lane == 0) {
-        if (!blob_header_ok(hdr, expect) && err_flag) atomicOr(err_flag, TQ_FLAG_BIT_BLOB);
-    }
+    for (int e = tid; e < E; e += TQ_PLACE_THREADS) hist[(size_t)b * E + e] = cnt[e];
+    if (tid == 0) hist[(size_t)gridDim.x * E + b] = cnt[E];
+}
+
+// orders one wavefront's LDS reads before its later writes (and the writes before the next reads) where its workgroup's
+// other waves do not take part
+__device__ inline void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // writes the row-tile tables from offs[0..ne] (LDS); `sm_base` is LDS scratch of TQ_N_TILINGS*(ne+1) ints;
-// tile_row0 holds 2 * TQ_N_TILINGS * rt_max ints: the first slots, then the row counts
+// tile_row0 holds 2 * TQ_N_TILINGS * rt_max ints: the first slots, then the row counts.  Workgroup `part` of `nparts`
+// (each with all of offs) writes its share of the entries; the first one writes the counts.
 __device__ inline void build_tile_tables(const int32_t* offs, int32_t* sm_base, int ne, int32_t* tile_e,
                                          int32_t* tile_row0, int rt_max, int32_t* ctrl, int tid, int nthreads,
-                                         int tilings = (1 << TQ_N_TILINGS) - 1)
+                                         int tilings, int part = 0, int nparts = 1)
 {
     // per tiling: tiles of expert e = ceil(count/bm); scan by wavefront `which` (or by wave 0 in turn)
     const int lane = tid & 63, wave = tid >> 6, nwaves = nthreads >> 6;
@@ -242,7 +337,10 @@ __device__ inline void build_tile_tables(const int32_t* offs, int32_t* sm_base, 
             if (i < ne) base[i] = carry + inc - v;
             carry += __shfl(inc, 63);
         }
-        if (lane == 0) { base[ne] = carry; ctrl[tile_ctrl_of(which)] = carry < rt_max ? carry : rt_max; }
+        if (lane == 0) {
+            base[ne] = carry;
+            if (part == 0) ctrl[tile_ctrl_of(which)] = carry < rt_max ? carry : rt_max;
+        }
     }
     __syncthreads();
     // one entry per thread: the expert of tile n is found by bisection over the per-expert first tiles
@@ -253,7 +351,7 @@ __device__ inline void build_tile_tables(const int32_t* offs, int32_t* sm_base, 
         const int total = base[ne] < rt_max ? base[ne] : rt_max;
         int32_t* te = tile_e + (size_t)which * rt_max;
         int32_t* tr = tile_row0 + (size_t)which * rt_max;
-        for (int n = tid; n < total; n += nthreads) {
+        for (int n = part * nthreads + tid; n < total; n += nparts * nthreads) {
             int lo = 0, hi = ne - 1;          // largest e with base[e] <= n (experts without rows share a base)
             while (lo < hi) {
                 int mid = (lo + hi + 1) >> 1;
@@ -267,225 +365,156 @@ __device__ inline void build_tile_tables(const int32_t* offs, int32_t* sm_base, 
     }
 }
 
-// One wavefront per routed expert: hist[b][e] becomes the number of assignments of expert e in chunks
-// before b, and counts[e] their total.
-__global__ void __launch_bounds__(64) chunk_scan_kernel(int32_t* __restrict__ hist, int nblk, int E,
-                                                        int32_t* __restrict__ counts)
+// Batches past one chunk: a workgroup places TQ_PLACE_CHUNK assignments, its eight waves 128 each.  It takes the number
+// of assignments of every expert in all chunks and in the chunks before its own (from `hist`, or by counting them when
+// hist is null), scans the totals into the offsets, turns its waves' own counts into cursors and places 64 assignments
+// per round, ranked by ballots: chunk-major, stable inside a chunk.  The work of every workgroup is the same few steps,
+// so nothing waits on one workgroup's scan: the five launches of one wave or one workgroup each that did this before
+// (clear, histogram, chunk scan, scan with tables, scatter) were latency: 9186 assignments of 64 experts 35 us in five launches,
+// 14 us in two here; 4096 assignments of 60 experts 17 us in one workgroup of 16 waves, 9.6 us here.
+__global__ void __launch_bounds__(TQ_PLACE_THREADS) permute_place_kernel(
+    const int32_t* __restrict__ idx, const float* __restrict__ w, int64_t n_assign, int E, int S, int T, int k,
+    const int32_t* __restrict__ hist, int32_t* __restrict__ offsets, int32_t* __restrict__ slot_of, int slot_stride,
+    int32_t* __restrict__ src_of, int32_t* __restrict__ row_token, float* __restrict__ row_w, int32_t* __restrict__ tile_e,
+    int32_t* __restrict__ tile_row0, int rt_max, int32_t* __restrict__ ctrl, int32_t* __restrict__ err_flag,
+    const TqBlobHeader* __restrict__ hdr, TqBlobHeader expect, int check_blob, int32_t* __restrict__ zero_buf, int zero_n,
+    int tilings)
 {
-    const int e = blockIdx.x, lane = threadIdx.x;
-    int run = 0;
-    for (int b0 = 0; b0 < nblk; b0 += 64) {
-        int b = b0 + lane;
-        int v = b < nblk ? hist[(size_t)b * E + e] : 0;
-        int inc = wave_incl_scan(v, lane);
-        if (b < nblk) hist[(size_t)b * E + e] = run + inc - v;
-        run += __shfl(inc, 63);
-    }
-    if (lane == 0) counts[e] = run;
-}
-
-// Single block of 1024 threads: expert offsets from the counts (left in offsets[1..E] by chunk_scan_kernel
-// when hist is null, else computed here from the few chunks of hist) and the row-tile tables.
-__global__ void __launch_bounds__(1024) scan_kernel(int32_t* __restrict__ hist, int nblk, int E, int S, int T,
-                                                    int32_t* __restrict__ offsets,
-                                                    int32_t* __restrict__ tile_e, int32_t* __restrict__ tile_row0,
-                                                    int rt_max, int32_t* __restrict__ ctrl, int check_blob)
-{
-    extern __shared__ int32_t sm[];   // counts[ne] | offs[ne+1] | tile scratch TQ_N_TILINGS*(ne+1)
+    extern __shared__ int32_t sm[];   // before[E] | totals[ne] | offs[ne+1] | tile scratch TQ_N_TILINGS*(ne+1) | cursor[waves][E] | flags
     const int ne = E + S;
-    int32_t* counts = sm;
-    int32_t* offs = sm + ne;
+    int32_t* before = sm;
+    int32_t* totals = before + E;
+    int32_t* offs = totals + ne;
     int32_t* tsm = offs + ne + 1;
+    int32_t* cursor = tsm + TQ_N_TILINGS * (ne + 1);
+    int32_t* flagw = cursor + TQ_PLACE_WAVES * E;
+    constexpr int NT = TQ_PLACE_THREADS;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (hist) {
-        // few chunks: the per-expert scan over chunks is one wave round per expert, done here
-        for (int e = wave; e < E; e += 16) {
-            int run = 0;
-            for (int b0 = 0; b0 < nblk; b0 += 64) {
-                int b = b0 + lane;
-                int v = b < nblk ? hist[(size_t)b * E + e] : 0;
-                int inc = wave_incl_scan(v, lane);
-                if (b < nblk) hist[(size_t)b * E + e] = run + inc - v;
-                run += __shfl(inc, 63);
-            }
-            if (lane == 0) counts[e] = run;
-        }
-        for (int s = tid; s < S; s += 1024) counts[E + s] = T;
-    } else {
-        for (int e = tid; e < ne; e += 1024) counts[e] = e < E ? offsets[e + 1] : T;
+    const int b = blockIdx.x, nb = gridDim.x;
+    const int64_t a_wave = (int64_t)b * TQ_PLACE_CHUNK + wave * (64 * TQ_PLACE_ROUNDS);
+
+    int ev[TQ_PLACE_ROUNDS];          // expert of this lane's assignment in each round; -1: invalid or past the end
+    float wv[TQ_PLACE_ROUNDS];
+#pragma unroll
+    for (int r = 0; r < TQ_PLACE_ROUNDS; ++r) {
+        const int64_t a = a_wave + r * 64 + lane;
+        ev[r] = a < n_assign ? idx[a] : -1;
+        wv[r] = (w && a < n_assign) ? w[a] : 1.0f;
+        if (ev[r] >= E) ev[r] = -1;
     }
+    TqBlobHeader hv = expect;
+    if (check_blob && b == 0 && tid == 0) hv = *hdr;
+    if (b == 0 && ctrl && tid < 64) ctrl[tid] = 0;
+    for (int i = b * NT + tid; i < zero_n; i += nb * NT) zero_buf[i] = 0;
+    for (int i = tid; i < E; i += NT) before[i] = 0;
+    for (int i = tid; i < ne; i += NT) totals[i] = i < E ? 0 : T;
+    for (int i = tid; i < TQ_PLACE_WAVES * E; i += NT) cursor[i] = 0;
+    if (tid == 0) *flagw = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < TQ_PLACE_ROUNDS; ++r)
+        if (ev[r] >= 0) atomicAdd(&cursor[wave * E + ev[r]], 1);
+    if (hist) {
+        // threads side by side on the experts, the chunks dealt to NT / ep groups of them
+        int ep = 1;
+        while (ep < E && ep < NT) ep *= 2;
+        const int np = NT / ep;
+        for (int e = tid & (ep - 1); e < E; e += ep) {
+            int tot = 0, bef = 0;
+#pragma unroll 8
+            for (int c = tid / ep; c < nb; c += np) {
+                const int v = hist[(size_t)c * E + e];
+                tot += v;
+                bef += c < b ? v : 0;
+            }
+            atomicAdd(&totals[e], tot);
+            atomicAdd(&before[e], bef);
+        }
+        if (b == 0)
+            for (int c = tid; c < nb; c += NT)
+                if (hist[(size_t)nb * E + c]) atomicOr(flagw, TQ_FLAG_BIT_RANGE);
+    } else {
+        constexpr int NL = TQ_PLACE_COUNT_SELF / NT;
+        int av[NL];
+#pragma unroll
+        for (int u = 0; u < NL; ++u) av[u] = idx[min((int64_t)u * NT + tid, n_assign - 1)];
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            const int64_t a = (int64_t)u * NT + tid;
+            if (a < n_assign) {
+                if (av[u] >= 0 && av[u] < E) {
+                    atomicAdd(&totals[av[u]], 1);
+                    if (a < (int64_t)b * TQ_PLACE_CHUNK) atomicAdd(&before[av[u]], 1);
+                } else {
+                    atomicOr(flagw, TQ_FLAG_BIT_RANGE);
+                }
+            }
+        }
+    }
+    if (check_blob && b == 0 && tid == 0 && !blob_header_ok(&hv, expect)) atomicOr(flagw, TQ_FLAG_BIT_BLOB);
     __syncthreads();
     if (wave == 0) {
-        int total = wave_excl_scan(counts, offs, ne, lane, [](int v) { return v; });
-        if (lane == 0 && ctrl) ctrl[3] = total;
+        const int total = wave_excl_scan(totals, offs, ne, lane, [](int v) { return v; });
+        if (b == 0 && lane == 0 && ctrl) ctrl[3] = total;
     }
     __syncthreads();
-    for (int e = tid; e <= ne; e += 1024) offsets[e] = offs[e];
-    if (tile_e) build_tile_tables(offs, tsm, ne, tile_e, tile_row0, rt_max, ctrl, tid, 1024);
-    // blob / descriptor mismatch (found by hist_kernel, which ran before): no row tiles and no rows, so that every
-    // later kernel of the forward ends at once instead of indexing the blob with the wrong geometry
-    __syncthreads();
-    if (check_blob && ctrl && tid == 0 && (ctrl[0] & TQ_FLAG_BIT_BLOB)) { ctrl[1] = 0; ctrl[2] = 0; ctrl[3] = 0; ctrl[4] = 0; ctrl[5] = 0; }
-}
-
-// stable placement of one chunk of assignments by one wavefront; cursor[e] (LDS) = next free slot of expert e.
-// `sync` orders this wavefront's reads of cursor before its writes and the writes before the next round's reads: a
-// workgroup barrier where the workgroup is this one wave, a wave-level fence where several waves each place a chunk
-// of their own (their trip counts differ, so they cannot meet at a workgroup barrier).
-template <typename Sync>
-__device__ inline void scatter_chunk(const int32_t* __restrict__ idx, const float* __restrict__ w, int64_t a0,
-                                     int64_t n_assign, int E, int k, int32_t* cursor, int lane,
-                                     int32_t* __restrict__ slot_of, int slot_stride, int32_t* __restrict__ src_of,
-                                     int32_t* __restrict__ row_token, float* __restrict__ row_w, Sync sync)
-{
-    for (int i0 = 0; i0 < TQ_PERM_CHUNK; i0 += 64) {
-        if (a0 + i0 >= n_assign) break;
-        int64_t a = a0 + i0 + lane;
-        int e = -1;
-        if (a < n_assign) {
-            e = idx[a];
-            if (e < 0 || e >= E) e = -1;
+    if (b == 0)
+        for (int e = tid; e <= ne; e += NT) offsets[e] = offs[e];
+    for (int e = tid; e < E; e += NT) {      // the waves' counts become their cursors
+        int run = offs[e] + before[e];
+#pragma unroll
+        for (int v = 0; v < TQ_PLACE_WAVES; ++v) {
+            const int c = cursor[v * E + e];
+            cursor[v * E + e] = run;
+            run += c;
         }
-        // rank of this lane among the lanes of the round that hold the same expert and come before it
+    }
+    if (tile_e) build_tile_tables(offs, tsm, ne, tile_e, tile_row0, rt_max, ctrl, tid, NT, tilings, b, nb);
+    __syncthreads();
+    int32_t* cur = cursor + wave * E;
+#pragma unroll
+    for (int r = 0; r < TQ_PLACE_ROUNDS; ++r) {
+        const int64_t a = a_wave + r * 64 + lane;
+        const int e = ev[r];
         // lanes holding the same expert: intersect, bit by bit of e, the ballots that agree with this lane
         uint64_t same = __ballot(e >= 0);
         for (int bit = 0; (1 << bit) < E; ++bit) {
             const uint64_t bal = __ballot((e >> bit) & 1);
             same &= ((e >> bit) & 1) ? bal : ~bal;
         }
-        const int before = __popcll(same & ((1ull << lane) - 1ull));
+        const int rank = __popcll(same & ((1ull << lane) - 1ull));
         const bool last = (same >> lane) <= 1ull;      // no higher lane with this expert
-        const int slot = e >= 0 ? cursor[e] + before : -1;
-        sync();
-        if (e >= 0 && last) cursor[e] = slot + 1;   // the last lane of each expert moves its cursor
-        sync();
+        const int slot = e >= 0 ? cur[e] + rank : -1;
+        wave_fence();
+        if (e >= 0 && last) cur[e] = slot + 1;         // the last lane of each expert moves its cursor
+        wave_fence();
         if (a < n_assign) {
-            int t = (int)(a / k), j = (int)(a % k);
+            const int t = (int)(a / k), j = (int)(a % k);
             if (slot_of) slot_of[(size_t)t * slot_stride + j] = slot;
             if (slot >= 0) {
                 if (src_of) src_of[slot] = (int32_t)a;
                 if (row_token) row_token[slot] = t;
-                if (row_w) row_w[slot] = w ? w[a] : 1.0f;
+                if (row_w) row_w[slot] = wv[r];
             }
         }
     }
-}
-
-__global__ void __launch_bounds__(64) scatter_kernel(const int32_t* __restrict__ idx, const float* __restrict__ w,
-                                                     int64_t n_assign, int E, int S, int T, int k,
-                                                     const int32_t* __restrict__ hist,
-                                                     const int32_t* __restrict__ offsets,
-                                                     int32_t* __restrict__ slot_of, int slot_stride,
-                                                     int32_t* __restrict__ src_of, int32_t* __restrict__ row_token,
-                                                     float* __restrict__ row_w)
-{
-    extern __shared__ int32_t cursor[];   // next free slot of each expert for this chunk
-    const int lane = threadIdx.x;
-    for (int e = lane; e < E; e += 64) cursor[e] = offsets[e] + hist[(size_t)blockIdx.x * E + e];
-    __syncthreads();
-    scatter_chunk(idx, w, (int64_t)blockIdx.x * TQ_PERM_CHUNK, n_assign, E, k, cursor, lane, slot_of, slot_stride,
-                  src_of, row_token, row_w, [] { __syncthreads(); });
     // shared experts: every token, weight 1, identity order
-    if (S > 0) {
-        const int64_t total = (int64_t)S * T;
-        for (int64_t i = (int64_t)blockIdx.x * 64 + lane; i < total; i += (int64_t)gridDim.x * 64) {
-            int s = (int)(i / T), t = (int)(i % T);
-            int slot = offsets[E + s] + t;
-            if (slot_of) slot_of[(size_t)t * slot_stride + k + s] = slot;
-            if (src_of) src_of[slot] = (int32_t)(n_assign + i);
-            if (row_token) row_token[slot] = t;
-            if (row_w) row_w[slot] = 1.0f;
-        }
-    }
-}
-
-// Batches of 2 to TQ_PERM_MID_CHUNKS chunks (a few thousand assignments): the whole permutation in ONE workgroup of 16
-// waves instead of four launches (clear, histogram, scan, scatter) that each cost a few microseconds of latency for
-// microseconds of work.  Wave w takes chunks w, w + 16, ...; the per-chunk histograms live in LDS and turn, after the
-// scans, into the per-chunk cursors.  Same slots as the several-launch path: chunk-major, stable inside a chunk.
-constexpr int TQ_PERM_MID_CHUNKS = 16;      // measured: 16 chunks -2 % on the step, 32 chunks +1 % against the several launches
-__global__ void __launch_bounds__(1024) permute_mid_kernel(const int32_t* __restrict__ idx, const float* __restrict__ w,
-                                                           int n_assign, int nblk, int E, int S, int T, int k,
-                                                           int32_t* __restrict__ offsets, int32_t* __restrict__ slot_of,
-                                                           int slot_stride, int32_t* __restrict__ src_of,
-                                                           int32_t* __restrict__ row_token, float* __restrict__ row_w,
-                                                           int32_t* __restrict__ tile_e, int32_t* __restrict__ tile_row0,
-                                                           int rt_max, int32_t* __restrict__ ctrl,
-                                                           int32_t* __restrict__ err_flag,
-                                                           const TqBlobHeader* __restrict__ hdr, TqBlobHeader expect,
-                                                           int check_blob, int32_t* __restrict__ zero_buf, int zero_n,
-                                                           int tilings)
-{
-    extern __shared__ int32_t sm[];   // counts[ne] | offs[ne+1] | tile scratch TQ_N_TILINGS*(ne+1) | flags[1] | hist[nblk][E]
-    const int ne = E + S;
-    int32_t* counts = sm;
-    int32_t* offs = counts + ne;
-    int32_t* tsm = offs + ne + 1;
-    int32_t* flagw = tsm + TQ_N_TILINGS * (ne + 1);
-    int32_t* hist = flagw + 1;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    TqBlobHeader hv = expect;
-    if (check_blob && tid == 0) hv = *hdr;
-    if (ctrl && tid < 64) ctrl[tid] = 0;
-    for (int i = tid; i < zero_n; i += 1024) zero_buf[i] = 0;
-    if (tid == 0) {
-        if (err_flag && err_flag != ctrl) *err_flag = 0;
-        *flagw = 0;
-    }
-    for (int i = tid; i < nblk * E; i += 1024) hist[i] = 0;
-    __syncthreads();
-    // per-chunk histograms
-    bool bad = false;
-    for (int b = wave; b < nblk; b += 16) {
-        for (int i = lane; i < TQ_PERM_CHUNK; i += 64) {
-            const int a = b * TQ_PERM_CHUNK + i;
-            if (a < n_assign) {
-                const int e = idx[a];
-                if (e >= 0 && e < E) atomicAdd(&hist[b * E + e], 1); else bad = true;
-            }
-        }
-    }
-    if (bad) atomicOr(flagw, TQ_FLAG_BIT_RANGE);
-    if (check_blob && tid == 0 && !blob_header_ok(&hv, expect)) atomicOr(flagw, TQ_FLAG_BIT_BLOB);
-    __syncthreads();
-    // per expert: exclusive scan over the chunks (at most 16: one round of a wave), total into counts
-    for (int e = wave; e < E; e += 16) {
-        const int v = lane < nblk ? hist[lane * E + e] : 0;
-        const int inc = wave_incl_scan(v, lane);
-        if (lane < nblk) hist[lane * E + e] = inc - v;
-        if (lane == 63) counts[e] = inc;
-    }
-    for (int sidx = tid; sidx < S; sidx += 1024) counts[E + sidx] = T;
-    __syncthreads();
-    if (wave == 0) {
-        const int total = wave_excl_scan(counts, offs, ne, lane, [](int v) { return v; });
-        if (lane == 0 && ctrl) ctrl[3] = total;
-    }
-    __syncthreads();
-    for (int e = tid; e <= ne; e += 1024) offsets[e] = offs[e];
-    if (tile_e) build_tile_tables(offs, tsm, ne, tile_e, tile_row0, rt_max, ctrl, tid, 1024, tilings);
-    for (int i = tid; i < nblk * E; i += 1024) hist[i] += offs[i % E];      // the chunks' cursors
-    __syncthreads();
-    for (int b = wave; b < nblk; b += 16)
-        scatter_chunk(idx, w, (int64_t)b * TQ_PERM_CHUNK, n_assign, E, k, hist + b * E, lane, slot_of, slot_stride, src_of,
-                      row_token, row_w, [] {
-                          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                          __builtin_amdgcn_wave_barrier();
-                          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                      });
-    for (int i = tid; i < S * T; i += 1024) {      // shared experts: every token, weight 1, identity order
-        const int sidx = i / T, t = i % T;
-        const int slot = offs[E + sidx] + t;
-        if (slot_of) slot_of[(size_t)t * slot_stride + k + sidx] = slot;
-        if (src_of) src_of[slot] = n_assign + i;
+    const int64_t n_sh = (int64_t)S * T;
+    for (int64_t i = (int64_t)b * NT + tid; i < n_sh; i += (int64_t)nb * NT) {
+        const int s = (int)(i / T), t = (int)(i % T);
+        const int slot = offs[E + s] + t;
+        if (slot_of) slot_of[(size_t)t * slot_stride + k + s] = slot;
+        if (src_of) src_of[slot] = (int32_t)(n_assign + i);
         if (row_token) row_token[slot] = t;
         if (row_w) row_w[slot] = 1.0f;
     }
-    const int flags = *flagw;
-    if (flags && tid == 0 && err_flag) atomicOr(err_flag, flags);
-    // a blob that does not belong to the descriptor: no row tiles and no rows, so that every later kernel of the
-    // forward ends at once instead of indexing the blob with the wrong geometry
-    if ((flags & TQ_FLAG_BIT_BLOB) && ctrl && tid == 0) { ctrl[1] = 0; ctrl[2] = 0; ctrl[3] = 0; ctrl[4] = 0; ctrl[5] = 0; }
+    if (b == 0 && tid == 0) {
+        const int flags = *flagw;
+        if (flags && err_flag) atomicOr(err_flag, flags);
+        // a blob that does not belong to the descriptor: no row tiles and no rows, so that every later kernel of the
+        // forward ends at once instead of indexing the blob with the wrong geometry
+        if ((flags & TQ_FLAG_BIT_BLOB) && ctrl) { ctrl[1] = 0; ctrl[2] = 0; ctrl[3] = 0; ctrl[4] = 0; ctrl[5] = 0; }
+    }
 }
 
 __device__ inline void permute_small_body(const int32_t* __restrict__ idx, const float* __restrict__ w,
@@ -694,13 +723,6 @@ __global__ void __launch_bounds__(64) permute_small_kernel(const int32_t* __rest
                        tile_row0, rt_max, ctrl, err_flag, hdr, expect, check_blob, zero_buf, zero_n, tilings);
 }
 
-__global__ void clear_ctrl_kernel(int32_t* ctrl, int32_t* err_flag, int32_t* zero_buf, int zero_n)
-{
-    if (threadIdx.x < 64 && ctrl) ctrl[threadIdx.x] = 0;
-    for (int i = threadIdx.x; i < zero_n; i += blockDim.x) zero_buf[i] = 0;
-    if (threadIdx.x == 0 && err_flag && err_flag != ctrl) *err_flag = 0;
-}
-
 }  // namespace
 
 tq_status tqi_launch_permute(const int32_t* topk_idx, const float* topk_w, int32_t T, int32_t E, int32_t S,
@@ -756,32 +778,18 @@ tq_status tqi_launch_permute(const int32_t* topk_idx, const float* topk_w, int32
                                (const TqBlobHeader*)blob, expect, check);
         TQ_CHECK_LAUNCH();
     }
-    const size_t sm_mid = ((size_t)ne + (ne + 1) + TQ_N_TILINGS * (ne + 1) + 1 + (size_t)nblk * E) * 4;
-    if (nblk <= TQ_PERM_MID_CHUNKS && sm_mid <= 64 * 1024 && (int64_t)S * T <= 0x3FFFFFFF) {
-        hipLaunchKernelGGL(permute_mid_kernel, dim3(1), dim3(1024), sm_mid, stream, topk_idx, topk_w, (int)n_assign, (int)nblk, E, S,
-                           T, k, offsets, slot_of, slot_stride, src_of, row_token, row_w, tile_e, tile_row0, rt_max, ctrl,
-                           err_flag, (const TqBlobHeader*)blob, expect, check, zero_buf, (int)zero_n, tilings);
-        TQ_CHECK_LAUNCH();
-        return TQ_OK;
-    }
-    if (ctrl) {
-        hipLaunchKernelGGL(clear_ctrl_kernel, dim3(1), dim3(64), 0, stream, ctrl, err_flag, zero_buf, (int)zero_n);
+    const unsigned nb = (unsigned)((n_assign + TQ_PLACE_CHUNK - 1) / TQ_PLACE_CHUNK);
+    const bool count_self = n_assign <= TQ_PLACE_COUNT_SELF;
+    if (!count_self) {      // the workspace's nblk x E words hold nb x E counts and nb flags: nb <= (nblk + 3) / 4, nblk > 16
+        hipLaunchKernelGGL(permute_hist_kernel, dim3(nb), dim3(TQ_PLACE_THREADS), (size_t)(E + 1) * 4, stream, topk_idx, n_assign, E,
+                           hist);
         TQ_CHECK_LAUNCH();
     }
-    hipLaunchKernelGGL(hist_kernel, dim3(nblk), dim3(64), (size_t)E * 4, stream, topk_idx, n_assign, E, hist,
-                       err_flag, (const TqBlobHeader*)blob, expect, check);
-    TQ_CHECK_LAUNCH();
-    const size_t sm_scan = ((size_t)ne + (ne + 1) + TQ_N_TILINGS * (ne + 1)) * 4;
-    const bool split_scan = nblk > 64;
-    if (split_scan) {
-        hipLaunchKernelGGL(chunk_scan_kernel, dim3(E), dim3(64), 0, stream, hist, nblk, E, offsets + 1);
-        TQ_CHECK_LAUNCH();
-    }
-    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), sm_scan, stream, split_scan ? nullptr : hist, nblk, E, S, T,
-                       offsets, tile_e, tile_row0, rt_max, ctrl, check && err_flag == ctrl ? 1 : 0);
-    TQ_CHECK_LAUNCH();
-    hipLaunchKernelGGL(scatter_kernel, dim3(nblk), dim3(64), (size_t)E * 4, stream, topk_idx, topk_w, n_assign, E,
-                       S, T, k, hist, offsets, slot_of, slot_stride, src_of, row_token, row_w);
+    // at most 64 KB: E <= 1024 and S <= 64 at every entry point
+    const size_t sm = ((size_t)E + ne + (ne + 1) + TQ_N_TILINGS * (ne + 1) + (size_t)TQ_PLACE_WAVES * E + 1) * 4;
+    hipLaunchKernelGGL(permute_place_kernel, dim3(nb), dim3(TQ_PLACE_THREADS), sm, stream, topk_idx, topk_w, n_assign, E, S, T, k,
+                       count_self ? nullptr : hist, offsets, slot_of, slot_stride, src_of, row_token, row_w, tile_e, tile_row0,
+                       rt_max, ctrl, err_flag, (const TqBlobHeader*)blob, expect, check, zero_buf, (int)zero_n, tilings);
     TQ_CHECK_LAUNCH();
     return TQ_OK;
 }
@@ -797,8 +805,10 @@ extern "C" tq_status tq_route(const float* logits, const float* bias, int32_t T,
     const int per_lane = (E + 63) / 64;
     const dim3 grid((T + 3) / 4), block(256);
     hipStream_t st = (hipStream_t)stream;
-    if (per_lane == 1) hipLaunchKernelGGL(route_kernel<1>, grid, block, 0, st, logits, bias, T, E, k, topk_idx, topk_w);
-    else if (per_lane == 2) hipLaunchKernelGGL(route_kernel<2>, grid, block, 0, st, logits, bias, T, E, k, topk_idx, topk_w);
+    const dim3 grid16((T + 15) / 16);
+    if (k <= 16 && E <= 64) hipLaunchKernelGGL(route_row_kernel<4>, grid16, block, 0, st, logits, bias, T, E, k, topk_idx, topk_w);
+    else if (k <= 16 && E <= 128) hipLaunchKernelGGL(route_row_kernel<8>, grid16, block, 0, st, logits, bias, T, E, k, topk_idx, topk_w);
+    else if (k <= 16 && E <= 256) hipLaunchKernelGGL(route_row_kernel<16>, grid16, block, 0, st, logits, bias, T, E, k, topk_idx, topk_w);
     else if (per_lane <= 4) hipLaunchKernelGGL(route_kernel<4>, grid, block, 0, st, logits, bias, T, E, k, topk_idx, topk_w);
     else hipLaunchKernelGGL(route_kernel<kMaxPerLane>, grid, block, 0, st, logits, bias, T, E, k, topk_idx, topk_w);
     TQ_CHECK_LAUNCH();
