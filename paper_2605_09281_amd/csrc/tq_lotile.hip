@@ -406,26 +406,34 @@ __global__ void __launch_bounds__(256) lt_gather_kernel(LtLayout L, const int32_
         const int bl = it / q4, c = (it % q4) * 4, b = b0 + bl;
         const int n = c / L.rp, rho = c % L.rp;
         float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-        for (int t = 0; t < k; ++t) {
-            if (tn[bl * k + t] != n) continue;
-            const float g = tg[bl * k + t];
-            const float* src = xproj + (size_t)b * ldx + tm[bl * k + t] * L.rp + rho;
-            float4 xp = {0.f, 0.f, 0.f, 0.f};
-            // planes is a power of two: four loads in flight at a time, added in ascending order
-            const size_t ps = (size_t)T * ldx;
-            int p = 0;
-            for (; p + 4 <= planes; p += 4) {
-                float4 v[4];
+        // the selections on this column tile first, then their loads: with the test in front of the loads a wave waited
+        // for memory once per selection that ANY of its lanes matched, as a rule all k of them (8192 tokens, top-8, 11 x 12
+        // tiles of rank 32: 14.7 -> 10.1 us)
+        for (int t0 = 0; t0 < k; t0 += 32) {
+            const int nt = min(32, k - t0);
+            uint32_t hits = 0;
+            for (int t = 0; t < nt; ++t) hits |= tn[bl * k + t0 + t] == n ? 1u << t : 0u;
+            for (; hits; hits &= hits - 1) {
+                const int t = t0 + __builtin_ctz(hits);
+                const float g = tg[bl * k + t];
+                const float* src = xproj + (size_t)b * ldx + tm[bl * k + t] * L.rp + rho;
+                float4 xp = {0.f, 0.f, 0.f, 0.f};
+                // planes is a power of two: four loads in flight at a time, added in ascending order
+                const size_t ps = (size_t)T * ldx;
+                int p = 0;
+                for (; p + 4 <= planes; p += 4) {
+                    float4 v[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const float4*>(src + (size_t)(p + u) * ps);
+                    for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const float4*>(src + (size_t)(p + u) * ps);
 #pragma unroll
-                for (int u = 0; u < 4; ++u) { xp.x += v[u].x; xp.y += v[u].y; xp.z += v[u].z; xp.w += v[u].w; }
+                    for (int u = 0; u < 4; ++u) { xp.x += v[u].x; xp.y += v[u].y; xp.z += v[u].z; xp.w += v[u].w; }
+                }
+                for (; p < planes; ++p) {
+                    const float4 v = *reinterpret_cast<const float4*>(src + (size_t)p * ps);
+                    xp.x += v.x; xp.y += v.y; xp.z += v.z; xp.w += v.w;
+                }
+                s0 = fmaf(g, xp.x, s0); s1 = fmaf(g, xp.y, s1); s2 = fmaf(g, xp.z, s2); s3 = fmaf(g, xp.w, s3);
             }
-            for (; p < planes; ++p) {
-                const float4 v = *reinterpret_cast<const float4*>(src + (size_t)p * ps);
-                xp.x += v.x; xp.y += v.y; xp.z += v.z; xp.w += v.w;
-            }
-            s0 = fmaf(g, xp.x, s0); s1 = fmaf(g, xp.y, s1); s2 = fmaf(g, xp.z, s2); s3 = fmaf(g, xp.w, s3);
         }
         if (sigma) {      // mixed-precision factors: X_proj was formed on U alone, Sigma scales its rank components
             const float4 sg = *reinterpret_cast<const float4*>(sigma + rho);
