@@ -233,7 +233,7 @@ __device__ inline int route_expert_of(const TqRouteIn& R, int t, int j, int E, i
 // Permutation.
 //   permute_small_kernel: the whole of it in one wavefront, up to TQ_PERM_CHUNK assignments (decode batches)
 //   permute_place_kernel: larger batches, a workgroup per TQ_PLACE_CHUNK assignments; past TQ_PLACE_COUNT_SELF of them
-//                         after a launch of permute_hist_kernel
+//                         after a launch of permute_hist_kernel (and of permute_scan_kernel where there are many counts)
 //
 // Row-tile tables: for each tiling (32, 128, 16, 64 rows) the list of (expert, first slot) of every tile,
 // expert-major; their lengths go to ctrl[1], ctrl[2], ctrl[4], ctrl[5]; ctrl[3] = number of rows in total.
@@ -280,7 +280,15 @@ constexpr int TQ_PLACE_CHUNK = 1024;                                   // assign
 constexpr int TQ_PLACE_ROUNDS = TQ_PLACE_CHUNK / TQ_PLACE_THREADS;     // 64-wide rounds of one wave
 // Up to this many assignments every workgroup of permute_place_kernel counts all of them itself (at most eight loads
 // per thread, one launch); beyond, permute_hist_kernel counts each chunk once and the workgroups add up the counts.
+// Measured, one launch against two: 2048 assignments of 8 / 128 experts 5.5 / 6.0 us against 7.4 / 7.9, 4096 6.1 / 6.3 against
+// 7.5 / 8.0; with 32 loads per thread 8192 take 8.3 / 7.9 against 7.6 / 8.4, 16384 10.9 / 8.9 against 7.6 / 9.0.
 constexpr int TQ_PLACE_COUNT_SELF = 4096;
+// From this many counts (chunks x experts) permute_scan_kernel adds them up; below, every workgroup of permute_place_kernel
+// adds up all of them, which saves that launch but reads (chunks)^2 x experts words in all.  Measured, without the launch against with it:
+// at 32768 counts 17.2 us against 16.9 (1024 experts), 12.8 / 12.8 (128), 14.0 / 14.3 (64), 63 / 44 (8); at a quarter of them
+// 14.1 / 16.2, 9.2 / 11.9, 8.9 / 12.4, 14.9 / 17.0; at four times 28.8 / 18.6, 48 / 23, 279 / 56 (8 times, 64 experts); 4 M assignments of
+// 1024 experts 4495 / 119.
+constexpr int64_t TQ_PLACE_SCAN_WORDS = 32768;
 
 // hist[b][e] = assignments of expert e in chunk b; hist[gridDim.x * E + b] = whether the chunk holds an invalid index
 __global__ void __launch_bounds__(TQ_PLACE_THREADS) permute_hist_kernel(const int32_t* __restrict__ idx, int64_t n_assign,
@@ -305,6 +313,51 @@ __global__ void __launch_bounds__(TQ_PLACE_THREADS) permute_hist_kernel(const in
     __syncthreads();
     for (int e = tid; e < E; e += TQ_PLACE_THREADS) hist[(size_t)b * E + e] = cnt[e];
     if (tid == 0) hist[(size_t)gridDim.x * E + b] = cnt[E];
+}
+
+// From TQ_PLACE_SCAN_WORDS counts on: hist[b][e] becomes the number of assignments of expert e in the chunks before b, and
+// hist[nb * E + nb + e] their total, so that a workgroup of permute_place_kernel reads 2 E words instead of all nb * E.
+// A thread owns one expert (of `ep` per workgroup, ep a power of two up to 32: whole lines of a row) and one of 1024 / ep runs of
+// consecutive chunks: it sums its run, the runs are scanned in LDS, and it rewrites its run.
+constexpr int TQ_SCAN_THREADS = 1024;
+__global__ void __launch_bounds__(TQ_SCAN_THREADS) permute_scan_kernel(int32_t* __restrict__ hist, int nb, int E, int ep)
+{
+    __shared__ int32_t sums[TQ_SCAN_THREADS];
+    const int tid = threadIdx.x, run = tid / ep, runs = TQ_SCAN_THREADS / ep;
+    const int e = blockIdx.x * ep + (tid & (ep - 1));
+    const int per = (nb + runs - 1) / runs;
+    const int64_t c0 = (int64_t)run * per;
+    const int n = e < E && c0 < nb ? (int)min((int64_t)per, nb - c0) : 0;
+    int32_t* h = hist + c0 * E + e;
+    int tot = 0;
+#pragma unroll 8
+    for (int i = 0; i < n; ++i) tot += h[(size_t)i * E];
+    sums[tid] = tot;
+    __syncthreads();
+    for (int off = ep; off < TQ_SCAN_THREADS; off *= 2) {
+        const int o = tid >= off ? sums[tid - off] : 0;
+        __syncthreads();
+        sums[tid] += o;
+        __syncthreads();
+    }
+    int before = sums[tid] - tot;
+    int i = 0;
+    for (; i + 8 <= n; i += 8) {
+        int v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = h[(size_t)(i + u) * E];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            h[(size_t)(i + u) * E] = before;
+            before += v[u];
+        }
+    }
+    for (; i < n; ++i) {
+        const int v = h[(size_t)i * E];
+        h[(size_t)i * E] = before;
+        before += v;
+    }
+    if (run == runs - 1 && e < E) hist[(size_t)nb * E + nb + e] = sums[tid];
 }
 
 // orders one wavefront's LDS reads before its later writes (and the writes before the next reads) where its workgroup's
@@ -366,15 +419,15 @@ __device__ inline void build_tile_tables(const int32_t* offs, int32_t* sm_base, 
 }
 
 // Batches past one chunk: a workgroup places TQ_PLACE_CHUNK assignments, its eight waves 128 each.  It takes the number
-// of assignments of every expert in all chunks and in the chunks before its own (from `hist`, or by counting them when
-// hist is null), scans the totals into the offsets, turns its waves' own counts into cursors and places 64 assignments
-// per round, ranked by ballots: chunk-major, stable inside a chunk.  The work of every workgroup is the same few steps,
+// of assignments of every expert in all chunks and in the chunks before its own (from `hist`, with `scanned` added up there
+// already, or by counting them when hist is null), scans the totals into the offsets, turns its waves' own counts into
+// cursors and places 64 assignments per round, ranked by ballots: chunk-major, stable inside a chunk.  The work of every workgroup is the same few steps,
 // so nothing waits on one workgroup's scan: the five launches of one wave or one workgroup each that did this before
 // (clear, histogram, chunk scan, scan with tables, scatter) were latency: 9186 assignments of 64 experts 35 us in five launches,
 // 14 us in two here; 4096 assignments of 60 experts 17 us in one workgroup of 16 waves, 9.6 us here.
 __global__ void __launch_bounds__(TQ_PLACE_THREADS) permute_place_kernel(
     const int32_t* __restrict__ idx, const float* __restrict__ w, int64_t n_assign, int E, int S, int T, int k,
-    const int32_t* __restrict__ hist, int32_t* __restrict__ offsets, int32_t* __restrict__ slot_of, int slot_stride,
+    const int32_t* __restrict__ hist, int scanned, int32_t* __restrict__ offsets, int32_t* __restrict__ slot_of, int slot_stride,
     int32_t* __restrict__ src_of, int32_t* __restrict__ row_token, float* __restrict__ row_w, int32_t* __restrict__ tile_e,
     int32_t* __restrict__ tile_row0, int rt_max, int32_t* __restrict__ ctrl, int32_t* __restrict__ err_flag,
     const TqBlobHeader* __restrict__ hdr, TqBlobHeader expect, int check_blob, int32_t* __restrict__ zero_buf, int zero_n,
@@ -414,7 +467,12 @@ __global__ void __launch_bounds__(TQ_PLACE_THREADS) permute_place_kernel(
 #pragma unroll
     for (int r = 0; r < TQ_PLACE_ROUNDS; ++r)
         if (ev[r] >= 0) atomicAdd(&cursor[wave * E + ev[r]], 1);
-    if (hist) {
+    if (hist && scanned) {
+        for (int e = tid; e < E; e += NT) {
+            totals[e] = hist[(size_t)nb * E + nb + e];
+            before[e] = hist[(size_t)b * E + e];
+        }
+    } else if (hist) {
         // threads side by side on the experts, the chunks dealt to NT / ep groups of them
         int ep = 1;
         while (ep < E && ep < NT) ep *= 2;
@@ -430,9 +488,6 @@ __global__ void __launch_bounds__(TQ_PLACE_THREADS) permute_place_kernel(
             atomicAdd(&totals[e], tot);
             atomicAdd(&before[e], bef);
         }
-        if (b == 0)
-            for (int c = tid; c < nb; c += NT)
-                if (hist[(size_t)nb * E + c]) atomicOr(flagw, TQ_FLAG_BIT_RANGE);
     } else {
         constexpr int NL = TQ_PLACE_COUNT_SELF / NT;
         int av[NL];
@@ -450,6 +505,12 @@ __global__ void __launch_bounds__(TQ_PLACE_THREADS) permute_place_kernel(
                 }
             }
         }
+    }
+    if (hist && b == 0) {
+        int bad = 0;
+#pragma unroll 8
+        for (int c = tid; c < nb; c += NT) bad |= hist[(size_t)nb * E + c];
+        if (bad) atomicOr(flagw, TQ_FLAG_BIT_RANGE);
     }
     if (check_blob && b == 0 && tid == 0 && !blob_header_ok(&hv, expect)) atomicOr(flagw, TQ_FLAG_BIT_BLOB);
     __syncthreads();
@@ -780,15 +841,23 @@ tq_status tqi_launch_permute(const int32_t* topk_idx, const float* topk_w, int32
     }
     const unsigned nb = (unsigned)((n_assign + TQ_PLACE_CHUNK - 1) / TQ_PLACE_CHUNK);
     const bool count_self = n_assign <= TQ_PLACE_COUNT_SELF;
-    if (!count_self) {      // the workspace's nblk x E words hold nb x E counts and nb flags: nb <= (nblk + 3) / 4, nblk > 16
+    const bool scan = !count_self && (int64_t)nb * E >= TQ_PLACE_SCAN_WORDS;
+    // the workspace's nblk x E words hold nb x E counts, nb flags and E totals: nblk >= 4 nb - 3 and nb >= 5 here
+    if (!count_self) {
         hipLaunchKernelGGL(permute_hist_kernel, dim3(nb), dim3(TQ_PLACE_THREADS), (size_t)(E + 1) * 4, stream, topk_idx, n_assign, E,
                            hist);
+        TQ_CHECK_LAUNCH();
+    }
+    if (scan) {
+        int ep = 1;
+        while (ep < E && ep < 32) ep *= 2;
+        hipLaunchKernelGGL(permute_scan_kernel, dim3((E + ep - 1) / ep), dim3(TQ_SCAN_THREADS), 0, stream, hist, (int)nb, E, ep);
         TQ_CHECK_LAUNCH();
     }
     // at most 64 KB: E <= 1024 and S <= 64 at every entry point
     const size_t sm = ((size_t)E + ne + (ne + 1) + TQ_N_TILINGS * (ne + 1) + (size_t)TQ_PLACE_WAVES * E + 1) * 4;
     hipLaunchKernelGGL(permute_place_kernel, dim3(nb), dim3(TQ_PLACE_THREADS), sm, stream, topk_idx, topk_w, n_assign, E, S, T, k,
-                       count_self ? nullptr : hist, offsets, slot_of, slot_stride, src_of, row_token, row_w, tile_e, tile_row0,
+                       count_self ? nullptr : hist, (int)scan, offsets, slot_of, slot_stride, src_of, row_token, row_w, tile_e, tile_row0,
                        rt_max, ctrl, err_flag, (const TqBlobHeader*)blob, expect, check, zero_buf, (int)zero_n, tilings);
     TQ_CHECK_LAUNCH();
     return TQ_OK;
