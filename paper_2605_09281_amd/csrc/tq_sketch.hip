@@ -263,7 +263,7 @@ __global__ void __launch_bounds__(NT, 4) sk_pass_kernel(float* __restrict__ W, i
 
 // Ends a pass: z[j] = inv * sum of the G partial sums of column j, inv = 1 / |q| from the G partial sums of squares
 // (0 if that is zero: the matrix has run out of rank); with u, u[i] = q[i] * inv as well.  Latency-bound: 64 columns per
-// workgroup, the partial sums in 16 groups side by side.
+// workgroup, the partial sums in 16 groups side by side; workgroups past the columns take their share of u.
 __global__ void __launch_bounds__(256) sk_finish_kernel(const float* __restrict__ partial, int G, int64_t cols,
                                                         const float* __restrict__ ssq, float* __restrict__ z,
                                                         const float* __restrict__ q, int64_t rows, float* __restrict__ u)
@@ -433,6 +433,10 @@ extern "C" tq_status tq_sketch_lowrank(float* W, int64_t rows, int64_t cols, int
         if (tqi_device_state(&ds) != TQ_OK) return TQ_ERR_HIP;      // (raised dynamic-LDS limits)
         const SketchShape& sh = P.shape;
         const unsigned fin = (unsigned)((cols + 63) / 64);
+        // where u is written the grid covers the rows as well, 256 per workgroup: on the few workgroups that a narrow matrix has
+        // columns for, u took longer than the passes (1000000 x 4, rank 4, no power iteration: 6.2 ms, now 2.5; 100000 x 64, rank 8:
+        // 1304 us, now 566; 16384 x 1024 267, now 261)
+        const unsigned fin_u = std::max(fin, (unsigned)std::min<int64_t>(1024, (rows + 255) / 256));
         int npend = 0;                 // the last npend deflations are not in W yet: u_k in U, p_k in V
         for (int rho = 0; rho < r; ++rho) {
             const float* x = sketch + (size_t)rho * cols;
@@ -444,7 +448,7 @@ extern "C" tq_status tq_sketch_lowrank(float* W, int64_t rows, int64_t cols, int
                 if (rc != TQ_OK) return rc;
                 if (write) npend = 0;
                 const bool last = i == it;      // p = W^T U = Sigma V, kept in V until sk_unit_kernel
-                hipLaunchKernelGGL(sk_finish_kernel, dim3(fin), dim3(256), 0, st, (const float*)partial, sh.wg, cols, (const float*)norms,
+                hipLaunchKernelGGL(sk_finish_kernel, dim3(last ? fin_u : fin), dim3(256), 0, st, (const float*)partial, sh.wg, cols, (const float*)norms,
                                    last ? V + (size_t)rho * cols : z, (const float*)q, rows, last ? U + (size_t)rho * rows : (float*)nullptr);
                 x = z;
             }
