@@ -419,8 +419,8 @@ __global__ void __launch_bounds__(256 * WM, (MT == 2 && WM == 1) ? 2 : (MT == 1 
     const int wg = blockIdx.x;
     const int ntiles = ctrl[ctrl_idx];
     const int nbx = (nb_count + 7) >> 3;
-    // (from 40 tiles on the remainder is too small for that, whatever the column count)
-    const bool by_cols = ntiles < 40 && ntiles * nbx * 6 <= ((ntiles + 7) >> 3) * nb_count * 5;
+    // (ceil(t / 8) <= (t + 7) / 8 and nbx >= nb / 8 make that impossible from 36 tiles on; the test keeps the products in 32 bits)
+    const bool by_cols = ntiles < 36 && ntiles * nbx * 6 <= ((ntiles + 7) >> 3) * nb_count * 5;
     int rt, nb;
     if (by_cols) {
         const int i = wg >> 3;
@@ -799,11 +799,9 @@ tq_status launch_main(const MGeom& G, const TqSection& sec, const uint8_t* blob,
     const size_t smem = (size_t)2 * mfma_chunk_units(MT, GS) * BM * ROWB + (size_t)2 * BM * 4;
     auto kern = moe_mfma_kernel<MT, WM, STAGE, GS, CW, G2>;      // dynamic-LDS limit: raised once per device by tqi_setup_mfma
     const int nb_count = (sec.pairs + 3) / 4;
-    // both ways of dealing the workgroups out fit (see the kernel); what neither uses ends at once.  The deal by columns needs
-    // 6 t nbx <= 5 ceil(t / 8) nb, and ceil(t / 8) < t / 8 + 1, hence t < 40 nb / (48 nbx - 5 nb) <= 40
-    const int nbx = (nb_count + 7) / 8;
-    const long cols_tiles = std::min<long>(row_tiles, 40l * nb_count / (48l * nbx - 5l * nb_count));
-    const long n_wg = std::max((long)((row_tiles + 7) / 8) * 8 * nb_count, cols_tiles * 8 * nbx);
+    // The deal by columns needs no more: it is taken where 6 t nbx <= 5 ceil(t / 8) nb, and its 8 t nbx ids are then at most
+    // (20 / 3) ceil(t / 8) nb.
+    const long n_wg = (long)((row_tiles + 7) / 8) * 8 * nb_count;
     if (n_wg > 0x7FFFFFFF || nb_count > 65535) return TQ_ERR_UNSUPPORTED;
     dim3 grid((unsigned)n_wg, 1, nsplit);
     hipLaunchKernelGGL(kern, grid, dim3(256 * WM), smem, st, G, sec, blob, xin, xaug, row_token, tile_e, tile_row0, offsets, ctrl,
