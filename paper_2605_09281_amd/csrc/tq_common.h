@@ -146,7 +146,7 @@ struct TqWorkspace {
     size_t row_src;     // int32 [A_tot]  assignment behind each slot: t * k + j (routed), T * k + s * T + t (shared expert s)
     size_t tile_e;      // int32 [4][RT]  expert of each row tile, for the 32-, 128-, 16- and 64-row tilings
     size_t tile_row0;   // int32 [4][RT]  first slot of each row tile, followed by int32 [4][RT] its number of rows
-    size_t hist;        // int32 [nblk][E] permutation scratch
+    size_t hist;        // nblk x E int32 of permutation scratch (used past 4096 assignments)
     size_t xaug_gu;     // bf16 [A_tot][ka_gu]   (bf16 path)
     size_t xaug_d;      // bf16 [A_tot][ka_d]
     size_t h;           // bf16 [A_tot][F]  or fp32 [A_tot][F]
@@ -166,7 +166,7 @@ struct TqWorkspace {
 };
 
 #define TQ_N_TILINGS 4      // row tilings with a tile table: 32, 128, 16, 64 rows (in this order)
-#define TQ_PERM_CHUNK 256   // assignments handled by one permutation block
+#define TQ_PERM_CHUNK 256   // assignments up to which one wave does the permutation, and unit of its scratch size
 #define TQ_MAX_SPLIT 8      // K-splits of the down projection on the small-tile path
 #define TQ_SKINNY_MAX_ROWS 1024   // assignment rows up to which the decode (16-row tile) path is considered
 #define TQ_AUG_SLICE_MAX_TILES 160   // 32-row tiles up to which the tiled kernels' pre-pass is cut over K
@@ -360,7 +360,9 @@ struct TqRouteIn {
 };
 inline bool tqi_route_fusable(int64_t T, int E, int S, int k, int nblk)
 {
-    // (one lane scans a token's E scores k times: beyond a few experts the routing kernel, a wave per token, is faster)
+    // One lane scans a token's E scores k times.  The line was measured against a routing kernel with a wave per token; against the one
+    // with 16 lanes per token the whole call of a small layer takes 30.4 us fused and 31.1 separate with 4 experts, 31.5 / 31.5 with 8,
+    // 52.9 / 52.3 with 12, 35.3 / 33.6 with 16 (16 or 32 tokens).
     return nblk == 1 && T >= 1 && T <= 64 && E <= 16 && T * k <= TQ_PERM_CHUNK && (int64_t)S * T <= 4096;
 }
 

@@ -17,8 +17,10 @@ struct PackGeom {
 // 512 bytes and the packed side in runs of 1 KB (CW x 256 bytes for dense codes), 128 bytes per thread in flight.  One
 // thread per packed word, which reads 8 bytes of a row of its own, measured 900 us on 8 experts of 4096 x 14336 (1.41 GB of
 // bytes to 0.70 GB of words: 2.3 TB/s); this form 339 us
-// (6.2 TB/s).
-// Row stride in LDS: 528 bytes, so that the 8-byte accesses of 32 rows fall into different banks.
+// (6.2 TB/s).  Rows shorter than eight chunks leave some of the loading threads idle: whole call on 128 experts of
+// 1024 x 512 207 us before, 88 now, on 64 of 512 x 256 (dense 2-bit codes) 28 / 18, on 8 of 256 x 512 19 / 12.
+// Row stride in LDS: 528 bytes is the 16-byte alignment that the b128 accesses need, and leaves two rows of 16 apart (of the 32
+// that a wave reads 8 bytes of at a time) on the same banks.
 constexpr int PK_CHUNKS = 8, PK_ROWB = 64 * PK_CHUNKS + 16;
 
 // the 32 codes of (pair, chunk, tile, lane) <-> CW words; v[w] = codes kk = 16 w + 8 hf + (0..7) as bytes
@@ -182,7 +184,8 @@ __device__ inline uint32_t zc_part(uint32_t sz, int which)
 // Scales and zero-points: a workgroup moves 64 groups of one column pair between the canonical rows and the sz words, and
 // on packing derives the pair's zc fragments from the same values.  Bound by memory: canonical rows are read in runs of
 // 128 bytes (one thread per word, strided by the number of groups, took 72 us for sz and another 90 us for zc on 8 experts of
-// 4096 x 14336, groups of 128; this form 35 us for both).
+// 4096 x 14336, groups of 128; this form 35 us for both).  Rows of fewer groups repeat the last one on the lanes past it; the whole
+// call's times on such layers stand at PK_CHUNKS.
 constexpr int SZ_GROUPS = 64;
 
 template <bool PACK>
@@ -252,7 +255,8 @@ __global__ void __launch_bounds__(256) sz_kernel(PackGeom G, uint8_t* __restrict
     }
 }
 
-// Factor fragments, one thread per 8-element fragment (B's in front of A's: one launch for both).  B:  Padding rows (rho >= r) are written as zero and skipped on unpack.
+// Factor fragments, one thread per 8-element fragment (B's in front of A's: one launch for both).
+// B: padding rows (rho >= r) are written as zero and skipped on unpack.
 // ET: uint16_t (fp16 bit patterns) or uint8_t (fp8 E4M3 codes): the layout is the same with 2- or 1-byte elements.
 template <bool PACK, typename ET>
 __device__ inline void bfrag_one(const PackGeom& G, uint8_t* __restrict__ blob, ET* __restrict__ B, size_t idx)
@@ -287,7 +291,7 @@ __device__ inline void bfrag_one(const PackGeom& G, uint8_t* __restrict__ blob, 
     }
 }
 
-// A:
+// A: padding columns (c >= NA or rho >= r) likewise.
 template <bool PACK, typename ET>
 __device__ inline void afrag_one(const PackGeom& G, uint8_t* __restrict__ blob, ET* __restrict__ A, size_t idx)
 {

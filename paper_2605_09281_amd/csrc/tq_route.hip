@@ -84,8 +84,9 @@ __global__ void __launch_bounds__(256) route_kernel(const float* __restrict__ lo
 // exchange values by DPP.  With a wave per token (route_kernel) each round is twelve exchanges through the LDS crossbar,
 // which is what that kernel is bound by: 8192 tokens of 128 experts, top-8, 15.4 us there and 5.6 us here (4 MB of scores: the rest is latency of the rounds).
 // A score is held as an integer that orders the same way, so a round is a maximum, then the lowest expert that has it:
-// the order of route_kernel (score desc, index asc; -0 counts as +0), and its arithmetic on the scores.  NaN orders below
-// every number, an expert already chosen (or past E) below that.
+// the order of route_kernel (score desc, index asc; -0 counts as +0), and its arithmetic on the scores.  An expert already
+// chosen (or past E) orders below everything.  NaN scores are not supported by the entry points: here they order below every number, in
+// the other two forms by where they stand.
 constexpr int32_t ROUTE_TAKEN = (int32_t)0x80000000, ROUTE_NAN = ROUTE_TAKEN + 1;
 __device__ inline int32_t route_key(float s)
 {
@@ -590,7 +591,7 @@ __device__ inline void permute_small_body(const int32_t* __restrict__ idx, const
                                                            int check_blob, int32_t* __restrict__ zero_buf, int zero_n,
                                                            int tilings)
 {
-    extern __shared__ int32_t sm[];   // counts[ne] | offs[ne+1] | cursor[E] | tile scratch 3*(ne+1)
+    extern __shared__ int32_t sm[];   // counts[ne] | offs[ne+1] | cursor[E] | tile scratch TQ_N_TILINGS*(ne+1)
     const int ne = E + S, lane = threadIdx.x;
     int32_t* counts = sm;
     int32_t* offs = counts + ne;
@@ -639,7 +640,7 @@ __device__ inline void permute_small_body(const int32_t* __restrict__ idx, const
     if (ctrl && lane == 0) ctrl[3] = total;
     if (tile_e) build_tile_tables(offs, tsm, ne, tile_e, tile_row0, rt_max, ctrl, lane, 64, tilings);
     __syncthreads();
-    // stable placement, 64 assignments per round in order (same ranking as scatter_chunk, from registers)
+    // stable placement, 64 assignments per round in order (same ranking as permute_place_kernel)
 #pragma unroll
     for (int j = 0; j < NR; ++j) {
         if (j * 64 >= n_assign) break;
@@ -748,7 +749,7 @@ __global__ void __launch_bounds__(64) pre_by_assign_kernel(TqPreByAssign P, cons
     pre_by_assign_block<FP8>(P, idx, T, E, k, blockIdx.x, threadIdx.x);
 }
 
-// The whole permutation for a few chunks of assignments in ONE wavefront (one launch instead of five); with
+// The whole permutation of at most TQ_PERM_CHUNK assignments in ONE wavefront and one launch; with
 // PRE != 0 the other workgroups of the launch compute the gate/up low-rank intermediate by assignment (1: fp16
 // factors, 2: fp8 factors).
 // With ROUTE the launch also does the routing (route_small; idx and w are then unused).
@@ -830,7 +831,7 @@ tq_status tqi_launch_permute(const int32_t* topk_idx, const float* topk_w, int32
         return TQ_OK;
     }
     if (route) return TQ_ERR_UNSUPPORTED;      // the caller routes by itself when the single-wave permutation does not run
-    if (n_pre > 0) {      // the permutation takes several launches: the pre-pass gets its own
+    if (n_pre > 0) {      // no launch of single waves to ride in: the pre-pass gets its own
         if (pre->fm.fp8)
             hipLaunchKernelGGL(pre_by_assign_kernel<true>, dim3((unsigned)n_pre), dim3(64), 0, stream, *pre, topk_idx, T, E, k,
                                (const TqBlobHeader*)blob, expect, check);

@@ -322,7 +322,11 @@ __global__ void __launch_bounds__(1024) sk_unit_kernel(float* __restrict__ V, in
 }
 
 // Shape of the fused pass for a row length: threads, float4 columns per thread, rows in work at a time; workgroups and
-// pending deflations that 156 KB of LDS per CU hold.  1024 threads per CU whatever the width.
+// pending deflations that 156 KB of LDS per CU hold.  1024 threads per CU whatever the width.  Whole calls of rank 8 with two
+// power iterations, a stream per product against this (us): 1024 x 1024 1384 / 255, 16384 x 1024 2021 / 686, 1024 x 2048
+// 897 / 256, 2048 x 4096 905 / 669, 32768 x 4096 5542 / 3096, 1024 x 8192 919 / 641, 4096 x 8192 1705 / 1037, 4096 x 8196
+// 1819 / 1024, 4096 x 16384 3034 / 1591, 4096 x 20000 3629 / 2269, 4096 x 32768 5644 / 3510, 16 x 32768 1273 / 360.  Matrices of so few
+// rows that a workgroup has one group of them (2048 x 4096, 1024 x 8192) write a row of partial sums per group and gain least.
 struct SketchShape {
     int nt, nc, rr, wg, maxpend;
     bool xlds;
