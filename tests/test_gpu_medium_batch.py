@@ -131,7 +131,7 @@ def test_many_experts_run_to_run_deterministic():
 @pytest.mark.parametrize("name,flags", [("g128_r32_shared", tq.TQ_FLAG_FORCE_LARGE_TILE), ("g64_r16_50_rows", tq.TQ_FLAG_FORCE_SMALL_TILE),
                                         ("40_experts_10_tokens", 0)], ids=["large_split", "tile32_sliced", "many_experts_decode"])
 def test_replayed_from_a_hip_graph(name, flags):
-    """The launches these batches add (slice sums, split planes, one-workgroup permutation, device-side deal) captured
+    """The launches these batches add (slice sums, split planes, permutation past one wave, device-side deal) captured
     in a HIP graph: every replay, with eager work in between, equals the eager result bit for bit."""
     cfg = WIDE.get(name) or MANY[name]
     layer = get_layer(cfg)
@@ -166,7 +166,7 @@ def test_replayed_from_a_hip_graph(name, flags):
 
 
 def test_blob_of_another_layer_in_a_mid_sized_batch():
-    """400 assignments (two chunks: the one-workgroup permutation) with a blob whose header does not match the
+    """400 assignments (past the one-wave permutation) with a blob whose header does not match the
     descriptor: flag bit 1 is set and the tile counts are cleared, so that no later kernel indexes the blob."""
     cfg = wide(1401, H=128, F=192, T=200, r=8)
     other = wide(1402, H=128, F=256, T=200, r=8)

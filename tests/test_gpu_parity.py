@@ -160,10 +160,9 @@ def test_permute_bit_exact(T, E, k, seed):
                                                  (5000, 1024, 3, 0, 17), (32768, 5, 1, 0, 18), (33, 128, 8, 0, 19),
                                                  (1365, 7, 3, 0, 21), (1366, 7, 3, 0, 22), (2048, 3, 2, 0, 23), (512, 250, 8, 0, 24)])
 def test_permute_mid_sized_batches_bit_exact(T, E, k, S_unused, seed):
-    """Batches of 2 to 129 chunks of 256 assignments: up to 16 chunks in the one-workgroup kernel (per-chunk
-    histograms and cursors in LDS), beyond on the several-launch permutation (chunk scan in the offsets kernel up to
-    64 chunks and in a kernel of its own beyond): ragged last chunks, empty experts, skewed loads, few and many
-    experts, 4095 / 4098 assignments on either side of the 16-chunk limit."""
+    """Batches of 257 to 32784 assignments, placed by workgroups of 1024 that count all assignments themselves (up to 4096) or
+    add up the counts of a launch of its own: ragged last chunks, empty experts, skewed loads, few and many
+    experts, 4095 / 4098 assignments on either side of that limit."""
     print(f"permute T={T} E={E} k={k}", flush=True)
     rng = np.random.default_rng(seed)
     p = rng.random(E) ** 3
