@@ -375,11 +375,9 @@ tq_status tqi_launch_permute(const int32_t* topk_idx, const float* topk_w, int32
                              int32_t* zero_buf, int32_t zero_n, hipStream_t stream,
                              const TqPreByAssign* pre = nullptr, int tilings = (1 << TQ_N_TILINGS) - 1,
                              const TqRouteIn* route = nullptr);
-// fills W.fac_ws with fp16 fragments (Sigma folded into the left factors) and the placement table (fp8 factors on the
-// tiled kernels)
-tq_status tqi_expand_fp8_factors(const TqLayout& L, const TqWorkspace& W, const uint8_t* blob, uint8_t* ws, hipStream_t stream);
-// fills W.zc_ws from the blob's scale / zero part (dense codes on the tiled kernels)
-tq_status tqi_derive_zc(const TqLayout& L, const TqWorkspace& W, const uint8_t* blob, uint8_t* ws, hipStream_t stream);
+// what the tiled kernels need beside the blob, in one launch: W.fac_ws with fp16 fragments (Sigma folded into the left factors) and the
+// placement table (fp8 factors); W.zc_ws from the blob's scale / zero part (dense codes)
+tq_status tqi_prepare_tiled(const TqLayout& L, const TqWorkspace& W, const uint8_t* blob, uint8_t* ws, hipStream_t stream);
 // whether the bf16 forward of this batch runs on the decode kernels, and whether its gate/up pre-pass is by assignment
 bool tqi_bf16_takes_skinny(const TqLayout& L, const TqWorkspace& W, int flags);
 inline bool tqi_pre_by_assign(const TqLayout& L, const TqWorkspace& W) { return L.r > 0 && W.a_tot <= TQ_PRE_ASSIGN_MAX_ROWS; }

@@ -361,13 +361,12 @@ __global__ void sig_kernel(PackGeom G, TqFactorMap fm, uint8_t* __restrict__ blo
 // fragments): left factors with Sigma folded in, A16 = fp16(fp8(A8) * sigma) (one rounding to nearest), right factors
 // exactly.  One thread per 8-element fragment of one block; blocks are experts (per-expert factors) or tiles.
 // which: 0 left factors, 1 right factors.
-__global__ void expand_fp8_kernel(PackGeom G, TqFactorMap src, TqFactorMap dstm, const uint8_t* __restrict__ blob,
-                                  uint8_t* __restrict__ fbase, int which, int n_blocks)
+__device__ inline void expand_fp8(const PackGeom& G, const TqFactorMap& src, const TqFactorMap& dstm, const uint8_t* __restrict__ blob,
+                                  uint8_t* __restrict__ fbase, int which, int n_blocks, size_t idx)
 {
     const size_t n_gu = which == 0 ? (size_t)G.gu.na_tiles * (G.gu.K / 16) * 64 : (size_t)G.gu.pairs * (G.r16 / 16) * 128;
     const size_t n_d = which == 0 ? (size_t)G.d.na_tiles * (G.d.K / 16) * 64 : (size_t)G.d.pairs * (G.r16 / 16) * 128;
     const size_t per = n_gu + n_d;
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= per * n_blocks) return;
     const int blk = (int)(idx / per);
     size_t w = idx % per;
@@ -400,30 +399,28 @@ __global__ void expand_fp8_kernel(PackGeom G, TqFactorMap src, TqFactorMap dstm,
 }
 
 // placement table of the expanded factors: the blob's own (shared factors) or the identity (per-expert factors)
-__global__ void expand_phi_kernel(TqFactorMap src, TqFactorMap dstm, const uint8_t* __restrict__ blob, uint8_t* __restrict__ fbase,
-                                  int n_exp)
+__device__ inline void expand_phi(const TqFactorMap& src, const TqFactorMap& dstm, const uint8_t* __restrict__ blob,
+                                  uint8_t* __restrict__ fbase, int n_exp, size_t e)
 {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n_exp) return;
+    if (e >= (size_t)n_exp) return;
     int32_t* dst = reinterpret_cast<int32_t*>(fbase + dstm.phi_off);
     if (src.shared) {
         const int32_t* p = reinterpret_cast<const int32_t*>(blob + src.phi_off);
         dst[2 * e] = p[2 * e]; dst[2 * e + 1] = p[2 * e + 1];
     } else {
-        dst[2 * e] = e; dst[2 * e + 1] = e;
+        dst[2 * e] = (int32_t)e; dst[2 * e + 1] = (int32_t)e;
     }
 }
 
 // The same zc fragments as sz_kernel derives, computed from the blob's own sz part into a buffer outside the blob (dense
 // codes on the tiled kernels: such blobs store no zc part).  One thread per (pair, block of 16 groups, tile, lane): it
 // reads its 8 scale / zero words once and writes the hi and the lo fragment.
-__global__ void zc_from_blob_kernel(PackGeom G, const uint8_t* __restrict__ blob, uint8_t* __restrict__ zc_ws,
-                                    size_t zc_stride, size_t zc_d_off)
+__device__ inline void zc_from_blob(const PackGeom& G, const uint8_t* __restrict__ blob, uint8_t* __restrict__ zc_ws,
+                                    size_t zc_stride, size_t zc_d_off, size_t idx)
 {
     const size_t n_gu = (size_t)G.gu.pairs * (G.gu.zfrag / 2) * 128;
     const size_t n_d = (size_t)G.d.pairs * (G.d.zfrag / 2) * 128;
     const size_t per_exp = n_gu + n_d;
-    size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= per_exp * G.n_exp) return;
     const int e = (int)(idx / per_exp);
     size_t w = idx % per_exp;
@@ -442,20 +439,35 @@ __global__ void zc_from_blob_kernel(PackGeom G, const uint8_t* __restrict__ blob
         const int grp = min(16 * gblock + 8 * hf + i, sec.groups - 1);
         v[i] = sz[(((size_t)pair * sec.groups + grp) * 2 + tile) * 32 + col];
     }
-    uint16_t hi16[8], lo16[8];
+    uint32_t hi[4], lo[4];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        const int grp = 16 * gblock + 8 * hf + i;
-        const bool live = grp < sec.groups;
-        hi16[i] = live ? (uint16_t)zc_part(v[i], 0) : (uint16_t)0;
-        lo16[i] = live ? (uint16_t)zc_part(v[i], 1) : (uint16_t)0;
+        const bool live = 16 * gblock + 8 * hf + i < sec.groups;
+        const uint32_t h = live ? zc_part(v[i], 0) : 0u, l = live ? zc_part(v[i], 1) : 0u;
+        if (i & 1) { hi[i >> 1] |= h << 16; lo[i >> 1] |= l << 16; }
+        else { hi[i >> 1] = h; lo[i >> 1] = l; }
     }
     // fragment f of (pair, tile, lane) sits at ((pair * zfrag + f) * 2 + tile) * 64 + lane, 8 values each
-    uint16_t* base = reinterpret_cast<uint16_t*>(zc_ws + (size_t)e * zc_stride + (is_d ? zc_d_off : 0));
-    uint16_t* dh = base + ((((size_t)pair * sec.zfrag + 2 * gblock) * 2 + tile) * 64 + lane) * 8;
-    uint16_t* dl = base + ((((size_t)pair * sec.zfrag + 2 * gblock + 1) * 2 + tile) * 64 + lane) * 8;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) { dh[i] = hi16[i]; dl[i] = lo16[i]; }
+    uint4* base = reinterpret_cast<uint4*>(zc_ws + (size_t)e * zc_stride + (is_d ? zc_d_off : 0));
+    base[(((size_t)pair * sec.zfrag + 2 * gblock) * 2 + tile) * 64 + lane] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+    base[(((size_t)pair * sec.zfrag + 2 * gblock + 1) * 2 + tile) * 64 + lane] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+}
+
+// What the tiled kernels read that follows from the blob alone, in one launch (the parts are independent; as launches of their own the small
+// ones took 4.6 us each: 24 us for fp8 factors and dense codes on a 66-expert layer, now 10): the placement table and the fp16
+// fragments of fp8 factors, the zero-point fragments that the blob does not store.  The parts are consecutive ranges of workgroups,
+// ending at end[0..3].
+struct PrepRanges { unsigned end[4]; };
+__global__ void __launch_bounds__(256) prep_kernel(PackGeom G, TqFactorMap src, TqFactorMap dstm, const uint8_t* __restrict__ blob,
+                                                   uint8_t* __restrict__ fbase, uint8_t* __restrict__ zc_ws, size_t zc_stride,
+                                                   size_t zc_d_off, PrepRanges R)
+{
+    const unsigned b = blockIdx.x;
+    auto idx = [&](unsigned first) { return (size_t)(b - first) * 256 + threadIdx.x; };
+    if (b < R.end[0]) expand_phi(src, dstm, blob, fbase, G.n_exp, idx(0));
+    else if (b < R.end[1]) expand_fp8(G, src, dstm, blob, fbase, 0, dstm.M, idx(R.end[0]));
+    else if (b < R.end[2]) expand_fp8(G, src, dstm, blob, fbase, 1, dstm.N, idx(R.end[1]));
+    else zc_from_blob(G, blob, zc_ws, zc_stride, zc_d_off, idx(R.end[2]));
 }
 
 // Shared 2D-tiled factors.  Left factors: one thread per 8-element fragment of block (section, m); the block has the
@@ -598,32 +610,23 @@ inline bool misaligned(const void* p, size_t a) { return ((uintptr_t)p & (a - 1)
 
 }  // namespace
 
-tq_status tqi_expand_fp8_factors(const TqLayout& L, const TqWorkspace& W, const uint8_t* blob, uint8_t* ws, hipStream_t stream)
+tq_status tqi_prepare_tiled(const TqLayout& L, const TqWorkspace& W, const uint8_t* blob, uint8_t* ws, hipStream_t stream)
 {
-    if (!L.fm.fp8 || W.fac_bytes == 0) return TQ_ERR_UNSUPPORTED;
+    const bool factors = L.fm.fp8 != 0, zc = L.cw != 4;
+    if ((factors && W.fac_bytes == 0) || (zc && W.zc_stride == 0)) return TQ_ERR_UNSUPPORTED;
+    if (!factors && !zc) return TQ_OK;
     const PackGeom G = make_geom(L);
-    uint8_t* fbase = ws + W.fac_ws;
-    const size_t per_a = ((size_t)L.gu.na_tiles * (L.gu.K / 16) + (size_t)L.d.na_tiles * (L.d.K / 16)) * 64;
-    const size_t per_b = ((size_t)L.gu.pairs + L.d.pairs) * (L.r16 / 16) * 128;
-    hipLaunchKernelGGL(expand_phi_kernel, dim3(blocks_for((size_t)(L.E + L.S))), dim3(256), 0, stream, L.fm, W.fac_fm, blob, fbase,
-                       L.E + L.S);
-    TQ_CHECK_LAUNCH();
-    hipLaunchKernelGGL(expand_fp8_kernel, dim3(blocks_for(per_a * W.fac_fm.M)), dim3(256), 0, stream, G, L.fm, W.fac_fm, blob, fbase,
-                       0, W.fac_fm.M);
-    TQ_CHECK_LAUNCH();
-    hipLaunchKernelGGL(expand_fp8_kernel, dim3(blocks_for(per_b * W.fac_fm.N)), dim3(256), 0, stream, G, L.fm, W.fac_fm, blob, fbase,
-                       1, W.fac_fm.N);
-    TQ_CHECK_LAUNCH();
-    return TQ_OK;
-}
-
-tq_status tqi_derive_zc(const TqLayout& L, const TqWorkspace& W, const uint8_t* blob, uint8_t* ws, hipStream_t stream)
-{
-    if (W.zc_stride == 0) return TQ_ERR_UNSUPPORTED;
-    const PackGeom G = make_geom(L);
-    const size_t n = ((size_t)L.gu.pairs * (L.gu.zfrag / 2) + (size_t)L.d.pairs * (L.d.zfrag / 2)) * 128 * (L.E + L.S);
-    hipLaunchKernelGGL(zc_from_blob_kernel, dim3(blocks_for(n)), dim3(256), 0, stream, G, blob, ws + W.zc_ws, W.zc_stride,
-                       W.zc_d_off);
+    PrepRanges R;
+    size_t n = 0;
+    auto part = [&](int i, size_t threads) { n += blocks_for(threads); R.end[i] = (unsigned)n; };
+    const size_t ne = L.E + L.S;
+    part(0, factors ? ne : 0);
+    part(1, factors ? (((size_t)L.gu.na_tiles * (L.gu.K / 16) + (size_t)L.d.na_tiles * (L.d.K / 16)) * 64) * W.fac_fm.M : 0);
+    part(2, factors ? (((size_t)L.gu.pairs + L.d.pairs) * (L.r16 / 16) * 128) * W.fac_fm.N : 0);
+    part(3, zc ? ((size_t)L.gu.pairs * (L.gu.zfrag / 2) + (size_t)L.d.pairs * (L.d.zfrag / 2)) * 128 * ne : 0);
+    if (n > 0x7FFFFFFF) return TQ_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL(prep_kernel, dim3((unsigned)n), dim3(256), 0, stream, G, L.fm, W.fac_fm, blob, ws + W.fac_ws, ws + W.zc_ws,
+                       W.zc_stride, W.zc_d_off, R);
     TQ_CHECK_LAUNCH();
     return TQ_OK;
 }
