@@ -139,19 +139,21 @@ moe_prefill_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob, con
         for (int p = 0; p < NP; ++p)
             *reinterpret_cast<u32x4*>(lds + buf * BUFB + p * RPP * ROWB + lds_wr) = xr[p];
     };
-    auto load_w = [&](WT (&dst)[2][WN], const WSrc& s, int u) {
+    auto load_wc = [&](WT (&dst)[2][WN], const WSrc& s, int u, int c) __attribute__((always_inline)) {      // chunk c of unit u
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < 2; ++t) {
+            if constexpr (CW == 4) {
+                dst[t][c] = s.codes[((size_t)(u * UC + c) * 2 + t) * 64 + lane];
+            } else {
 #pragma unroll
-            for (int c = 0; c < UC; ++c) {
-                if constexpr (CW == 4) {
-                    dst[t][c] = s.codes[((size_t)(u * UC + c) * 2 + t) * 64 + lane];
-                } else {
-#pragma unroll
-                    for (int d = 0; d < CW; ++d)
-                        dst[t][c * CW + d] = s.codes32[(((size_t)(u * UC + c) * 2 + t) * CW + d) * 64 + lane];
-                }
+                for (int d = 0; d < CW; ++d)
+                    dst[t][c * CW + d] = s.codes32[(((size_t)(u * UC + c) * 2 + t) * CW + d) * 64 + lane];
             }
+        }
+    };
+    auto load_w = [&](WT (&dst)[2][WN], const WSrc& s, int u) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < UC; ++c) load_wc(dst, s, u, c);
     };
     auto load_sz = [&](uint32_t (&dst)[NG][2], const WSrc& s, int u) {
 #pragma unroll
@@ -295,9 +297,11 @@ moe_prefill_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob, con
         const int nn_e = __builtin_amdgcn_readfirstlane(nn_e_v), nn_slot0 = __builtin_amdgcn_readfirstlane(nn_slot0_v);
 
         // ---- main units ----------------------------------------------------------------------------------
-        const bool upper = cur_rows > 32;
-        auto main_unit = [&](int mu, auto slot_tag) {
+        // A tile of at most 32 rows runs the MFMAs of its first row block only: two copies of the loop, since a branch around
+        // the second block's MFMAs in every step costs 3 % of a full tile.
+        auto main_unit = [&](int mu, auto slot_tag, auto upper_tag) __attribute__((always_inline)) {
             constexpr int SLOT = decltype(slot_tag)::value;
+            constexpr int NM = decltype(upper_tag)::value ? MT : 1;
 #ifndef TQ_PRIO_GS
 #define TQ_PRIO_GS 8
 #endif
@@ -309,34 +313,22 @@ moe_prefill_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob, con
             // the next item is fetched after the loop, where registers are free to recompute the row offsets)
             xsb = reinterpret_cast<const uint8_t*>(xin) + (size_t)min(mu + 1, nmain - 1) * UNIT_K * 2;
             load_x();
-            WT wc[2][WN];
+            // Two units ahead; past the end of this item that is unit SLOT of the next one, so that its units 0 and 1 land in
+            // slots 0 and 1 whatever the parity of the unit count.  A chunk's codes are requested right after the last use of
+            // those they replace: nothing has to be copied out of the way.
+            const bool here = mu + 2 < nmain;
+            const WSrc& ws = here ? cur : nxt;
+            const int wu = here ? mu + 2 : SLOT;
+            WT (&wc)[2][WN] = wq[SLOT];
             uint32_t szc[NG][2];
             // The copies are opaque moves: the slot is dead afterwards, so the prefetch below can land in the very
             // same registers.  Left to itself the compiler keeps the old values in place instead and renames the
             // slot, and then has to move freshly requested registers at the loop end, which waits for those loads.
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int c = 0; c < WN; ++c) {
-                    if constexpr (CW == 4) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) wc[t][c][i] = opaque_mov(wq[SLOT][t][c][i]);
-                    } else {
-                        wc[t][c] = opaque_mov(wq[SLOT][t][c]);
-                    }
-                }
-#pragma unroll
             for (int gi = 0; gi < NG; ++gi)
 #pragma unroll
                 for (int t = 0; t < 2; ++t) szc[gi][t] = opaque_mov(szq[SLOT][gi][t]);
-            {
-                // two units ahead; past the end of this item that is unit SLOT of the next one, so that its
-                // units 0 and 1 land in slots 0 and 1 whatever the parity of the unit count
-                const bool here = mu + 2 < nmain;
-                const WSrc& s = here ? cur : nxt;
-                const int u = here ? mu + 2 : SLOT;
-                load_w(wq[SLOT], s, u); load_sz(szq[SLOT], s, u);
-            }
+            load_sz(szq[SLOT], ws, wu);
             const int buf = gstep & 1;
             if (cur_active) {
                 bf16x8 xa[2][MT];
@@ -349,8 +341,7 @@ moe_prefill_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob, con
                         xa[kk & 1][mt] = f.v;
                     }
                 };
-                read_a(0, 0, 1);
-                if (upper) read_a(0, 1, MT);
+                read_a(0, 0, NM);
 #pragma unroll
                 for (int kidx = 0; kidx < US; ++kidx) {
                     const int gi = kidx / GS, ks = kidx % GS;
@@ -390,14 +381,15 @@ moe_prefill_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob, con
                     };
                     mfmas(0, 1);
                     if (ks == GS - 1) fold(0, 1);
-                    // a tile of at most 32 rows runs the MFMAs of its first row block only (one wave-uniform branch
-                    // around each block of the second one's)
-                    if (upper) {
+                    if constexpr (NM > 1) {
                         if (kidx + 1 < US) read_a(kidx + 1, 1, MT);
                         mfmas(1, MT);
                         if (ks == GS - 1) fold(1, MT);
                     }
+                    if (kidx % 4 == 3) load_wc(wq[SLOT], ws, wu, kidx / 4);
                 }
+            } else {
+                load_w(wq[SLOT], ws, wu);
             }
             if (mu + 1 < nmain) {
                 store_x((gstep + 1) & 1);
@@ -408,14 +400,18 @@ moe_prefill_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob, con
         // The first pair stands outside the loop (there are at least two units): the wait counts the compiler
         // derives at the loop head are the minimum over all ways in, and the way in from the augmented units has
         // fewer loads in flight than the steady state, which would shorten the prefetch distance of every unit.
-        main_unit(0, std::integral_constant<int, 0>{});
-        main_unit(1, std::integral_constant<int, 1>{});
-        int mu = 2;
-        for (; mu + 1 < nmain; mu += 2) {
-            main_unit(mu, std::integral_constant<int, 0>{});
-            main_unit(mu + 1, std::integral_constant<int, 1>{});
-        }
-        if (mu < nmain) main_unit(mu, std::integral_constant<int, 0>{});
+        auto main_loop = [&](auto upper_tag) __attribute__((always_inline)) {
+            main_unit(0, std::integral_constant<int, 0>{}, upper_tag);
+            main_unit(1, std::integral_constant<int, 1>{}, upper_tag);
+            int mu = 2;
+            for (; mu + 1 < nmain; mu += 2) {
+                main_unit(mu, std::integral_constant<int, 0>{}, upper_tag);
+                main_unit(mu + 1, std::integral_constant<int, 1>{}, upper_tag);
+            }
+            if (mu < nmain) main_unit(mu, std::integral_constant<int, 0>{}, upper_tag);
+        };
+        if (cur_rows > 32) main_loop(std::true_type{});
+        else main_loop(std::false_type{});
 
         // the first augmented unit of the next item and its correction operands travel during the epilogue
         // (when there is no next item this reloads the current one: harmless)
@@ -515,28 +511,14 @@ tq_status tqi_forward_prefill_stage(int stage, const TqLayout& L, const TqWorksp
     const int gs = L.g / 16;
     const TqSection& sec = stage == 0 ? L.gu : L.d;
     const int ka = stage == 0 ? W.ka_gu : W.ka_d;
-#define TQ_CASE(GSV)                                                                                                  \
-    case GSV:                                                                                                         \
-        return stage == 0 ? launch_prefill<0, GSV>(G, sec, blob, xin, xaug, row_token, tile_e, tile_row0, offsets, ctrl, \
-                                                   ctrl_idx, out, ka, st)                                             \
-                          : launch_prefill<1, GSV>(G, sec, blob, xin, xaug, row_token, tile_e, tile_row0, offsets, ctrl, \
-                                                   ctrl_idx, out, ka, st)
-    if (L.cw != 4) {      // dense codes: groups of 64 and 128
-#define TQ_DENSE(GSV, CWV)                                                                                                  \
+#define TQ_CASE(GSV, CWV)                                                                                                   \
     if (gs == GSV && L.cw == CWV)                                                                                           \
         return stage == 0 ? launch_prefill<0, GSV, CWV>(G, sec, blob, xin, xaug, row_token, tile_e, tile_row0, offsets, ctrl, \
                                                         ctrl_idx, out, ka, st)                                              \
                           : launch_prefill<1, GSV, CWV>(G, sec, blob, xin, xaug, row_token, tile_e, tile_row0, offsets, ctrl, \
                                                         ctrl_idx, out, ka, st)
-        TQ_DENSE(4, 3); TQ_DENSE(8, 3); TQ_DENSE(4, 2); TQ_DENSE(8, 2);
-#undef TQ_DENSE
-        return TQ_ERR_UNSUPPORTED;
-    }
-    switch (gs) {
-        TQ_CASE(2);
-        TQ_CASE(4);
-        TQ_CASE(8);
-    }
+    TQ_CASE(2, 4); TQ_CASE(4, 4); TQ_CASE(8, 4);
+    TQ_CASE(4, 3); TQ_CASE(8, 3); TQ_CASE(4, 2); TQ_CASE(8, 2);      // dense codes: groups of 64 and 128
 #undef TQ_CASE
     return TQ_ERR_UNSUPPORTED;
 }
