@@ -1009,8 +1009,15 @@ static bool bf16_large_tiles_rows(const TqLayout& L, int64_t a_tot, int flags)
     // 66-expert layers (hidden size 2048) between 24 rows (32-row kernel 4-5 % ahead) and 32 (large tiles 3 % ahead).
     // (Before the 32-row kernel was compiled for more waves per SIMD and its pre-pass cut over K, these crossovers
     // lay at 12 to 16 rows.)
+    // Rows alone are not enough where the whole call is small: the large tilings start up, derive and drain over a
+    // few long workgroups, 60-105 us whatever the layer, while the 32-row kernel's many short ones end at 45-90.  Below
+    // 2e9 multiplications per matrix (assignments x H x F) it is ahead by 10 to 30 % (10 experts of 512x3392, 303
+    // assignments: 68 against 104 us; 31 of 448x2816, 909: 68 against 93; 38 of 256x5504, 1361: 73 against 99; 28 of
+    // 896x1792, 1008, 1.6e9: 79 against 90); past it the large tilings are (38 of 896x704, 4000, 2.5e9: 101 against
+    // 76; 60 of 2048x1408, 1984, 5.7e9: 172 against 135).
     const int64_t avg_rows = a_tot / (L.E + L.S);
-    bool large = avg_rows >= (L.E + L.S <= 16 ? 30 : L.H <= 2048 ? 28 : 20);
+    bool large = avg_rows >= (L.E + L.S <= 16 ? 30 : L.H <= 2048 ? 28 : 20) &&
+                 a_tot * ((int64_t)L.H * L.F) >= 2000000000;
     if (flags & TQ_FLAG_FORCE_SMALL_TILE) large = false;
     if (flags & TQ_FLAG_FORCE_LARGE_TILE) large = true;
     return large;
@@ -1033,7 +1040,16 @@ bool tqi_bf16_rows_take_skinny(const TqLayout& L, int64_t a_tot, int flags)
     const int64_t avg_rows = a_tot / (L.E + L.S);
     const int ne = L.E + L.S;
     const bool few_rows = ne <= 32 ? avg_rows <= (ne <= 8 ? 12 : 10) : a_tot <= (L.H <= 2048 ? 8 : 3) * (int64_t)ne;
-    bool skinny = !bf16_large_tiles_rows(L, a_tot, flags) && few_rows && !(flags & TQ_FLAG_FORCE_SMALL_TILE);
+    // Each (tile, column pair) of the decode kernels is a workgroup of its own, F/32 pairs a tile: past some 320
+    // assignments they queue for the 256 CUs behind one another, and a wide F over a short H makes so many short ones
+    // that launching them is the time.  There the 32-row kernel is ahead (24 experts of 384x12032, 216 assignments: 83
+    // against 222 us; 64 of 256x13824, 144: 162 against 344; 91 of 512x8960, 69: 129 against 224; 112 of 896x6528, 252
+    // with the shared one: 275 against 430), with up to 16 assignments it is not whatever the widths (61 of 512x4864,
+    // T = 6: 45 against 53).  Codes in the dense form and fp8 factors leave the line where the rows put it: what the
+    // tiled kernels derive from such a blob costs more than that (119 experts of 384x10368, T = 10: 66 against 134).
+    const bool plain = L.cw == 4 && !L.fm.fp8;
+    const bool queues = plain && a_tot > 16 && (a_tot > 320 || L.F > 6 * L.H);
+    bool skinny = !bf16_large_tiles_rows(L, a_tot, flags) && few_rows && !queues && !(flags & TQ_FLAG_FORCE_SMALL_TILE);
     if (flags & TQ_FLAG_FORCE_SKINNY) skinny = true;
     // (dense codes and fp8 factors follow the same rule: the parts the tiled kernels derive per call are laid out in
     // the workspace exactly when this returns false)
