@@ -12,15 +12,15 @@ pytestmark = pytest.mark.gpu
 
 DECODE, SMALL, LARGE = tq.TQ_FLAG_FORCE_SKINNY, tq.TQ_FLAG_FORCE_SMALL_TILE, tq.TQ_FLAG_FORCE_LARGE_TILE
 CASES = {
-    "320_assignments": (wide(2501, E=41, k=4, H=256, F=384, T=80), DECODE),
-    "324_assignments": (wide(2502, E=41, k=4, H=256, F=384, T=81), SMALL),
-    "width_6_times_height": (wide(2503, E=8, H=256, F=1536, T=20), DECODE),
-    "width_past_6_times_height": (wide(2504, E=8, H=256, F=1600, T=20), SMALL),
-    "wide_16_assignments": (wide(2505, E=8, H=256, F=1600, T=8), DECODE),
-    "wide_18_assignments": (wide(2506, E=8, H=256, F=1600, T=9), SMALL),
-    "wide_dense_codes": (wide(2507, E=8, H=256, F=1600, T=9, bits=3, dense=True), DECODE),
-    "1906_by_1024_by_1024": (wide(2508, H=1024, F=1024, T=953), SMALL),
-    "1908_by_1024_by_1024": (wide(2509, H=1024, F=1024, T=954), LARGE),
+    "320_assignments": (wide(2701, E=41, k=4, H=256, F=384, T=80), DECODE),
+    "324_assignments": (wide(2702, E=41, k=4, H=256, F=384, T=81), SMALL),
+    "width_6_times_height": (wide(2703, E=8, H=256, F=1536, T=20), DECODE),
+    "width_past_6_times_height": (wide(2704, E=8, H=256, F=1600, T=20), SMALL),
+    "wide_16_assignments": (wide(2705, E=8, H=256, F=1600, T=8), DECODE),
+    "wide_18_assignments": (wide(2706, E=8, H=256, F=1600, T=9), SMALL),
+    "wide_dense_codes": (wide(2707, E=8, H=256, F=1600, T=9, bits=3, dense=True), DECODE),
+    "1906_by_1024_by_1024": (wide(2708, H=1024, F=1024, T=953), SMALL),
+    "1908_by_1024_by_1024": (wide(2709, H=1024, F=1024, T=954), LARGE),
 }
 
 
