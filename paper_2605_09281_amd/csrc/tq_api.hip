@@ -1,6 +1,6 @@
 // Host side of the C ABI: argument checks, workspace carve-up and the kernel sequence of
 // tq_moe_forward.  Nothing here allocates, frees or synchronises.
-#include "tq_common.h"
+#include "tq_prep.h"
 
 extern "C" const char* tq_status_str(tq_status s)
 {
@@ -247,14 +247,21 @@ tq_status forward_impl(const tq_layer_desc* desc, const void* packed, const void
     // the large tiles on the tiled ones; none on the fp32 path
     const int tilings = desc->act_dtype == TQ_ACT_FP32 ? 0 : tqi_bf16_takes_skinny(L, W, desc->flags) ? 1 << 2
                         : 1 << 0 | 1 << (L.g == 256 ? 1 : 3);
+    // dense codes and fp8 factors on the tiled kernels: what these read beside the blob is derived in the permutation's launch
+    TqPrep prep;
+    prep.n_waves = 0;
+    if (desc->act_dtype == TQ_ACT_BF16 && !tqi_bf16_takes_skinny(L, W, desc->flags)) {
+        const tq_status rp = tqi_make_prep(L, W, (const uint8_t*)packed, ws, &prep);
+        if (rp != TQ_OK) return rp;
+    }
     tq_status rc = tqi_launch_permute(topk_idx, topk_w, T, L.E, L.S, L.k, (int32_t*)(ws + W.offsets),
                                       (int32_t*)(ws + W.slot_of), L.k + L.S, (int32_t*)(ws + W.row_src),
                                       (int32_t*)(ws + W.row_token), (float*)(ws + W.row_w),
                                       (int32_t*)(ws + W.tile_e), (int32_t*)(ws + W.tile_row0), W.rt_max, ctrl,
                                       ctrl, (int32_t*)(ws + W.hist), W.nblk, packed, &L,
                                       (int32_t*)(ws + W.sk_cnt), W.sk_cnt_n, st, with_pre ? &pre : nullptr,
-                                      tilings,
-                                      route);
+                                      tilings, route,
+                                      &prep);
     if (rc != TQ_OK) return rc;
     tqi_record_stage(1, st);
     if (desc->act_dtype == TQ_ACT_FP32)

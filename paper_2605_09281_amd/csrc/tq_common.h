@@ -367,6 +367,7 @@ inline bool tqi_route_fusable(int64_t T, int E, int S, int k, int nblk)
 }
 
 // internal entry points implemented across the translation units (host side)
+struct TqPrep;      // (tq_prep.h)
 tq_status tqi_launch_permute(const int32_t* topk_idx, const float* topk_w, int32_t T, int32_t E, int32_t S,
                              int32_t k, int32_t* offsets, int32_t* slot_of, int32_t slot_stride,
                              int32_t* src_of, int32_t* row_token, float* row_w, int32_t* tile_e,
@@ -374,10 +375,10 @@ tq_status tqi_launch_permute(const int32_t* topk_idx, const float* topk_w, int32
                              int32_t* hist, int32_t nblk, const void* blob, const TqLayout* L,
                              int32_t* zero_buf, int32_t zero_n, hipStream_t stream,
                              const TqPreByAssign* pre = nullptr, int tilings = (1 << TQ_N_TILINGS) - 1,
-                             const TqRouteIn* route = nullptr);
-// what the tiled kernels need beside the blob, in one launch: W.fac_ws with fp16 fragments (Sigma folded into the left factors) and the
-// placement table (fp8 factors); W.zc_ws from the blob's scale / zero part (dense codes)
-tq_status tqi_prepare_tiled(const TqLayout& L, const TqWorkspace& W, const uint8_t* blob, uint8_t* ws, hipStream_t stream);
+                             const TqRouteIn* route = nullptr, const TqPrep* prep = nullptr);
+// what the tiled kernels need beside the blob, as work for the permutation's launch (n_waves 0: nothing): W.fac_ws with fp16 fragments
+// (Sigma folded into the left factors) and the placement table (fp8 factors); W.zc_ws from the blob's scale / zero part (dense codes)
+tq_status tqi_make_prep(const TqLayout& L, const TqWorkspace& W, const uint8_t* blob, uint8_t* ws, TqPrep* P);
 // whether the bf16 forward of this batch runs on the decode kernels, and whether its gate/up pre-pass is by assignment
 bool tqi_bf16_takes_skinny(const TqLayout& L, const TqWorkspace& W, int flags);
 inline bool tqi_pre_by_assign(const TqLayout& L, const TqWorkspace& W) { return L.r > 0 && W.a_tot <= TQ_PRE_ASSIGN_MAX_ROWS; }

@@ -1098,17 +1098,15 @@ tq_status tqi_forward_bf16(const TqLayout& L, const TqWorkspace& W, int flags, c
         return TQ_OK;
     }
 
-    // fp8 factors: the tiled kernels read fp16 fragments, expanded into the workspace for this call; dense codes: the blob stores no
-    // zero-point coefficient fragments, they are derived into the workspace
+    // fp8 factors: the tiled kernels read fp16 fragments, dense codes: zero-point coefficient fragments that the blob does not store;
+    // both are in the workspace, written in the permutation's launch
     if (L.cw != 4 && gs == 16) return TQ_ERR_UNSUPPORTED;
-    tq_status rc = tqi_prepare_tiled(L, W, blob, ws, stream);
-    if (rc != TQ_OK) return rc;
     if (L.fm.fp8) {
         G.fm = W.fac_fm;
         G.fm.fbase = ws + W.fac_ws;
     }
     if (L.cw != 4) { G.zc_ws = ws + W.zc_ws; G.zc_stride = W.zc_stride; G.zc_d_off = W.zc_d_off; }
-    rc = launch_aug<0>(G, L.gu, blob, x, row_token, tile_e, tile_row0, offsets, ctrl, xaug_gu, W.ka_gu, rt32,
+    tq_status rc = launch_aug<0>(G, L.gu, blob, x, row_token, tile_e, tile_row0, offsets, ctrl, xaug_gu, W.ka_gu, rt32,
                        reinterpret_cast<float*>(ws + W.tpart), W.tpart_bytes, stream);
     if (rc != TQ_OK) return rc;
     tqi_record_stage(2, stream);

@@ -1,16 +1,13 @@
 // tq_pack_weights / tq_unpack_weights: canonical expert weights <-> the packed blob whose layout
 // include/tileq.h specifies.  Pure index arithmetic; every element is moved bit for bit.
-#include "tq_device.h"
+#include "tq_prep.h"
 
 namespace {
 
+using tqprep::PackGeom;
+using tqprep::make_geom;
+using tqprep::zc_part;
 using tqdev::u32x4;
-
-struct PackGeom {
-    int32_t n_exp, H, F, g, r, r16, qmax, cw;
-    TqSection gu, d;
-    size_t expert_stride;
-};
 
 // Codes: a workgroup moves a span of up to eight 64-wide chunks of one column pair (64 canonical rows) between the
 // canonical bytes and the packed words, through LDS.  Bound by memory: canonical rows are read (written) in runs of
@@ -163,22 +160,6 @@ __global__ void __launch_bounds__(256) codes_kernel(PackGeom G, uint8_t* __restr
                     *reinterpret_cast<const u32x4*>(lds + (row0 + i * (256 / SEGS)) * PK_ROWB + seg * 16);
         }
     }
-}
-
-__device__ inline uint32_t bf16_rne_bits(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
-
-// bf16 hi (which 0) or lo (which 1) part of c = -scale * (128 + zero), the coefficient of the group sum of the
-// activations once the codes are fed to the MFMA as 128 + q; sz = scale | zero << 16 (fp16 bits)
-__device__ inline uint32_t zc_part(uint32_t sz, int which)
-{
-    const float s = __half2float(__ushort_as_half((uint16_t)(sz & 0xFFFF))), z = __half2float(__ushort_as_half((uint16_t)(sz >> 16)));
-    const float c = -s * (128.0f + z);
-    const uint32_t hi = bf16_rne_bits(c);
-    return which == 0 ? hi : bf16_rne_bits(c - __uint_as_float(hi << 16));
 }
 
 // Scales and zero-points: a workgroup moves 64 groups of one column pair between the canonical rows and the sz words, and
@@ -357,119 +338,6 @@ __global__ void sig_kernel(PackGeom G, TqFactorMap fm, uint8_t* __restrict__ blo
     else if (live) *src = __half_as_ushort(__float2half(*dst));      // exact: the value came from an fp16
 }
 
-// fp8 factor fragments of the blob -> fp16 fragments in the workspace, for the tiled kernels (which read fp16
-// fragments): left factors with Sigma folded in, A16 = fp16(fp8(A8) * sigma) (one rounding to nearest), right factors
-// exactly.  One thread per 8-element fragment of one block; blocks are experts (per-expert factors) or tiles.
-// which: 0 left factors, 1 right factors.
-__device__ inline void expand_fp8(const PackGeom& G, const TqFactorMap& src, const TqFactorMap& dstm, const uint8_t* __restrict__ blob,
-                                  uint8_t* __restrict__ fbase, int which, int n_blocks, size_t idx)
-{
-    const size_t n_gu = which == 0 ? (size_t)G.gu.na_tiles * (G.gu.K / 16) * 64 : (size_t)G.gu.pairs * (G.r16 / 16) * 128;
-    const size_t n_d = which == 0 ? (size_t)G.d.na_tiles * (G.d.K / 16) * 64 : (size_t)G.d.pairs * (G.r16 / 16) * 128;
-    const size_t per = n_gu + n_d;
-    if (idx >= per * n_blocks) return;
-    const int blk = (int)(idx / per);
-    size_t w = idx % per;
-    const bool is_d = w >= n_gu;
-    if (is_d) w -= n_gu;
-    const TqSection& sec = is_d ? G.d : G.gu;
-    const uint8_t* sp;        // the block's fp8 fragments
-    if (src.shared) sp = blob + (which == 0 ? src.apool[is_d] + (size_t)blk * src.astride[is_d] : src.bpool[is_d] + (size_t)blk * src.bstride[is_d]);
-    else sp = blob + TQ_HEADER_BYTES + (size_t)blk * G.expert_stride + (which == 0 ? sec.afrag : sec.bfrag);
-    uint8_t* dp = fbase + (which == 0 ? dstm.apool[is_d] + (size_t)blk * dstm.astride[is_d] : dstm.bpool[is_d] + (size_t)blk * dstm.bstride[is_d]);
-    const uint2 raw = reinterpret_cast<const uint2*>(sp)[w];
-    float sg = 1.f;
-    if (which == 0) {
-        // column of t this fragment belongs to: 32 ta + lane % 32; Sigma is stored per column (gate then up in GU)
-        const int lane = (int)(w & 63), ta = (int)((w >> 6) / (sec.K / 16));
-        const int c = 32 * ta + (lane & 31), na = is_d ? G.r16 : 2 * G.r16;
-        const float* sig = src.shared ? reinterpret_cast<const float*>(blob + src.sig_off[is_d])
-                                      : reinterpret_cast<const float*>(blob + TQ_HEADER_BYTES + (size_t)blk * G.expert_stride + sec.sig);
-        sg = c < na ? sig[c] : 0.f;
-    }
-    uint32_t o[4];
-#pragma unroll
-    for (int i = 0; i < 8; i += 2) {
-        const uint32_t b0 = ((i < 4 ? raw.x : raw.y) >> (8 * (i & 3))) & 0xFF, b1 = ((i < 4 ? raw.x : raw.y) >> (8 * ((i + 1) & 3))) & 0xFF;
-        const uint32_t h0 = __half_as_ushort(__float2half(tq_fp8_to_float(b0) * sg));
-        const uint32_t h1 = __half_as_ushort(__float2half(tq_fp8_to_float(b1) * sg));
-        o[i >> 1] = h0 | (h1 << 16);
-    }
-    reinterpret_cast<uint4*>(dp)[w] = make_uint4(o[0], o[1], o[2], o[3]);
-}
-
-// placement table of the expanded factors: the blob's own (shared factors) or the identity (per-expert factors)
-__device__ inline void expand_phi(const TqFactorMap& src, const TqFactorMap& dstm, const uint8_t* __restrict__ blob,
-                                  uint8_t* __restrict__ fbase, int n_exp, size_t e)
-{
-    if (e >= (size_t)n_exp) return;
-    int32_t* dst = reinterpret_cast<int32_t*>(fbase + dstm.phi_off);
-    if (src.shared) {
-        const int32_t* p = reinterpret_cast<const int32_t*>(blob + src.phi_off);
-        dst[2 * e] = p[2 * e]; dst[2 * e + 1] = p[2 * e + 1];
-    } else {
-        dst[2 * e] = (int32_t)e; dst[2 * e + 1] = (int32_t)e;
-    }
-}
-
-// The same zc fragments as sz_kernel derives, computed from the blob's own sz part into a buffer outside the blob (dense
-// codes on the tiled kernels: such blobs store no zc part).  One thread per (pair, block of 16 groups, tile, lane): it
-// reads its 8 scale / zero words once and writes the hi and the lo fragment.
-__device__ inline void zc_from_blob(const PackGeom& G, const uint8_t* __restrict__ blob, uint8_t* __restrict__ zc_ws,
-                                    size_t zc_stride, size_t zc_d_off, size_t idx)
-{
-    const size_t n_gu = (size_t)G.gu.pairs * (G.gu.zfrag / 2) * 128;
-    const size_t n_d = (size_t)G.d.pairs * (G.d.zfrag / 2) * 128;
-    const size_t per_exp = n_gu + n_d;
-    if (idx >= per_exp * G.n_exp) return;
-    const int e = (int)(idx / per_exp);
-    size_t w = idx % per_exp;
-    const bool is_d = w >= n_gu;
-    const TqSection& sec = is_d ? G.d : G.gu;
-    if (is_d) w -= n_gu;
-    const int lane = (int)(w & 63), tile = (int)((w >> 6) & 1);
-    const size_t ps = w >> 7;
-    const int nblocks = sec.zfrag / 2;
-    const int gblock = (int)(ps % nblocks), pair = (int)(ps / nblocks);
-    const int col = lane & 31, hf = lane >> 5;
-    const uint32_t* sz = reinterpret_cast<const uint32_t*>(blob + TQ_HEADER_BYTES + (size_t)e * G.expert_stride + sec.sz);
-    uint32_t v[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int grp = min(16 * gblock + 8 * hf + i, sec.groups - 1);
-        v[i] = sz[(((size_t)pair * sec.groups + grp) * 2 + tile) * 32 + col];
-    }
-    uint32_t hi[4], lo[4];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const bool live = 16 * gblock + 8 * hf + i < sec.groups;
-        const uint32_t h = live ? zc_part(v[i], 0) : 0u, l = live ? zc_part(v[i], 1) : 0u;
-        if (i & 1) { hi[i >> 1] |= h << 16; lo[i >> 1] |= l << 16; }
-        else { hi[i >> 1] = h; lo[i >> 1] = l; }
-    }
-    // fragment f of (pair, tile, lane) sits at ((pair * zfrag + f) * 2 + tile) * 64 + lane, 8 values each
-    uint4* base = reinterpret_cast<uint4*>(zc_ws + (size_t)e * zc_stride + (is_d ? zc_d_off : 0));
-    base[(((size_t)pair * sec.zfrag + 2 * gblock) * 2 + tile) * 64 + lane] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-    base[(((size_t)pair * sec.zfrag + 2 * gblock + 1) * 2 + tile) * 64 + lane] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
-}
-
-// What the tiled kernels read that follows from the blob alone, in one launch (the parts are independent; as launches of their own the small
-// ones took 4.6 us each: 24 us for fp8 factors and dense codes on a 66-expert layer, now 10): the placement table and the fp16
-// fragments of fp8 factors, the zero-point fragments that the blob does not store.  The parts are consecutive ranges of workgroups,
-// ending at end[0..3].
-struct PrepRanges { unsigned end[4]; };
-__global__ void __launch_bounds__(256) prep_kernel(PackGeom G, TqFactorMap src, TqFactorMap dstm, const uint8_t* __restrict__ blob,
-                                                   uint8_t* __restrict__ fbase, uint8_t* __restrict__ zc_ws, size_t zc_stride,
-                                                   size_t zc_d_off, PrepRanges R)
-{
-    const unsigned b = blockIdx.x;
-    auto idx = [&](unsigned first) { return (size_t)(b - first) * 256 + threadIdx.x; };
-    if (b < R.end[0]) expand_phi(src, dstm, blob, fbase, G.n_exp, idx(0));
-    else if (b < R.end[1]) expand_fp8(G, src, dstm, blob, fbase, 0, dstm.M, idx(R.end[0]));
-    else if (b < R.end[2]) expand_fp8(G, src, dstm, blob, fbase, 1, dstm.N, idx(R.end[1]));
-    else zc_from_blob(G, blob, zc_ws, zc_stride, zc_d_off, idx(R.end[2]));
-}
-
 // Shared 2D-tiled factors.  Left factors: one thread per 8-element fragment of block (section, m); the block has the
 // afrag layout, its columns being [gate factor | up factor] (r16 each) in section GU and the down factor in D.
 template <typename ET>
@@ -557,16 +425,6 @@ __global__ void phi_kernel(TqFactorMap fm, int n_exp, int n_padded, uint8_t* __r
     dst[2 * e + 1] = n;
 }
 
-inline PackGeom make_geom(const TqLayout& L)
-{
-    PackGeom G;
-    G.n_exp = L.E + L.S; G.H = L.H; G.F = L.F; G.g = L.g; G.r = L.r; G.r16 = L.r16;
-    G.qmax = (1 << L.bits) - 1;
-    G.cw = L.cw;
-    G.gu = L.gu; G.d = L.d; G.expert_stride = L.expert_stride;
-    return G;
-}
-
 inline unsigned blocks_for(size_t n) { return (unsigned)((n + 255) / 256); }
 
 template <bool PACK>
@@ -610,24 +468,25 @@ inline bool misaligned(const void* p, size_t a) { return ((uintptr_t)p & (a - 1)
 
 }  // namespace
 
-tq_status tqi_prepare_tiled(const TqLayout& L, const TqWorkspace& W, const uint8_t* blob, uint8_t* ws, hipStream_t stream)
+tq_status tqi_make_prep(const TqLayout& L, const TqWorkspace& W, const uint8_t* blob, uint8_t* ws, TqPrep* P)
 {
     const bool factors = L.fm.fp8 != 0, zc = L.cw != 4;
+    P->n_waves = 0;
     if ((factors && W.fac_bytes == 0) || (zc && W.zc_stride == 0)) return TQ_ERR_UNSUPPORTED;
     if (!factors && !zc) return TQ_OK;
-    const PackGeom G = make_geom(L);
-    PrepRanges R;
+    P->G = make_geom(L);
+    P->src = L.fm; P->dstm = W.fac_fm;
+    P->blob = blob; P->fbase = ws + W.fac_ws; P->zc_ws = ws + W.zc_ws;
+    P->zc_stride = W.zc_stride; P->zc_d_off = W.zc_d_off;
     size_t n = 0;
-    auto part = [&](int i, size_t threads) { n += blocks_for(threads); R.end[i] = (unsigned)n; };
+    auto part = [&](int i, size_t threads) { n += (threads + 63) / 64; P->end[i] = (unsigned)n; };
     const size_t ne = L.E + L.S;
     part(0, factors ? ne : 0);
     part(1, factors ? (((size_t)L.gu.na_tiles * (L.gu.K / 16) + (size_t)L.d.na_tiles * (L.d.K / 16)) * 64) * W.fac_fm.M : 0);
     part(2, factors ? (((size_t)L.gu.pairs + L.d.pairs) * (L.r16 / 16) * 128) * W.fac_fm.N : 0);
     part(3, zc ? ((size_t)L.gu.pairs * (L.gu.zfrag / 2) + (size_t)L.d.pairs * (L.d.zfrag / 2)) * 128 * ne : 0);
-    if (n > 0x7FFFFFFF) return TQ_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(prep_kernel, dim3((unsigned)n), dim3(256), 0, stream, G, L.fm, W.fac_fm, blob, ws + W.fac_ws, ws + W.zc_ws,
-                       W.zc_stride, W.zc_d_off, R);
-    TQ_CHECK_LAUNCH();
+    if (n > 0x3FFFFFFF) return TQ_ERR_UNSUPPORTED;
+    P->n_waves = (unsigned)n;
     return TQ_OK;
 }
 

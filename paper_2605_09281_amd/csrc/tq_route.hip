@@ -1,7 +1,7 @@
 // tq_route (top-k selection and routing weights) and the token -> expert permutation with
 // prefix-sum offsets (histogram, scan, stable scatter) that tq_permute exports and tq_moe_forward
 // runs as its first step.
-#include "tq_common.h"
+#include "tq_prep.h"
 
 namespace {
 
@@ -426,14 +426,23 @@ __device__ inline void build_tile_tables(const int32_t* offs, int32_t* sm_base, 
 // so nothing waits on one workgroup's scan: the five launches of one wave or one workgroup each that did this before
 // (clear, histogram, chunk scan, scan with tables, scatter) were latency: 9186 assignments of 64 experts 35 us in five launches,
 // 14 us in two here; 4096 assignments of 60 experts 17 us in one workgroup of 16 waves, 9.6 us here.
+// With PREP the workgroups past the first nb derive what the tiled kernels read beside the blob (tq_prep.h).
+struct NoPrep {};
+template <bool PREP>
 __global__ void __launch_bounds__(TQ_PLACE_THREADS) permute_place_kernel(
     const int32_t* __restrict__ idx, const float* __restrict__ w, int64_t n_assign, int E, int S, int T, int k,
     const int32_t* __restrict__ hist, int scanned, int32_t* __restrict__ offsets, int32_t* __restrict__ slot_of, int slot_stride,
     int32_t* __restrict__ src_of, int32_t* __restrict__ row_token, float* __restrict__ row_w, int32_t* __restrict__ tile_e,
     int32_t* __restrict__ tile_row0, int rt_max, int32_t* __restrict__ ctrl, int32_t* __restrict__ err_flag,
     const TqBlobHeader* __restrict__ hdr, TqBlobHeader expect, int check_blob, int32_t* __restrict__ zero_buf, int zero_n,
-    int tilings)
+    int tilings, int nb, std::conditional_t<PREP, TqPrep, NoPrep> P)
 {
+    if constexpr (PREP) {
+        if ((int)blockIdx.x >= nb) {
+            tq_prep_wave(P, (blockIdx.x - nb) * (TQ_PLACE_THREADS / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), threadIdx.x & 63);
+            return;
+        }
+    }
     extern __shared__ int32_t sm[];   // before[E] | totals[ne] | offs[ne+1] | tile scratch TQ_N_TILINGS*(ne+1) | cursor[waves][E] | flags
     const int ne = E + S;
     int32_t* before = sm;
@@ -444,7 +453,7 @@ __global__ void __launch_bounds__(TQ_PLACE_THREADS) permute_place_kernel(
     int32_t* flagw = cursor + TQ_PLACE_WAVES * E;
     constexpr int NT = TQ_PLACE_THREADS;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int b = blockIdx.x, nb = gridDim.x;
+    const int b = blockIdx.x;
     const int64_t a_wave = (int64_t)b * TQ_PLACE_CHUNK + wave * (64 * TQ_PLACE_ROUNDS);
 
     int ev[TQ_PLACE_ROUNDS];          // expert of this lane's assignment in each round; -1: invalid or past the end
@@ -751,7 +760,7 @@ __global__ void __launch_bounds__(64) pre_by_assign_kernel(TqPreByAssign P, cons
 
 // The whole permutation of at most TQ_PERM_CHUNK assignments in ONE wavefront and one launch; with
 // PRE != 0 the other workgroups of the launch compute the gate/up low-rank intermediate by assignment (1: fp16
-// factors, 2: fp8 factors).
+// factors, 2: fp8 factors) or derive what the tiled kernels read beside the blob (3).
 // With ROUTE the launch also does the routing (route_small; idx and w are then unused).
 template <int PRE, bool ROUTE>
 __global__ void __launch_bounds__(64) permute_small_kernel(const int32_t* __restrict__ idx, const float* __restrict__ w,
@@ -764,9 +773,15 @@ __global__ void __launch_bounds__(64) permute_small_kernel(const int32_t* __rest
                                                            int32_t* __restrict__ err_flag,
                                                            const TqBlobHeader* __restrict__ hdr, TqBlobHeader expect,
                                                            int check_blob, int32_t* __restrict__ zero_buf, int zero_n,
-                                                           TqPreByAssign P, int tilings, TqRouteIn R, int route_off)
+                                                           std::conditional_t<PRE == 3, TqPrep, TqPreByAssign> P, int tilings, TqRouteIn R,
+                                                           int route_off)
 {
-    if (PRE != 0 && blockIdx.x > 0) {
+    if constexpr (PRE == 3) {
+        if (blockIdx.x > 0) {
+            tq_prep_wave(P, blockIdx.x - 1, threadIdx.x);
+            return;
+        }
+    } else if (PRE != 0 && blockIdx.x > 0) {
         if (check_blob && !blob_header_ok(hdr, expect)) return;      // a blob of another layer is not indexed
         pre_by_assign_block<PRE == 2>(P, idx, T, E, k, blockIdx.x - 1, threadIdx.x, ROUTE ? &R : nullptr);
         return;
@@ -793,9 +808,10 @@ tq_status tqi_launch_permute(const int32_t* topk_idx, const float* topk_w, int32
                              int32_t* tile_row0, int32_t rt_max, int32_t* ctrl, int32_t* err_flag,
                              int32_t* hist, int32_t nblk, const void* blob, const TqLayout* L,
                              int32_t* zero_buf, int32_t zero_n, hipStream_t stream, const TqPreByAssign* pre, int tilings,
-                             const TqRouteIn* route)
+                             const TqRouteIn* route, const TqPrep* prep)
 {
     const int64_t n_assign = (int64_t)T * k;
+    const unsigned n_prep = prep ? prep->n_waves : 0;
     const int64_t n_pre = pre ? (int64_t)pre->a_tot * pre->n_slices * pre->na_tiles : 0;
     if (n_pre > 0x3FFFFFFF) return TQ_ERR_UNSUPPORTED;
     TqBlobHeader expect = {};
@@ -816,15 +832,18 @@ tq_status tqi_launch_permute(const int32_t* topk_idx, const float* topk_w, int32
         const int pre_kind = n_pre > 0 ? (pre->fm.fp8 ? 2 : 1) : 0;
         const TqRouteIn R = fused ? *route : TqRouteIn{};
         const TqPreByAssign P = n_pre > 0 ? *pre : TqPreByAssign{};
-#define TQ_PS(PREV, ROUTEV)                                                                                               \
-        hipLaunchKernelGGL((permute_small_kernel<PREV, ROUTEV>), dim3(1 + (unsigned)n_pre), dim3(64), sm, stream, topk_idx, \
+#define TQ_PS(PREV, ROUTEV, P, NV)                                                                                        \
+        hipLaunchKernelGGL((permute_small_kernel<PREV, ROUTEV>), dim3(1 + (unsigned)(NV)), dim3(64), sm, stream, topk_idx,  \
                            topk_w, (int)n_assign, E, S, T, k, offsets, slot_of, slot_stride, src_of, row_token, row_w,     \
                            tile_e, tile_row0, rt_max, ctrl, err_flag, (const TqBlobHeader*)blob, expect, check, zero_buf,  \
                            (int)zero_n, P, tilings, R, sm_words)
-        if (fused) {
-            if (pre_kind == 2) TQ_PS(2, true); else if (pre_kind == 1) TQ_PS(1, true); else TQ_PS(0, true);
+        if (n_prep > 0) {      // (a tiled path: no pre-pass by assignment)
+            if (n_pre > 0) return TQ_ERR_UNSUPPORTED;
+            if (fused) TQ_PS(3, true, *prep, n_prep); else TQ_PS(3, false, *prep, n_prep);
+        } else if (fused) {
+            if (pre_kind == 2) TQ_PS(2, true, P, n_pre); else if (pre_kind == 1) TQ_PS(1, true, P, n_pre); else TQ_PS(0, true, P, n_pre);
         } else {
-            if (pre_kind == 2) TQ_PS(2, false); else if (pre_kind == 1) TQ_PS(1, false); else TQ_PS(0, false);
+            if (pre_kind == 2) TQ_PS(2, false, P, n_pre); else if (pre_kind == 1) TQ_PS(1, false, P, n_pre); else TQ_PS(0, false, P, n_pre);
         }
 #undef TQ_PS
         TQ_CHECK_LAUNCH();
@@ -857,9 +876,13 @@ tq_status tqi_launch_permute(const int32_t* topk_idx, const float* topk_w, int32
     }
     // at most 64 KB: E <= 1024 and S <= 64 at every entry point
     const size_t sm = ((size_t)E + ne + (ne + 1) + TQ_N_TILINGS * (ne + 1) + (size_t)TQ_PLACE_WAVES * E + 1) * 4;
-    hipLaunchKernelGGL(permute_place_kernel, dim3(nb), dim3(TQ_PLACE_THREADS), sm, stream, topk_idx, topk_w, n_assign, E, S, T, k,
-                       count_self ? nullptr : hist, (int)scan, offsets, slot_of, slot_stride, src_of, row_token, row_w, tile_e, tile_row0,
-                       rt_max, ctrl, err_flag, (const TqBlobHeader*)blob, expect, check, zero_buf, (int)zero_n, tilings);
+#define TQ_PP(PREPV, P)                                                                                                     \
+    hipLaunchKernelGGL(permute_place_kernel<PREPV>, dim3(nb + (n_prep + TQ_PLACE_THREADS / 64 - 1) / (TQ_PLACE_THREADS / 64)), \
+                       dim3(TQ_PLACE_THREADS), sm, stream, topk_idx, topk_w, n_assign, E, S, T, k, count_self ? nullptr : hist, \
+                       (int)scan, offsets, slot_of, slot_stride, src_of, row_token, row_w, tile_e, tile_row0, rt_max, ctrl, err_flag, \
+                       (const TqBlobHeader*)blob, expect, check, zero_buf, (int)zero_n, tilings, (int)nb, P)
+    if (n_prep > 0) TQ_PP(true, *prep); else TQ_PP(false, NoPrep{});
+#undef TQ_PP
     TQ_CHECK_LAUNCH();
     return TQ_OK;
 }
