@@ -161,6 +161,10 @@ __global__ void __launch_bounds__(256) aug_kernel(MGeom G, TqSection sec, const 
 // aug_staged_kernel: the same result as aug_kernel for groups of at most 128, with the activation rows read in
 // whole 4-group chunks by all threads (each row's chunk is one contiguous run of up to 1 KB instead of
 // 16 bytes per lane and step) and staged through LDS; wave w of the workgroup owns group w of every chunk.
+// LDS: the staged rows or the reduction, then the group sums of two chunks: a row's sums go out four groups at a time and the
+// padding behind t in 16 bytes.  As stores of one value they were 192 of 2 bytes a row (K 4096, groups of 128), each to a line of
+// its own: 65536 rows 166 us, now 152 (t of 64 columns), 26624 rows of K 2048 38.5, now 33.
+__host__ __device__ constexpr int aug_stage_bytes(int gs) { return 32 * (4 * gs * 32 + 16) > 16384 ? 32 * (4 * gs * 32 + 16) : 16384; }
 template <int STAGE, int NAT, int GS>
 __global__ void __launch_bounds__(256, NAT == 1 ? 3 : 2) aug_staged_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob,
                                                             const uint16_t* __restrict__ xin,
@@ -180,6 +184,7 @@ __global__ void __launch_bounds__(256, NAT == 1 ? 3 : 2) aug_staged_kernel(MGeom
     constexpr int NP = 32 / RPP;           // passes
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];     // 32 x ROWB (one buffer: the next chunk waits
                                                                        // in registers); reused for the reduction
+    u32x4* gsb = reinterpret_cast<u32x4*>(lds + aug_stage_bytes(GS));  // [2][32] rows of a chunk's four group sums, hi | lo << 16
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int tile = blockIdx.x;
     if (tile >= ctrl[1]) return;
@@ -197,9 +202,6 @@ __global__ void __launch_bounds__(256, NAT == 1 ? 3 : 2) aug_staged_kernel(MGeom
     const u32x4* af = reinterpret_cast<const u32x4*>(na_tiles > 0 ? tq_afrag_base(blob, G.expert_stride, sec, G.fm, STAGE, e)
                                                                   : rec + sec.codes) + lane;
     const size_t af_live = na_tiles > 0 ? 1 : 0;
-    uint16_t* orow = xaug + (size_t)(slot0 + col) * ka;
-    const bool writer = (hf == 0) && (col < rows);
-
     const int prow = tid / SPR, seg = tid % SPR;
     uint32_t roff[NP];                     // byte offset of this thread's rows in xin
 #pragma unroll
@@ -267,14 +269,9 @@ __global__ void __launch_bounds__(256, NAT == 1 ? 3 : 2) aug_staged_kernel(MGeom
 #pragma unroll
                 for (int j = 0; j < 4; ++j) gsum += bf_lo(xa[ks].u[j]) + bf_hi(xa[ks].u[j]);
             const float tot = gsum + __shfl_xor(gsum, 32);
-            if (writer) {
-                const uint32_t hi = f2bf_bits(tot);
-                const uint32_t lo = f2bf_bits(tot - __uint_as_float(hi << 16));
-                uint16_t* zb = orow + 48 * (gi >> 4) + (gi & 15);        // block of 16 groups: hi | lo | hi
-                zb[0] = (uint16_t)hi;
-                zb[16] = (uint16_t)lo;
-                zb[32] = (uint16_t)hi;
-            }
+            const uint32_t hi = f2bf_bits(tot);
+            const uint32_t lo = f2bf_bits(tot - __uint_as_float(hi << 16));
+            if (hf == 0) reinterpret_cast<uint32_t*>(gsb + (c & 1) * 32 + col)[wave] = hi | (lo << 16);
             // NAT is the number of column tiles of t whenever there are factors at all, so one uniform test covers
             // the block (a test per MFMA turns into a copy of the accumulator per MFMA)
             if (na_tiles > 0) {
@@ -291,9 +288,19 @@ __global__ void __launch_bounds__(256, NAT == 1 ? 3 : 2) aug_staged_kernel(MGeom
                             acc[j0 + j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[ks].v, half8_to_bf8(aq[ks][j]), acc[j0 + j], 0, 0, 0);
                 }
             }
+        } else if (hf == 0) {
+            reinterpret_cast<uint32_t*>(gsb + (c & 1) * 32 + col)[wave] = 0;      // (padding up to whole blocks: zeros)
         }
         store_chunk();
         lds_barrier();
+        // the chunk's four group sums of every row, three stores of 8 bytes: block of 16 groups hi | lo | hi
+        if (tid < 96 && (tid & 31) < rows) {
+            const u32x4 q = gsb[(c & 1) * 32 + (tid & 31)];
+            const int part = tid >> 5;
+            const uint2 o = part == 1 ? make_uint2((q[0] >> 16) | (q[1] & 0xFFFF0000u), (q[2] >> 16) | (q[3] & 0xFFFF0000u))
+                                      : make_uint2((q[0] & 0xFFFFu) | (q[1] << 16), (q[2] & 0xFFFFu) | (q[3] << 16));
+            *reinterpret_cast<uint2*>(xaug + (size_t)(slot0 + (tid & 31)) * ka + 48 * (c >> 2) + 4 * (c & 3) + 16 * part) = o;
+        }
     }
     // sum the four waves' partial t tiles through LDS (the staging buffers are free now) and write them out
     float* red = reinterpret_cast<float*>(lds);       // [4][16][64]
@@ -317,12 +324,16 @@ __global__ void __launch_bounds__(256, NAT == 1 ? 3 : 2) aug_staged_kernel(MGeom
         }
     }
     // the padding must be finite (it meets zero weights in the MFMA): write zeros
-    if (writer && wave == 0 && blockIdx.y == 0) {
-        for (int gi = groups; gi < 16 * ((groups + 15) / 16); ++gi) {
-            uint16_t* zb = orow + 48 * (gi >> 4) + (gi & 15);
-            zb[0] = 0; zb[16] = 0; zb[32] = 0;
+    if (blockIdx.y == 0) {
+        const int nq = (nchunks + 3) / 4 * 4 - nchunks;      // chunks missing from the last block of 16 groups
+        for (int i = tid; i < 32 * 3 * nq; i += 256) {
+            const int row = i & 31, part = (i >> 5) % 3, c = nchunks + (i >> 5) / 3;
+            if (row < rows)
+                *reinterpret_cast<uint2*>(xaug + (size_t)(slot0 + row) * ka + 48 * (c >> 2) + 4 * (c & 3) + 16 * part) = make_uint2(0u, 0u);
         }
-        for (int kk = ZT + ((G.r > 0) ? NA : 0); kk < ka; ++kk) orow[kk] = 0;
+        const int k0 = ZT + ((G.r > 0) ? NA : 0), per = (ka - k0) / 8;      // (both multiples of 16)
+        for (int i = tid; i < per * rows; i += 256)
+            *reinterpret_cast<u32x4*>(xaug + (size_t)(slot0 + i / per) * ka + k0 + 8 * (i % per)) = u32x4{0u, 0u, 0u, 0u};
     }
 }
 
@@ -947,7 +958,7 @@ tq_status launch_aug(const MGeom& G, const TqSection& sec, const uint8_t* blob, 
         float* ts = (nsl > 1 && nat > 0) ? tslice : nullptr;
 #define TQ_AUGS(NATV, GSV)                                                                                          \
     hipLaunchKernelGGL((aug_staged_kernel<STAGE, NATV, GSV>), dim3(rt32, nsl), dim3(256),                       \
-                       std::max<size_t>((size_t)32 * (4 * GSV * 32 + 16), 4 * 16 * 64 * sizeof(float)) /* staging | reduction */, \
+                       aug_stage_bytes(GSV) + 2 * 32 * 16,                                                                \
                        st, G, sec, blob, xin, row_token, tile_e, tile_row0, offsets, ctrl, xaug, ka, cps, ts)
         if (nat <= 1) { if (gs == 8) TQ_AUGS(1, 8); else if (gs == 4) TQ_AUGS(1, 4); else TQ_AUGS(1, 2); }
         else if (nat == 2) { if (gs == 8) TQ_AUGS(2, 8); else if (gs == 4) TQ_AUGS(2, 4); else TQ_AUGS(2, 2); }
