@@ -163,10 +163,10 @@ __global__ void __launch_bounds__(256) aug_kernel(MGeom G, TqSection sec, const 
 // 16 bytes per lane and step) and staged through LDS; wave w of the workgroup owns group w of every chunk.
 // LDS: the staged rows or the reduction, then the group sums of two chunks: a row's sums go out four groups at a time and the
 // padding behind t in 16 bytes.  As stores of one value they were 192 of 2 bytes a row (K 4096, groups of 128), each to a line of
-// its own: 65536 rows 166 us, now 152 (t of 64 columns), 26624 rows of K 2048 38.5, now 33.
+// its own: 65536 rows 166 us, then 152 (t of 64 columns; 133 now), 26624 rows of K 2048 38.5, now 33.
 __host__ __device__ constexpr int aug_stage_bytes(int gs) { return 32 * (4 * gs * 32 + 16) > 16384 ? 32 * (4 * gs * 32 + 16) : 16384; }
 template <int STAGE, int NAT, int GS>
-__global__ void __launch_bounds__(256, NAT == 1 ? 3 : 2) aug_staged_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob,
+__global__ void __launch_bounds__(256, NAT == 1 || NAT * GS <= 16 ? 3 : 2) aug_staged_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob,
                                                             const uint16_t* __restrict__ xin,
                                                             const int32_t* __restrict__ row_token,
                                                             const int32_t* __restrict__ tile_e,
@@ -174,7 +174,7 @@ __global__ void __launch_bounds__(256, NAT == 1 ? 3 : 2) aug_staged_kernel(MGeom
                                                             const int32_t* __restrict__ offsets,
                                                             const int32_t* __restrict__ ctrl,
                                                             uint16_t* __restrict__ xaug, int ka, int cps,
-                                                            float* __restrict__ tslice)
+                                                            float* __restrict__ tslice, int runs)
 {
     constexpr int CK = 4 * GS * 16;        // contraction indices per chunk (four groups)
     constexpr int CKB = CK * 2;            // bytes of one row's chunk
@@ -186,8 +186,10 @@ __global__ void __launch_bounds__(256, NAT == 1 ? 3 : 2) aug_staged_kernel(MGeom
                                                                        // in registers); reused for the reduction
     u32x4* gsb = reinterpret_cast<u32x4*>(lds + aug_stage_bytes(GS));  // [2][32] rows of a chunk's four group sums, hi | lo << 16
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int tile = blockIdx.x;
-    if (tile >= ctrl[1]) return;
+    // workgroups go to the eight XCDs in turn: with `runs` each XCD takes neighbouring tiles, whose experts' factors stay in its L2
+    const int n_tiles = ctrl[1];
+    const int tile = runs ? (int)(blockIdx.x & 7) * ((n_tiles + 7) / 8) + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+    if (tile >= n_tiles || (runs && (int)(blockIdx.x >> 3) >= (n_tiles + 7) / 8)) return;
     const int e = tile_e[tile], slot0 = tile_row0[tile];
     const int rows = min(32, offsets[e + 1] - slot0);
     const int col = lane & 31, hf = lane >> 5;
@@ -241,9 +243,11 @@ __global__ void __launch_bounds__(256, NAT == 1 ? 3 : 2) aug_staged_kernel(MGeom
         // The factor fragments of this chunk are requested BEFORE the next chunk's rows: loads return in order, and
         // behind the gathered rows (memory-side cache or HBM) these L2 hits would wait for them.  Unconditional
         // with a clamped group, so that the compiler can count them.
-        // (four column tiles at groups of 128 are 128 registers of fragments: they come in two halves, the second one
-        // requested after the first one's MFMAs)
-        constexpr int NJ = (NAT * GS > 16) ? NAT / 2 : NAT;
+        // (from 16 fragments on they come in two halves, the second one requested after the first one's MFMAs: four column tiles at
+        // groups of 128 would be 128 registers, and 64 leave room for two waves per SIMD where 32 leave it for three: 65536 rows of
+        // 4096, two column tiles 152 -> 139.5 us; four column tiles at groups of 64 the same at 1024 tokens, 60 experts, 8192 tokens 861 -> 842
+        // a call together with the runs)
+        constexpr int NJ = (NAT > 1 && NAT * GS >= 16) ? NAT / 2 : NAT;
         u32x4 aq[GS][NJ];
         const int gic = min(gi, groups - 1);
         auto load_aq = [&](int j0) {
@@ -956,10 +960,14 @@ tq_status launch_aug(const MGeom& G, const TqSection& sec, const uint8_t* blob, 
             if (nat > 0 && (size_t)rt32 * nsl * natv * 4096 > tslice_bytes) { cps = nchunks; nsl = 1; }
         }
         float* ts = (nsl > 1 && nat > 0) ? tslice : nullptr;
+        // neighbouring tiles on one XCD: from more row tiles on than the chip holds at once (two or three a CU).  65536 rows of 4096, 2048 tiles:
+        // 152 -> 141.5 us, the factors of an expert then come once or twice from memory instead of eight times; below that nothing
+        // is shared and the next kernel finds the tiles in another L2: 16 experts of 256x512, 600 rows 37.6 -> 38.4 us a call.
+        const bool runs = rt32 >= 768;
 #define TQ_AUGS(NATV, GSV)                                                                                          \
-    hipLaunchKernelGGL((aug_staged_kernel<STAGE, NATV, GSV>), dim3(rt32, nsl), dim3(256),                       \
+    hipLaunchKernelGGL((aug_staged_kernel<STAGE, NATV, GSV>), dim3(runs ? (rt32 + 7) / 8 * 8 : rt32, nsl), dim3(256), \
                        aug_stage_bytes(GSV) + 2 * 32 * 16,                                                                \
-                       st, G, sec, blob, xin, row_token, tile_e, tile_row0, offsets, ctrl, xaug, ka, cps, ts)
+                       st, G, sec, blob, xin, row_token, tile_e, tile_row0, offsets, ctrl, xaug, ka, cps, ts, (int)runs)
         if (nat <= 1) { if (gs == 8) TQ_AUGS(1, 8); else if (gs == 4) TQ_AUGS(1, 4); else TQ_AUGS(1, 2); }
         else if (nat == 2) { if (gs == 8) TQ_AUGS(2, 8); else if (gs == 4) TQ_AUGS(2, 4); else TQ_AUGS(2, 2); }
         else { if (gs == 8) TQ_AUGS(4, 8); else if (gs == 4) TQ_AUGS(4, 4); else TQ_AUGS(4, 2); }
