@@ -325,7 +325,10 @@ def main():
             if i:
                 times.append(ev.elapsed_ms(0, 1))
         ms = sum(times) / len(times)
-        moved = rows * cols * 4.0 * (r * (it + 1) + 2)         # it + 1 reads of the matrix per rank; the residual read and written once
+        # reads of the matrix: `it` per rank and two per 16 ranks for their first products (64-bit column sums, up to 16384 columns), else
+        # it + 1 per rank; the residual read and written once
+        reads = r * it + 2 * -(-r // 16) if it > 0 and cols <= 16384 else r * (it + 1)
+        moved = rows * cols * 4.0 * (reads + 2)
         print(json.dumps({"sketch": {"rows": rows, "cols": cols, "rank": r, "power_iterations": it, "ms": round(ms, 3),
                                      "ms_per_rank": round(ms / r, 3),
                                      "roofline": {"bound": "hbm", "achieved": round(moved / ms / 1e6, 1), "peak": 8000.0,
