@@ -1063,15 +1063,15 @@ bool tqi_bf16_rows_take_skinny(const TqLayout& L, int64_t a_tot, int flags)
     // assignments they queue for the 256 CUs behind one another, and a wide F over a short H makes so many short ones
     // that launching them is the time.  There the 32-row kernel is ahead (24 experts of 384x12032, 216 assignments: 83
     // against 222 us; 64 of 256x13824, 144: 162 against 344; 91 of 512x8960, 69: 129 against 224; 112 of 896x6528, 252
-    // with the shared one: 275 against 430), with up to 16 assignments it is not whatever the widths (61 of 512x4864,
-    // T = 6: 45 against 53).  Codes in the dense form and fp8 factors leave the line where the rows put it: what the
+    // with the shared one: 275 against 430), with up to 16 assignments it is not whatever the widths (51 of 640x4736,
+    // 16: 64 against 54; just past the line 62 of 512x4864, 18: 53 against 45).  Codes in the dense form and fp8 factors leave the line where the rows put it: what the
     // tiled kernels derive from such a blob costs more than that (119 experts of 384x10368, T = 10: 66 against 134).
     const bool plain = L.cw == 4 && !L.fm.fp8;
     const bool queues = plain && a_tot > 16 && (a_tot > 320 || L.F > 6 * L.H);
     bool skinny = !bf16_large_tiles_rows(L, a_tot, flags) && few_rows && !queues && !(flags & TQ_FLAG_FORCE_SMALL_TILE);
     if (flags & TQ_FLAG_FORCE_SKINNY) skinny = true;
-    // (dense codes and fp8 factors follow the same rule: the parts the tiled kernels derive per call are laid out in
-    // the workspace exactly when this returns false)
+    // (the parts that the tiled kernels derive per call from dense codes and fp8 factors are laid out in the workspace
+    // exactly when this returns false)
     return skinny && a_tot <= TQ_SKINNY_MAX_ROWS && tqi_skinny_supported(L);
 }
 
