@@ -1059,16 +1059,12 @@ bool tqi_bf16_rows_take_skinny(const TqLayout& L, int64_t a_tot, int flags)
     const int64_t avg_rows = a_tot / (L.E + L.S);
     const int ne = L.E + L.S;
     const bool few_rows = ne <= 32 ? avg_rows <= (ne <= 8 ? 12 : 10) : a_tot <= (L.H <= 2048 ? 8 : 3) * (int64_t)ne;
-    // Each (tile, column pair) of the decode kernels is a workgroup of its own, F/32 pairs a tile: past some 320
-    // assignments they queue for the 256 CUs behind one another, and a wide F over a short H makes so many short ones
-    // that launching them is the time.  There the 32-row kernel is ahead (24 experts of 384x12032, 216 assignments: 83
-    // against 222 us; 64 of 256x13824, 144: 162 against 344; 91 of 512x8960, 69: 129 against 224; 112 of 896x6528, 252
-    // with the shared one: 275 against 430), with up to 16 assignments it is not whatever the widths (51 of 640x4736,
-    // 16: 64 against 54; just past the line 62 of 512x4864, 18: 53 against 45).  Codes in the dense form and fp8 factors leave the line where the rows put it: what the
-    // tiled kernels derive from such a blob costs more than that (119 experts of 384x10368, T = 10: 66 against 134).
-    const bool plain = L.cw == 4 && !L.fm.fp8;
-    const bool queues = plain && a_tot > 16 && (a_tot > 320 || L.F > 6 * L.H);
-    bool skinny = !bf16_large_tiles_rows(L, a_tot, flags) && few_rows && !queues && !(flags & TQ_FLAG_FORCE_SMALL_TILE);
+    // A size line beside the rows (plain layers to the 32-row kernel past 320 assignments, or past 16 where F > 6 H) was faster on wide
+    // layers of small H (24 experts of 384x12032, 216 assignments: 222 against 83 us) but is not taken: the 32-row kernel holds the group
+    // sums as bf16 pairs and multiplies by left factors rounded to bf16 where these kernels have fp32 sums and, up to 256
+    // assignments, the fp16 factors themselves (error against 64 bits 2.35e-3 -> up to 2.54e-3), and 60 experts of 2048x1408 were
+    // slower for it (404 assignments: 111 against 130 us).
+    bool skinny = !bf16_large_tiles_rows(L, a_tot, flags) && few_rows && !(flags & TQ_FLAG_FORCE_SMALL_TILE);
     if (flags & TQ_FLAG_FORCE_SKINNY) skinny = true;
     // (the parts that the tiled kernels derive per call from dense codes and fp8 factors are laid out in the workspace
     // exactly when this returns false)
