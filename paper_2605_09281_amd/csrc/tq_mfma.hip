@@ -1030,13 +1030,19 @@ static bool bf16_large_tiles_rows(const TqLayout& L, int64_t a_tot, int flags)
     // lay at 12 to 16 rows.)
     // Rows alone are not enough where the whole call is small: the large tilings start up, derive and drain over a
     // few long workgroups, 60-105 us whatever the layer, while the 32-row kernel's many short ones end at 45-90.  Below
-    // 2e9 multiplications per matrix (assignments x H x F) it is ahead by 10 to 30 % (10 experts of 512x3392, 303
-    // assignments: 68 against 104 us; 31 of 448x2816, 909: 68 against 93; 38 of 256x5504, 1361: 73 against 99; 28 of
-    // 896x1792, 1008, 1.6e9: 79 against 90); past it the large tilings are (38 of 896x704, 4000, 2.5e9: 101 against
-    // 76; 60 of 2048x1408, 1984, 5.7e9: 172 against 135).
+    // 2e9 multiplications per matrix (assignments x H x F) it takes 15 % less time on average, up to 45 % (10 experts of 512x3392, 303
+    // assignments: 68 against 104 us; 31 of 448x2816, 909: 68 against 93; 28 of 896x1792, 1008, 1.6e9: 79 against 90); past it the
+    // large tilings are ahead (38 of 896x704, 4000, 2.5e9: 101 against 76; 60 of 2048x1408, 1984, 5.7e9: 172 against 135).
+    // Except for the planes: up to 4096 assignments the 32-row kernel cuts the down projection over K into up to eight fp32 planes, and
+    // from 0.8 M values a plane (assignments x H) on, with a contraction too short to hide them (F below 1280), these cost more than is
+    // gained (26 of 1216x512, 2556: 101 against 86; 60 of 704x512, 4020: 76 against 68).  26000 batches of 8000 drawn layers below
+    // 2e9: without that exception 5.8 % are slower by more than 3 %, the worst by 29 %; with it 0.2 %, the worst by 6 %, and
+    // 95 % of the gain stays.  How many rows an expert holds does not decide: up to 8600 were measured,
+    // and past 4096 assignments (one plane) none is slower by more than 5 %.
     const int64_t avg_rows = a_tot / (L.E + L.S);
-    bool large = avg_rows >= (L.E + L.S <= 16 ? 30 : L.H <= 2048 ? 28 : 20) &&
-                 a_tot * ((int64_t)L.H * L.F) >= 2000000000;
+    const int64_t out = a_tot * L.H;
+    const bool short_call = out * L.F < 2000000000 && (a_tot > TQ_SPLITK_MAX_ROWS || out <= 800000 || L.F >= 1280);
+    bool large = avg_rows >= (L.E + L.S <= 16 ? 30 : L.H <= 2048 ? 28 : 20) && !short_call;
     if (flags & TQ_FLAG_FORCE_SMALL_TILE) large = false;
     if (flags & TQ_FLAG_FORCE_LARGE_TILE) large = true;
     return large;

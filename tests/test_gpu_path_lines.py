@@ -21,8 +21,15 @@ CASES = {
     "11_rows_of_16_experts": (wide(2711, E=16, H=256, F=384, T=88), SMALL),
     "8_rows_of_41_experts": (wide(2712, E=41, k=4, H=256, F=384, T=82), DECODE),
     "past_8_rows_of_41_experts": (wide(2713, E=41, k=4, H=256, F=384, T=83), SMALL),
-    "1906_by_1024_by_1024": (wide(2708, H=1024, F=1024, T=953), SMALL),
-    "1908_by_1024_by_1024": (wide(2709, H=1024, F=1024, T=954), LARGE),
+    "1524_by_1024_by_1280": (wide(2708, H=1024, F=1280, T=762), SMALL),
+    "1526_by_1024_by_1280": (wide(2709, H=1024, F=1280, T=763), LARGE),
+    # at most 4096 assignments, a short F: by the values of a plane, assignments x H
+    "planes_of_800000": (wide(2714, E=8, H=640, F=640, T=625), SMALL),
+    "planes_past_800000": (wide(2715, E=8, H=640, F=640, T=626), LARGE),
+    "planes_past_800000_F_1216": (wide(2716, E=8, H=640, F=1216, T=640), LARGE),
+    "planes_past_800000_F_1280": (wide(2717, E=8, H=640, F=1280, T=640), SMALL),
+    "4096_assignments": (wide(2718, E=8, H=256, F=320, T=2048), LARGE),
+    "4098_assignments": (wide(2719, E=8, H=256, F=320, T=2049), SMALL),
 }
 
 
