@@ -1,6 +1,8 @@
-"""tq_sketch_lowrank where every workgroup of a pass takes several steps: the loop that refills one register buffer while the
-other is in work and reuses each half of the reduction buffer, on every shape of the pass, with even and odd numbers of
-steps, a ragged last group of rows, and more ranks than pending deflations, so that passes that also store run through it."""
+"""tq_sketch_lowrank on every shape of the pass over the matrix, with few and many steps a workgroup: up to as many steps as there are row
+buffers nothing is requested twice (an instantiation of its own), beyond that a loop refills each buffer as soon as its rows are used, so what
+matters is the number of steps modulo the number of buffers; some workgroups have a step less, and the last group of rows is ragged.  And matrices
+so tall that a workgroup visits the vectors found so far more than once.  More than eight ranks, so that every count of earlier ranks that the
+kernels are instantiated for occurs."""
 import numpy as np
 import pytest
 import torch
@@ -43,27 +45,40 @@ def test_device_reference_is_the_oracle():
         assert np.max(np.abs(a.cpu().numpy() - b)) <= 1e-10
 
 
-# columns, rows that all workgroups take in one step, pending deflations that fit; the shape of the pass (threads, float4
-# columns per thread, rows at a time) follows from the columns alone
-SHAPES = {
-    "256x1x8": (64, 8192, 4), "256x1x8_full": (1024, 8192, 4), "256x2x4": (1028, 4096, 4), "256x4x2": (2052, 2048, 4),
-    "512x4x2": (4100, 1024, 4), "1024x4x2": (8196, 512, 4), "1024x4x2_three_pending": (12672, 512, 3),
-    "1024x4x2_two_pending": (16384, 512, 2), "1024x8x1": (16388, 256, 1), "1024x8x1_full": (32768, 256, 1),
-}
+# columns -> threads, rows in work at a time, row buffers, whether the column sums have 32 bits
+def pass_shape(cols):
+    nt = 256 if cols <= 4096 else 512 if cols <= 8192 else 1024
+    rr = 8 if cols <= 1024 else 4 if cols <= 2048 else 1
+    wide = cols > 16384
+    return nt, rr, 2 if wide or rr > 1 else 3, wide
 
 
-@pytest.mark.parametrize("steps", [4, 5])
-@pytest.mark.parametrize("name", list(SHAPES))
-def test_several_steps_per_workgroup(name, steps):
-    cols, per_step, pending = SHAPES[name]
-    # some workgroups take `steps` whole steps, some one fewer, and one ends inside a group of rows (single-row groups: none)
-    rows = (steps - 1) * per_step + per_step // 3 + (1 if per_step > 256 else 0)
-    r, it = pending + 2, 1
-    print(f"sketch {name} {rows}x{cols} r={r}", flush=True)
+def steps_of(rows, cols):
+    """Steps of the first workgroup, and whether another has one less."""
+    nt, rr, _, wide = pass_shape(cols)
+    wg = min(256 * 1024 // nt, max(256 if wide else 128, min(256, -(-rows // 16)), -(-rows // 32)), -(-rows // rr))
+    groups = -(-rows // rr)
+    return -(-groups // wg), groups % wg != 0
+
+
+def rows_for(steps, cols):
+    rr = pass_shape(cols)[1]
+    for rows in range(100 + (rr > 1), 60000, 31):
+        if steps_of(rows, cols) == (steps, steps > 1) and (rr == 1 or rows % rr):
+            return rows
+    raise AssertionError((steps, cols))
+
+
+COLS = [64, 1024, 1028, 2052, 4100, 8196, 12672, 16384, 16388, 32768]
+
+
+def check(rows, cols, r, it):
+    print(f"sketch {rows}x{cols} r={r} it={it}", flush=True)
     gen = torch.Generator(device=DEV).manual_seed(rows + cols)
     n = lambda *shape: torch.randn(shape, generator=gen, device=DEV, dtype=torch.float64)
+    k = min(24, cols)
     # the same construction, and the same bound for the same reason, as in test_gpu_sketch.py
-    W = ((n(rows, 24) * 0.7 ** torch.arange(24, device=DEV)) @ n(24, cols) + 0.05 * n(rows, cols)).float()
+    W = ((n(rows, k) * (0.7 if r < 9 else 0.85) ** torch.arange(k, device=DEV)) @ n(k, cols) + 0.05 * n(rows, cols)).float()
     S = n(r, cols).float()
     ref = reference(W, it, S)
     sigma1, norm = float(ref[1][0]), float(W.double().norm())
@@ -74,3 +89,16 @@ def test_several_steps_per_workgroup(name, steps):
            float((V - ref[2]).norm(dim=1).max()), float((W - ref[3]).norm()) / norm]
     print("errors " + " ".join(f"{e:.1e}" for e in err), flush=True)
     assert max(err) <= TOL_NORM
+
+
+@pytest.mark.parametrize("cols", COLS)
+@pytest.mark.parametrize("more", [-1, 0, 1, 2, 3])
+def test_steps_around_the_number_of_row_buffers(more, cols):
+    nb = pass_shape(cols)[2]
+    check(rows_for(nb + more, cols), cols, 6, 1)
+
+
+@pytest.mark.parametrize("rows,cols", [(520, 1028), (300, 8196), (300, 16388), (5001, 68)])
+@pytest.mark.parametrize("it", [0, 1])
+def test_up_to_twelve_earlier_ranks(rows, cols, it):
+    check(rows, cols, 13, it)
