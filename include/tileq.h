@@ -381,9 +381,10 @@ tq_status tq_lotile_place(const int32_t *ideal, int32_t n_experts, int32_t tiles
  *        U, Sigma, V).
  * U      fp32 [r][rows] (unit vectors), sigma fp32 [r], V fp32 [r][cols] (unit vectors), device.  A matrix that runs
  *        out of rank yields zero vectors and Sigma = 0 from there on.
- * workspace: tq_sketch_workspace_size(rows, cols) bytes, device, 256-byte aligned (0 = unsupported shape): partial column
- *        sums, the vectors of up to 16 ranks in 64 bits and what the block products need of them (33 MiB for 16384 x 12672,
- *        69 MiB for 1000000 x 4).
+ * workspace: tq_sketch_workspace_size(rows, cols) bytes, device, 256-byte aligned (0 = unsupported shape).  Up to 32768 columns
+ *        8 rows (1 + min(16, rows, cols)) bytes for the left vectors of up to 16 ranks in 64 bits (2.2 GB at 2^24 rows of 16 columns and more),
+ *        whatever r is, and at most 38 MiB of partial sums, right vectors and block products (31 MiB in all for 16384 x 12672, 39 MiB for
+ *        1000000 x 4); beyond, 4 (rows + 2 cols) bytes and at most 4 MiB or 4 cols bytes, whichever is more.
  * 1 <= r <= 4096, it <= 64.  Asynchronous on `stream`; all sums have a fixed order. */
 size_t tq_sketch_workspace_size(int64_t rows, int64_t cols);
 tq_status tq_sketch_lowrank(float *W, int64_t rows, int64_t cols, int32_t r, int32_t it, const float *sketch, float *U,

@@ -527,8 +527,8 @@ __device__ inline void sk_load_u(const double* __restrict__ p, int k, double (&u
 
 // Without power iterations: q = W_k s = Y_k - sum_{j<k} u_j c_j, c_j = p_j . s (also written to ctot), with the sums that a pass forms
 template <int KP>
-__global__ void __launch_bounds__(256) sk_project_kernel(const double* __restrict__ Y, int us, int64_t rows,
-                                                         const double* __restrict__ U, int k, const double* __restrict__ spart,
+__global__ void __launch_bounds__(256) sk_project_kernel(const double* __restrict__ U, int us, int64_t rows, int k,
+                                                         const double* __restrict__ spart,
                                                          int n_c, double* __restrict__ q, double* __restrict__ ctot,
                                                          double* __restrict__ ssq, double* __restrict__ dpart)
 {
@@ -537,7 +537,7 @@ __global__ void __launch_bounds__(256) sk_project_kernel(const double* __restric
     double u[KP > 0 ? KP : 1], y = 0.;
     auto load = [&](int64_t i) {
         i = min(i, rows - 1);
-        y = Y[i * us + k];
+        y = U[i * us + k];      // (Y_k, until u_k takes its place)
         if constexpr (KP > 0) sk_load_u<KP>(U + i * us, k, u);
     };
     SkCoefs coefs;
@@ -994,7 +994,7 @@ struct SketchPlan {
     // products and of the residual, workgroups of the projection without power iterations
     int nbs, n_c, ksplit, zslabs, wslabs, n_q;
     int64_t z_rows, w_rows;
-    size_t x, U, P, Y, Z, cpart, spart, dpart, ssq, ctot, zexp;
+    size_t x, U, P, Z = 0, cpart, spart, dpart, ssq, ctot, zexp = 0;
 };
 
 bool make_plan(int64_t rows, int64_t cols, SketchPlan* P)
@@ -1022,10 +1022,11 @@ bool make_plan(int64_t rows, int64_t cols, SketchPlan* P)
         P->x = take((size_t)cols * 4);
         P->U = take((size_t)rows * nb * 8);
         P->P = take((size_t)cols * nb * 8);
-        P->Y = take((size_t)rows * nb * 8);
-        P->Z = take((size_t)cols * nb * 8);
+        // (Y lies in U: column k is Y_k until rank k has been found, u_k from there)
+        const bool block = !P->shape.wide && nb >= 3;
+        if (block) P->Z = take((size_t)cols * nb * 8);
         const size_t pass = (size_t)P->shape.wg * cols * (P->shape.wide ? 4 : 8);
-        const size_t yp = P->ksplit > 1 ? (size_t)P->ksplit * rows * nb * 8 : 0, zp = (size_t)P->zslabs * cols * nb * 8;
+        const size_t yp = block && P->ksplit > 1 ? (size_t)P->ksplit * rows * nb * 8 : 0, zp = block ? (size_t)P->zslabs * cols * nb * 8 : 0;
         P->partial = take(std::max(pass, std::max(yp, zp)));
         P->cpart = take((size_t)P->n_c * MAXB * 8);
         P->spart = take((size_t)P->n_c * MAXB * nb * 8);
@@ -1033,7 +1034,7 @@ bool make_plan(int64_t rows, int64_t cols, SketchPlan* P)
         P->dpart = take(nq * MAXB * 8);
         P->ssq = take(nq * 8);
         P->ctot = take(MAXB * 8);
-        P->zexp = take((size_t)cdiv(cols, 64) * nb * 4);
+        if (block) P->zexp = take((size_t)cdiv(cols, 64) * nb * 4);
         P->total = off;
         return true;
     }
@@ -1059,7 +1060,7 @@ tq_status fused_lowrank(const SketchPlan& P, float* W, int64_t rows, int64_t col
 {
     const SketchShape& sh = P.shape;
     auto f64 = [&](size_t o) { return reinterpret_cast<double*>(ws + o); };
-    double *q = f64(P.q), *U = f64(P.U), *Pv = f64(P.P), *Y = f64(P.Y), *Z = f64(P.Z), *cpart = f64(P.cpart), *spart = f64(P.spart),
+    double *q = f64(P.q), *U = f64(P.U), *Pv = f64(P.P), *Y = U, *Z = f64(P.Z), *cpart = f64(P.cpart), *spart = f64(P.spart),
            *dpart = f64(P.dpart), *ssq = f64(P.ssq), *ctot = f64(P.ctot);
     float* x = reinterpret_cast<float*>(ws + P.x);
     int* zexp = reinterpret_cast<int*>(ws + P.zexp);
@@ -1120,8 +1121,8 @@ tq_status fused_lowrank(const SketchPlan& P, float* W, int64_t rows, int64_t col
             };
             if (block && it == 0) {
 #define TQ_PRO(KP)                                                                                                             \
-    hipLaunchKernelGGL(sk_project_kernel<KP>, dim3(P.n_q), dim3(256), 0, st, (const double*)Y, us, rows, (const double*)U, k, \
-                       (const double*)spart, P.n_c, q, ctot, ssq, dpart)
+    hipLaunchKernelGGL(sk_project_kernel<KP>, dim3(P.n_q), dim3(256), 0, st, (const double*)U, us, rows, k, (const double*)spart, \
+                       P.n_c, q, ctot, ssq, dpart)
                 TQ_BY_RANKS(k, TQ_PRO);
 #undef TQ_PRO
                 finish(true, Z + (size_t)k * cols, 1, P.n_q, ctot);

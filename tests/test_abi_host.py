@@ -289,3 +289,11 @@ def test_bench_refuses_more_than_one_gpu():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert r.returncode != 0
     assert "one GPU" in (r.stderr + r.stdout)
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 4), (16384, 12672), (1000000, 4), (1 << 24, 16), (1024, 2048), (4096, 16384), (4096, 20000), (6000, 32768),
+                                       (16, 32768), (2, 17000), (1 << 24, 64), (32768, 4096)])
+def test_sketch_workspace_grows_with_the_left_vectors_alone(rows, cols):
+    n = tq.lib().tq_sketch_workspace_size(rows, cols)
+    vectors = 8 * rows * (1 + min(16, rows, cols))
+    assert vectors <= n <= vectors + 38 * 2 ** 20
