@@ -664,6 +664,9 @@ __global__ void __launch_bounds__(256) sk_finish_kernel(const ACC* __restrict__ 
 #pragma unroll
             for (int i = 0; i < KP; ++i) a = fma(-pj[i], dj[i] + de[i], a);
             a *= inv;
+            // 32-bit column sums: x of about unit length instead of Sigma, as a power of two (the next sums have the size of Sigma^2 then, and
+            // not of Sigma^3, which leaves the fp32 range for matrices of 1e12 or 1e-15)
+            if (sizeof(ACC) == 4 && !LAST && inv > 0.) a = ldexp(a, ilogb(inv));
             if (col >= cols) a = 0.;
             else if (LAST) P[k * cols + col] = a;
             else x[col] = (float)a;

@@ -50,6 +50,16 @@ def test_cancellation_over_five_digits(it, scale):
     assert max(e) <= TOL_NORM
 
 
+@pytest.mark.parametrize("it", [0, 2])
+@pytest.mark.parametrize("scale", [1e-15, 1e12])
+def test_scales_where_the_column_sums_have_32_bits(it, scale):
+    """Past 16384 columns: the first q of a rank has the length of W s, and the column sums that of W^T W s."""
+    W, n = matrix(300, 17000, 0.7, 0.05, 6)
+    e = errors((W * scale).float(), n(6, 17000).float(), it)
+    print("errors " + " ".join(f"{x:.1e}" for x in e), flush=True)
+    assert max(e) <= TOL_NORM
+
+
 @pytest.mark.parametrize("rows,cols", [(3, 64), (64, 4), (2, 17000)])
 @pytest.mark.parametrize("it", [0, 2])
 def test_more_ranks_than_the_matrix_has(rows, cols, it):
