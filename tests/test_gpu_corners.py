@@ -112,16 +112,18 @@ def test_workspace_serves_smaller_batches_across_the_path_thresholds():
         assert rel_err(got, ref) <= TOL_BF16
 
 
-def test_many_rows_small_layer():
-    """Tens of thousands of tokens on a small layer: thousands of row tiles per expert, multi-chunk permutation,
-    persistent workgroups walking long item lists; sampled tokens against the oracle, all tokens finite."""
+@pytest.mark.parametrize("flags", [tq.TQ_FLAG_FORCE_LARGE_TILE, 0], ids=["persistent", "auto"])
+def test_many_rows_small_layer(flags):
+    """Tens of thousands of tokens on a small layer: thousands of row tiles per expert, multi-chunk permutation; on the large
+    tilings persistent workgroups walking long item lists, without a forced path the 32-row kernel (1.97e9 multiplications per
+    matrix); sampled tokens against the oracle, all tokens finite."""
     cfg = corner(530, H=128, F=128, g=64, r=8, E=4, k=2, T=60000)
     layer = make_layer(cfg, workers=8)
     x = make_x(cfg)
     logits, bias = make_logits(cfg)
     packed = pack_layer_gpu(layer)
     idx, w = tq.tq_route(torch.from_numpy(logits).to(DEV), None, cfg.k)
-    desc = desc_of(cfg, tq.TQ_ACT_BF16, 0)
+    desc = desc_of(cfg, tq.TQ_ACT_BF16, flags)
     ws = torch.empty(tq.tq_moe_workspace_size(desc, cfg.T), dtype=torch.uint8, device=DEV)
     y = tq.tq_moe_forward(desc, packed, x_device(x, tq.TQ_ACT_BF16), idx, w, workspace=ws)
     torch.cuda.synchronize()

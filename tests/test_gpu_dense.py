@@ -146,11 +146,12 @@ def test_dense_forward_bf16_tiled_kernels(name, kind, path):
     assert err <= (REG_LR_BF16 if kind == "amplified" else REG_BF16)
 
 
+@pytest.mark.parametrize("flags", [0, tq.TQ_FLAG_FORCE_LARGE_TILE], ids=["auto", "large_tile"])      # auto: the 32-row kernel
 @pytest.mark.parametrize("bits", [3, 2])
-def test_dense_batch_beyond_the_decode_kernels_takes_the_tiled_kernels(bits):
+def test_dense_batch_beyond_the_decode_kernels_takes_the_tiled_kernels(bits, flags):
     cfg = dcfg(820 + bits, bits=bits, E=5, k=2, T=700, H=256, F=384, g=128, r=16)     # 1400 assignment rows, ragged tiles
     layer = make_layer(cfg, workers=8)
-    got, ref = forward(layer, make_x(cfg), *make_logits(cfg), tq.TQ_ACT_BF16)
+    got, ref = forward(layer, make_x(cfg), *make_logits(cfg), tq.TQ_ACT_BF16, flags)
     err = rel_err(got, ref)
     print(f"dense {bits}-bit, 1400 rows: rel err {err:.3e}", flush=True)
     assert err <= REG_BF16

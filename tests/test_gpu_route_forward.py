@@ -83,6 +83,15 @@ def test_fused_equals_route_then_forward(name, act):
     assert rel_err(y2.float().cpu().numpy(), ref) <= (REG_BF16 if act == tq.TQ_ACT_BF16 else TOL_FP32)
 
 
+def test_prefill_sized_batch_on_the_large_tiles():
+    """Without a forced path this small layer takes the 32-row kernel."""
+    layer, x, logits, bias, (idx, w, y), (idx2, w2, y2) = both_ways(CASES["prefill_sized"][0], tq.TQ_ACT_BF16, tq.TQ_FLAG_FORCE_LARGE_TILE)
+    assert torch.equal(idx, idx2) and torch.equal(w.view(torch.int32), w2.view(torch.int32))
+    assert torch.equal(y.view(torch.int16), y2.view(torch.int16))
+    ref = oracle.moe_forward_layer(layer, x, idx2.cpu().numpy(), w2.cpu().numpy())
+    assert rel_err(y2.float().cpu().numpy(), ref) <= REG_BF16
+
+
 def test_fused_routing_ties_and_infinite_scores():
     """Equal scores go to the lower index and -inf scores come last, inside the permutation's launch as in tq_route."""
     cfg = rcfg(981, T=4, E=8, k=3)
