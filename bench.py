@@ -90,6 +90,22 @@ def algorithmic_work(cfg, idx_np, fp8=False):
                 path_flops=flops_gu + flops_d, gate_up_flops=flops_gu, down_flops=flops_d)
 
 
+def sketch_streams(rows, cols, r, it):
+    """(reads, writes) of the matrix by one tq_sketch_lowrank call, as its kernels make them."""
+    if cols > 32768:      # two products per rank and two per iteration; the deflation is stored with the next rank's first product
+        return r * (2 * it + 2) + 1, r
+    reads = writes = 0
+    batch = min(16, rows, cols)
+    while r > 0:
+        nb = min(batch, r)
+        # first products of all ranks from two block products, then a pass per iteration; else it + 1 passes per rank
+        block = cols <= 16384 and nb >= 3 and (it > 0 or nb * rows * cols >= 12 << 20)
+        reads += (nb * it + 2 if block else nb * (it + 1)) + 1      # and the residual
+        writes += 1
+        r -= nb
+    return reads, writes
+
+
 def bench_lotile(args, cfg, dev):
     """One step = tq_route + tq_lotile_forward on x [T, hidden] -> y [T, ffn] with factors resident in HBM."""
     import numpy as np
@@ -325,10 +341,7 @@ def main():
             if i:
                 times.append(ev.elapsed_ms(0, 1))
         ms = sum(times) / len(times)
-        # reads of the matrix: `it` per rank and two per 16 ranks for their first products (64-bit column sums, up to 16384 columns), else
-        # it + 1 per rank; the residual read and written once
-        reads = r * it + 2 * -(-r // 16) if it > 0 and cols <= 16384 else r * (it + 1)
-        moved = rows * cols * 4.0 * (reads + 2)
+        moved = rows * cols * 4.0 * sum(sketch_streams(rows, cols, r, it))
         print(json.dumps({"sketch": {"rows": rows, "cols": cols, "rank": r, "power_iterations": it, "ms": round(ms, 3),
                                      "ms_per_rank": round(ms / r, 3),
                                      "roofline": {"bound": "hbm", "achieved": round(moved / ms / 1e6, 1), "peak": 8000.0,
