@@ -10,11 +10,32 @@
 //            16-byte stores per thread) and the workgroup barrier that publishes it
 // Every level runs with two workgroups per compute unit (two waves per SIMD), as the kernel does.  The kernel reports
 // its own cycle count and wall-clock time, so the clock the chip sustained under that load is known.
+// Operands are random: activations of a normal distribution in bf16, codes of all values (128 + q as bf16 where nothing is unpacked).  The
+// chip is at its power limit under such a load; with constant operands, which switch hardly any gate, the same MFMAs run at 2.4 GHz
+// and the figures are up to 40 % too good.
 #include "tq_device.h"
 
 using namespace tqdev;
 
 namespace {
+
+__device__ inline uint32_t probe_hash(uint32_t v)
+{
+    v ^= v >> 16; v *= 0x7FEB352Du; v ^= v >> 15; v *= 0x846CA68Bu;
+    return v ^ (v >> 16);
+}
+// two bf16 values of (nearly) a standard normal distribution: the sum of four random bytes, centred
+__device__ inline uint32_t probe_normals(uint32_t seed)
+{
+    uint32_t o = 0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const uint32_t h = probe_hash(2 * seed + i);
+        const float f = ((float)((h & 255) + ((h >> 8) & 255) + ((h >> 16) & 255) + (h >> 24)) - 510.f) * (1.f / 147.8f);
+        o |= (__float_as_uint(f) >> 16) << (16 * i);
+    }
+    return o;
+}
 
 template <int LEVEL>
 __global__ void __launch_bounds__(256, 2) issue_probe_kernel(float* __restrict__ out, int iters, uint32_t mask, uint32_t magic_s,
@@ -24,11 +45,13 @@ __global__ void __launch_bounds__(256, 2) issue_probe_kernel(float* __restrict__
     constexpr int MT = 2, NT = 2, GS = 8, ROWB = 272, BUFB = 32 * MT * ROWB;
     constexpr int NBUF = LEVEL >= 4 ? 2 : 1;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    for (int i = threadIdx.x; i < (NBUF * BUFB) / 4; i += blockDim.x) reinterpret_cast<uint32_t*>(lds)[i] = 0x3F803F80u + (i & 3);
+    for (int i = threadIdx.x; i < (NBUF * BUFB) / 4; i += blockDim.x) reinterpret_cast<uint32_t*>(lds)[i] = probe_normals(i);
     __syncthreads();
     u32x4 xr[MT];
 #pragma unroll
-    for (int m = 0; m < MT; ++m) { xr[m][0] = 0x3F803F80u; xr[m][1] = 0x3F803F81u; xr[m][2] = 0x3F803F82u; xr[m][3] = 0x3F803F83u; }
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) xr[m][j] = probe_normals(0x10000u + (threadIdx.x * MT + m) * 4 + j);
     const uint32_t wr_off = (threadIdx.x >> 4) * ROWB + (threadIdx.x & 15) * 16;      // 16 rows x 256 bytes per pass
     const int lane = threadIdx.x & 63, col = lane & 31, hf = lane >> 5;
     uint32_t magic;
@@ -44,13 +67,19 @@ __global__ void __launch_bounds__(256, 2) issue_probe_kernel(float* __restrict__
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int s = 0; s < GS; ++s) w[t][s] = 0x12345678u * (threadIdx.x + 1) + t * 977 + s * 131;
-    Frag areg[MT], breg[NT];
+        for (int s = 0; s < GS; ++s) w[t][s] = probe_hash(0x20000u + (threadIdx.x * NT + t) * GS + s);
+    constexpr int NREG = LEVEL < 2 ? GS : 1;      // register operands: fragments of their own for every step
+    Frag areg[NREG][MT], breg[NREG][NT];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        areg[0].u[j] = 0x3F803F80u + j; areg[1].u[j] = 0x3F813F80u + j;
-        breg[0].u[j] = 0x43014302u + j; breg[1].u[j] = 0x43034304u + j;
-    }
+    for (int s = 0; s < NREG; ++s)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+#pragma unroll
+            for (int m = 0; m < MT; ++m) areg[s][m].u[j] = probe_normals(0x30000u + ((threadIdx.x * GS + s) * MT + m) * 4 + j);
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                breg[s][t].u[j] = 0x43004300u | (probe_hash(0x50000u + ((threadIdx.x * GS + s) * NT + t) * 4 + j) & 0x000F000Fu);
+        }
     const uint8_t* base0 = lds + col * ROWB + hf * 16;
     const unsigned long long c0 = clock64(), w0 = wall_clock64();
     for (int it = 0; it < iters; ++it) {
@@ -66,12 +95,12 @@ __global__ void __launch_bounds__(256, 2) issue_probe_kernel(float* __restrict__
 #pragma unroll
             for (int m = 0; m < MT; ++m) {
                 if (LEVEL >= 1) a[m].q = *reinterpret_cast<const u32x4*>(base + m * 32 * ROWB + ((ks + it) & 7) * 32);
-                else a[m] = areg[m];
+                else a[m] = areg[ks % NREG][m];
             }
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 if (LEVEL >= 2) b[t] = unpack_word(w[t][ks] + it, mask, magic);
-                else b[t] = breg[t].v;
+                else b[t] = breg[ks % NREG][t].v;
             }
 #pragma unroll
             for (int m = 0; m < MT; ++m)
@@ -107,7 +136,7 @@ __global__ void __launch_bounds__(256, 2) issue_probe_kernel(float* __restrict__
         } else if (LEVEL < 2) {
             // keep the register operands loop-variant so that the steps are not merged
 #pragma unroll
-            for (int t = 0; t < NT; ++t) breg[t].u[0] ^= (uint32_t)(sc[t] != 7.f);
+            for (int t = 0; t < NT; ++t) breg[0][t].u[0] ^= (uint32_t)(sc[t] != 7.f);
         }
     }
     const unsigned long long c1 = clock64(), w1 = wall_clock64();
