@@ -1,6 +1,6 @@
 """tq_sketch_lowrank at the edges of its pass shapes: row lengths on either side of every switch of the workgroup width
-(1024, 2048, 4096, 8192, 16384 and 32768 columns), row counts below and just past a whole number of row groups, and more
-ranks than pending deflations fit."""
+(1024, 2048, 4096, 8192, 16384 and 32768 columns), row counts below and just past a whole number of row groups, and several
+ranks."""
 import numpy as np
 import pytest
 
