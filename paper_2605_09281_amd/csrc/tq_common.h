@@ -335,7 +335,7 @@ __device__ inline int tq_find_expert(const int32_t* __restrict__ offsets, int n,
 
 // Decode batches: the low-rank intermediate of gate/up, t = x A_e, computed per ASSIGNMENT (it needs the routing
 // table only, not the permutation) so that it can share the permutation's launch:
-//   tpart[v][slice][ta][c] = sum over the 256-wide slice of x[token(v)][kk] * A_e(v)[kk][32 ta + c]   (fp32)
+//   t[v][c] = bf16(sigma_c * sum over kk of x[token(v)][kk] * A_e(v)[kk][c])      (summed in fp32, 256-wide slices in order)
 // v = t * k + j for routed assignments, T * k + s * T + t for shared expert s.
 #define TQ_PRE_ASSIGN_MAX_ROWS 256    // assignment rows up to which the decode path takes this form (A_e is read per row;
                                       // measured: saves 7 % of the step at 96 rows, 5 % at 160, 1-2 % at 256)
@@ -345,8 +345,8 @@ struct TqPreByAssign {
     size_t expert_stride;
     TqSection sec;           // section GU
     TqFactorMap fm;
-    float* tpart;
-    int32_t H, n_slices, na_tiles, a_tot;
+    uint16_t* t;             // [a_tot][na]
+    int32_t H, n_slices, na_tiles, na, a_tot;      // (at most 16 slices: the decode kernels take a hidden size of at most 4096)
 };
 
 // Routing inputs of tq_route_moe_forward: when the single-wave permutation runs (one chunk of assignments) and the

@@ -690,15 +690,18 @@ __device__ inline void permute_small_body(const int32_t* __restrict__ idx, const
     if ((flags & TQ_FLAG_BIT_BLOB) && ctrl && lane == 0) { ctrl[1] = 0; ctrl[2] = 0; ctrl[3] = 0; ctrl[4] = 0; ctrl[5] = 0; }
 }
 
-// One wavefront per (assignment v, 256-wide slice, 32-column tile of t): see TqPreByAssign.  Plain fp32 FMAs on the
-// exact values of x (bf16) and A (fp16, or fp8 with FP8), the two halves of a 16-wide step in the two halves of the wave.
+// One workgroup per (assignment v, 32-column tile of t), a wave per 256-wide slice of the contraction: see TqPreByAssign.  Plain fp32 FMAs on
+// the exact values of x (bf16) and A (fp16, or fp8 with FP8), the two halves of a 16-wide step in the two halves of a wave; the slices are
+// added in order through LDS.
 template <bool FP8>
 __device__ inline void pre_by_assign_block(const TqPreByAssign& P, const int32_t* __restrict__ idx, int T, int E, int k,
-                                           int b, int lane, const TqRouteIn* route = nullptr)
+                                           int b, const TqRouteIn* route = nullptr)
 {
+    __shared__ float red[16][32];
+    __shared__ __attribute__((aligned(16))) uint2 xl[16][64];      // each wave's slice of the row
+    const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6;
     const int ta = b % P.na_tiles;
-    const int slice = (b / P.na_tiles) % P.n_slices;
-    const int v = b / (P.na_tiles * P.n_slices);
+    const int v = b / P.na_tiles;
     if (v >= P.a_tot) return;
     int e, t;
     if (v < T * k) {
@@ -713,19 +716,21 @@ __device__ inline void pre_by_assign_block(const TqPreByAssign& P, const int32_t
     const uint4* af = reinterpret_cast<const uint4*>(tq_afrag_base(P.blob, P.expert_stride, P.sec, P.fm, 0, e));
     constexpr int NS = 16;                       // steps per slice
     const int s0 = slice * NS;
-    uint4 xa[NS], aq[NS];
+    uint4 aq[NS];
+    const uint2 xv = *reinterpret_cast<const uint2*>(xrow + min(256 * slice + 4 * lane, P.H - 4));
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
-        const int sidx = min(s0 + u, ksteps - 1);
-        xa[u] = *reinterpret_cast<const uint4*>(xrow + 16 * sidx + 8 * hf);
-        const size_t f = (size_t)ta * ksteps + sidx;       // fragment; fp8 fragments: 8 bytes per lane, two lanes per word
+        const size_t f = (size_t)ta * ksteps + min(s0 + u, ksteps - 1);       // fragment; fp8 fragments: 8 bytes per lane, two lanes per word
         aq[u] = af[FP8 ? f * 32 + (lane >> 1) : f * 64 + lane];
     }
+    xl[slice][lane] = xv;
+    wave_fence();
     float acc = 0.f;
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
         if (s0 + u < ksteps) {
-            const uint32_t xw[4] = {xa[u].x, xa[u].y, xa[u].z, xa[u].w};
+            const uint4 xa = *reinterpret_cast<const uint4*>(&xl[slice][4 * u + 2 * hf]);
+            const uint32_t xw[4] = {xa.x, xa.y, xa.z, xa.w};
             const uint32_t aw[4] = {aq[u].x, aq[u].y, aq[u].z, aq[u].w};
             if (FP8) {
                 const uint32_t d[2] = {(lane & 1) ? aw[2] : aw[0], (lane & 1) ? aw[3] : aw[1]};
@@ -746,24 +751,24 @@ __device__ inline void pre_by_assign_block(const TqPreByAssign& P, const int32_t
         }
     }
     acc += __shfl_xor(acc, 32);
-    if (hf == 0) P.tpart[(((size_t)v * P.n_slices + slice) * P.na_tiles + ta) * 32 + col] = acc;
-}
-
-template <bool FP8>
-__global__ void __launch_bounds__(64) pre_by_assign_kernel(TqPreByAssign P, const int32_t* __restrict__ idx, int T, int E, int k,
-                                                           const TqBlobHeader* __restrict__ hdr, TqBlobHeader expect,
-                                                           int check_blob)
-{
-    if (check_blob && !blob_header_ok(hdr, expect)) return;      // a blob of another layer is not indexed
-    pre_by_assign_block<FP8>(P, idx, T, E, k, blockIdx.x, threadIdx.x);
+    if (hf == 0) red[slice][col] = acc;
+    __syncthreads();
+    const int c = 32 * ta + (int)threadIdx.x;
+    if (threadIdx.x < 32 && c < P.na) {
+        float s = 0.f;
+        for (int i = 0; i < P.n_slices; ++i) s += red[i][threadIdx.x];
+        if (FP8) s *= tq_sig_base(P.blob, P.expert_stride, P.sec, P.fm, 0, e)[c];
+        P.t[(size_t)v * P.na + c] = (uint16_t)tqdev::f2bf_bits(s);
+    }
 }
 
 // The whole permutation of at most TQ_PERM_CHUNK assignments in ONE wavefront and one launch; with
 // PRE != 0 the other workgroups of the launch compute the gate/up low-rank intermediate by assignment (1: fp16
 // factors, 2: fp8 factors) or derive what the tiled kernels read beside the blob (3).
 // With ROUTE the launch also does the routing (route_small; idx and w are then unused).
+// (Workgroups of as many waves as the pre-pass has slices; the permutation's is one wave, the others end at once.)
 template <int PRE, bool ROUTE>
-__global__ void __launch_bounds__(64) permute_small_kernel(const int32_t* __restrict__ idx, const float* __restrict__ w,
+__global__ void __launch_bounds__(PRE == 1 || PRE == 2 ? 1024 : 64) permute_small_kernel(const int32_t* __restrict__ idx, const float* __restrict__ w,
                                                            int n_assign, int E, int S, int T, int k,
                                                            int32_t* __restrict__ offsets, int32_t* __restrict__ slot_of,
                                                            int slot_stride, int32_t* __restrict__ src_of,
@@ -783,9 +788,10 @@ __global__ void __launch_bounds__(64) permute_small_kernel(const int32_t* __rest
         }
     } else if (PRE != 0 && blockIdx.x > 0) {
         if (check_blob && !blob_header_ok(hdr, expect)) return;      // a blob of another layer is not indexed
-        pre_by_assign_block<PRE == 2>(P, idx, T, E, k, blockIdx.x - 1, threadIdx.x, ROUTE ? &R : nullptr);
+        pre_by_assign_block<PRE == 2>(P, idx, T, E, k, blockIdx.x - 1, ROUTE ? &R : nullptr);
         return;
     }
+    if (threadIdx.x >= 64) return;
     if (ROUTE) {
         extern __shared__ int32_t sm_all[];
         float* sc = reinterpret_cast<float*>(sm_all + route_off);
@@ -812,7 +818,7 @@ tq_status tqi_launch_permute(const int32_t* topk_idx, const float* topk_w, int32
 {
     const int64_t n_assign = (int64_t)T * k;
     const unsigned n_prep = prep ? prep->n_waves : 0;
-    const int64_t n_pre = pre ? (int64_t)pre->a_tot * pre->n_slices * pre->na_tiles : 0;
+    const int64_t n_pre = pre ? (int64_t)pre->a_tot * pre->na_tiles : 0;
     if (n_pre > 0x3FFFFFFF) return TQ_ERR_UNSUPPORTED;
     TqBlobHeader expect = {};
     int check = 0;
@@ -833,7 +839,7 @@ tq_status tqi_launch_permute(const int32_t* topk_idx, const float* topk_w, int32
         const TqRouteIn R = fused ? *route : TqRouteIn{};
         const TqPreByAssign P = n_pre > 0 ? *pre : TqPreByAssign{};
 #define TQ_PS(PREV, ROUTEV, P, NV)                                                                                        \
-        hipLaunchKernelGGL((permute_small_kernel<PREV, ROUTEV>), dim3(1 + (unsigned)(NV)), dim3(64), sm, stream, topk_idx,  \
+        hipLaunchKernelGGL((permute_small_kernel<PREV, ROUTEV>), dim3(1 + (unsigned)(NV)), dim3(pre_kind ? 64 * pre->n_slices : 64), sm, stream, topk_idx,  \
                            topk_w, (int)n_assign, E, S, T, k, offsets, slot_of, slot_stride, src_of, row_token, row_w,     \
                            tile_e, tile_row0, rt_max, ctrl, err_flag, (const TqBlobHeader*)blob, expect, check, zero_buf,  \
                            (int)zero_n, P, tilings, R, sm_words)
@@ -850,15 +856,7 @@ tq_status tqi_launch_permute(const int32_t* topk_idx, const float* topk_w, int32
         return TQ_OK;
     }
     if (route) return TQ_ERR_UNSUPPORTED;      // the caller routes by itself when the single-wave permutation does not run
-    if (n_pre > 0) {      // no launch of single waves to ride in: the pre-pass gets its own
-        if (pre->fm.fp8)
-            hipLaunchKernelGGL(pre_by_assign_kernel<true>, dim3((unsigned)n_pre), dim3(64), 0, stream, *pre, topk_idx, T, E, k,
-                               (const TqBlobHeader*)blob, expect, check);
-        else
-            hipLaunchKernelGGL(pre_by_assign_kernel<false>, dim3((unsigned)n_pre), dim3(64), 0, stream, *pre, topk_idx, T, E, k,
-                               (const TqBlobHeader*)blob, expect, check);
-        TQ_CHECK_LAUNCH();
-    }
+    if (n_pre > 0) return TQ_ERR_UNSUPPORTED;  // (at most 256 rows: always the single-wave permutation)
     const unsigned nb = (unsigned)((n_assign + TQ_PLACE_CHUNK - 1) / TQ_PLACE_CHUNK);
     const bool count_self = n_assign <= TQ_PLACE_COUNT_SELF;
     const bool scan = !count_self && (int64_t)nb * E >= TQ_PLACE_SCAN_WORDS;

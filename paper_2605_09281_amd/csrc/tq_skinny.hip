@@ -6,15 +6,20 @@
 //   * A workgroup has 8 waves; wave w owns a 512-wide slice (256 on contractions up to 2048) of the contraction range and walks over the
 //     workgroup's column-tile pairs, streaming its slice of the packed codes (already in MFMA fragment
 //     order) straight from global memory into registers, one pair ahead.  No barrier in that stream.
-//   * Codes go to v_mfma_f32_32x32x16_bf16 as 128 + q (rows 16..31 of the tile are padding); each
-//     quantisation group's fp32 partial sum is folded as  acc += s * part - s (128 + z) * xsum, with the
-//     group sums of the activations computed once per workgroup by an MFMA against a matrix of ones.
+//   * Codes go to v_mfma_f32_16x16x32_bf16 as 128 + q; each quantisation group's fp32 partial sum is folded as
+//     acc += s * part - s (128 + z) * xsum, with the group sums of the activations added up as the rows are staged.  The blob's
+//     fragments are those of the 32x32x16 instruction of the tiled kernels; one row exchange (v_permlane16_swap) of the words of
+//     two steps makes the 16-column fragments of a 32-deep step of them, so no MFMA row is padding.
 //   * The 8 partial results of a pair are summed across the waves through LDS in a fixed order (the
 //     "wavefront reduction"), then SwiGLU (stage 0) or the store of the split-K plane (stage 1).
-//   * The low-rank intermediate t = x A is produced per 256-wide slice by skinny_pre_kernel (for decode batches
-//     proper the gate/up slices come per assignment from the permutation's launch instead); a workgroup
-//     adds the slices of its own range, so a split contraction needs no global reduction: the partial
-//     t of a split times B lands in that split's output plane, and the planes are summed by the combine.
+//   * The low-rank intermediate t = x A of a workgroup's range comes ready as bf16 from skinny_pre_kernel (for decode batches
+//     proper that of gate/up per assignment from the permutation's launch); a split contraction needs no global reduction: the
+//     partial t of a split times B lands in that split's output plane, and the planes are summed by the combine.
+// Measured on 8 experts of 4096 x 14336, 16 tokens: gate/up 84.4 us for 514 MB, down 50.5 for 257 MB (with 32x32 MFMAs half of whose rows were padding,
+// the intermediate added up from fp32 slices in the set-up and group sums by MFMAs against ones: 91.9 and 56.9); whole call 163 -> 149 us.
+// The same call with codes of 3 bits and fp8 factors 162 -> 145 (there the MFMAs and their operands counted); 128 experts of 4096 x 1536: 112 -> 104.
+// Tried: two pairs in flight (spills at 512 indices a wave; at 256 the deal gets coarser: 44.6 -> 52.2 us on 60 experts of 2048 x 1408, 4
+// tokens); touching every workgroup's first pair in the launch before (down 2 us shorter, that launch 2 us longer).
 #include "tq_device.h"
 
 #include <algorithm>
@@ -24,58 +29,112 @@ using namespace tqdev;
 
 namespace {
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 constexpr int SK_NW = 8;        // waves per workgroup
 constexpr int SK_RED_BYTES = SK_NW * 7 * 2 * 64 * 4;   // per wave: 7 of its 8 row groups, 2 tiles, 64 lanes
 
-__device__ inline int row_of_v(int v, int hf) { return 8 * (v >> 2) + 4 * hf + (v & 3); }
-
-// Partial low-rank intermediate of one 16-row tile over one 256-wide slice of the contraction:
-//   tpart[tile][slice][ta][v][lane] = sum_{kk in slice} x[row(v, lane)][kk] * A[kk][32 ta + lane % 32]   (fp32)
-// One wave per (tile, slice, ta); all of its loads are in flight at once.
+// Low-rank intermediate of one 16-row tile over the contraction range of one split, ready for the low-rank step:
+//   t[tile][split][m][c] = bf16(sigma_c * sum_{kk in range} x[row m][kk] * A[kk][c])
+// One workgroup per (tile, split, 32 columns of t); wave w takes the 256-wide slice w of the range, with all of its loads in flight
+// at once, and the slices are added in order through LDS.  (Left as fp32 slices for the kernel that reads them, they were 64 loads a lane of its
+// set-up.)
 constexpr int SK_PRE_K = 256;
 
-template <int STAGE, bool FP8>
-__global__ void __launch_bounds__(64) skinny_pre_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob,
-                                                        const uint16_t* __restrict__ xin,
-                                                        const int32_t* __restrict__ row_token,
-                                                        const int32_t* __restrict__ tile_e,
-                                                        const int32_t* __restrict__ tile_row0,
-                                                        const int32_t* __restrict__ offsets,
-                                                        const int32_t* __restrict__ ctrl, float* __restrict__ tpart,
-                                                        int n_slices, int na_tiles)
+// Exchanges 16-lane rows: a keeps its even rows and takes b's in its odd ones, b the other way round.  On the words of two 16-deep steps
+// (lane = column + 32 * k-half) a becomes the word of a 32-deep step's columns 0..15, b that of columns 16..31; the four rows of either hold
+// (step, k-half) = (0, 0), (1, 0), (0, 1), (1, 1).
+__device__ inline void swap_rows(uint32_t& a, uint32_t& b)
 {
-    const int tile = blockIdx.x, slice = blockIdx.y, ta = blockIdx.z, lane = threadIdx.x;
+    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+
+template <int STAGE, bool FP8>
+__global__ void __launch_bounds__(1024) skinny_pre_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob,
+                                                          const uint16_t* __restrict__ xin,
+                                                          const int32_t* __restrict__ row_token,
+                                                          const int32_t* __restrict__ tile_e,
+                                                          const int32_t* __restrict__ tile_row0,
+                                                          const int32_t* __restrict__ tile_rows,
+                                                          const int32_t* __restrict__ ctrl, uint16_t* __restrict__ t_out, int range_k)
+{
+    __shared__ float red[16][8][64];
+    const int tile = blockIdx.x, split = blockIdx.y, ta = blockIdx.z, lane = threadIdx.x & 63, slice = threadIdx.x >> 6;
     if (tile >= ctrl[4]) return;
-    const int e = tile_e[tile], slot0 = tile_row0[tile];
-    const int rows = min(16, offsets[e + 1] - slot0);
-    const int col = lane & 31, hf = lane >> 5;
+    const int e = tile_e[tile], slot0 = tile_row0[tile], rows = tile_rows[tile];
     const int K = sec.K, ksteps = K / 16;
-    const int r = min(col & 15, rows - 1);
-    const uint16_t* xrow = STAGE == 0 ? xin + (size_t)row_token[slot0 + r] * K : xin + (size_t)(slot0 + r) * K;
-    const u32x4* af = reinterpret_cast<const u32x4*>(tq_afrag_base(blob, G.expert_stride, sec, G.fm, STAGE, e));
+    const int r = min(lane & 15, rows - 1), lrow = lane >> 4;
+    const uint16_t* xrow = (STAGE == 0 ? xin + (size_t)row_token[slot0 + r] * K : xin + (size_t)(slot0 + r) * K) + 16 * (lrow & 1) + 8 * (lrow >> 1);
+    const u32x4* af = reinterpret_cast<const u32x4*>(tq_afrag_base(blob, G.expert_stride, sec, G.fm, STAGE, e)) + (FP8 ? lane >> 1 : lane);
     constexpr int NS = SK_PRE_K / 16;
-    const int s0 = slice * NS;
-    const int n = min(NS, ksteps - s0);
-    Frag xa[NS];
+    const int s0 = split * (range_k / 16) + slice * NS;
+    const int n = min(NS, min(ksteps, (split + 1) * (range_k / 16)) - s0);      // (<= 0: past the end of the last split); even: ranges are whole chunks of 64
+    Frag xa[NS / 2];
     u32x4 aq[NS];
 #pragma unroll
     for (int u = 0; u < NS; ++u)
         if (u < n) {
-            xa[u].q = *reinterpret_cast<const u32x4*>(xrow + 16 * (s0 + u) + 8 * hf);
+            if (u % 2 == 0) xa[u / 2].q = *reinterpret_cast<const u32x4*>(xrow + 16 * (s0 + u));
             const size_t f = (size_t)ta * ksteps + s0 + u;                  // fragment; fp8 fragments are half as long
-            aq[u] = af[FP8 ? f * 32 + (lane >> 1) : f * 64 + lane];
+            aq[u] = af[f * (FP8 ? 32 : 64)];
         }
-    f32x16 acc;
+    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    for (int u = 0; u < NS; u += 2)
+        if (u < n) {
+            Frag b[2];
 #pragma unroll
-    for (int u = 0; u < NS; ++u)
-        if (u < n)
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[u].v, FP8 ? fp8_frag_to_bf8(aq[u], lane) : half8_to_bf8(aq[u]), acc,
-                                                          0, 0, 0);
-    float* dst = tpart + (((size_t)tile * n_slices + slice) * na_tiles + ta) * 512 + lane;
+            for (int i = 0; i < 2; ++i) b[i].v = FP8 ? fp8_frag_to_bf8(aq[u + i], lane) : half8_to_bf8(aq[u + i]);
 #pragma unroll
-    for (int v = 0; v < 8; ++v) dst[v * 64] = acc[v];
+            for (int j = 0; j < 4; ++j) swap_rows(b[0].u[j], b[1].u[j]);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[u / 2].v, b[i].v, acc[i], 0, 0, 0);
+        }
+#pragma unroll
+    for (int v = 0; v < 8; ++v) red[slice][v][lane] = acc[v >> 2][v & 3];
+    __syncthreads();
+    const int nsl = blockDim.x >> 6, NA = STAGE == 0 ? 2 * G.r16 : G.r16;
+    for (int i = threadIdx.x; i < 512; i += blockDim.x) {
+        const int v = i >> 6, l = i & 63, c = 32 * ta + 16 * (v >> 2) + (l & 15), m = 4 * (l >> 4) + (v & 3);
+        if (c >= NA) continue;
+        float t = 0.f;
+        for (int sl = 0; sl < nsl; ++sl) t += red[sl][v][l];
+        if (FP8) t *= tq_sig_base(blob, G.expert_stride, sec, G.fm, STAGE, e)[c];
+        t_out[(((size_t)tile * gridDim.y + split) * 16 + m) * NA + c] = (uint16_t)f2bf_bits(t);
+    }
+}
+
+// A buffer descriptor of `bytes` bytes at p: loads past its end return zeros without a request, so a load that has nothing to
+// fetch (no further pair, a wave without a slice) is switched off by a length of 0 instead of a condition, after which the
+// compiler would wait for all loads in flight.
+__device__ inline __amdgpu_buffer_rsrc_t buffer(const uint8_t* p, uint32_t bytes)
+{
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    const uint64_t u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)a) |
+                       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(a >> 32)) << 32;
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(u), 0, (int)bytes, 0x00020000);
+}
+constexpr int BUF_NT = 2;      // non-temporal: read once, never again; the hint keeps the stream out of the caches
+
+template <int CTRL>
+__device__ inline float dpp_add(float v)
+{
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+
+// the sum of 8 bf16 values a lane over runs of LANES lanes (4, 8, 16 or 32), in every lane of the run
+template <int LANES>
+__device__ inline float run_sum(const u32x4& q)
+{
+    float s = ((bf_lo(q[0]) + bf_hi(q[0])) + (bf_lo(q[1]) + bf_hi(q[1]))) + ((bf_lo(q[2]) + bf_hi(q[2])) + (bf_lo(q[3]) + bf_hi(q[3])));
+    s = dpp_add<0xB1>(s);                        // lanes 1, 0, 3, 2 of a quad
+    s = dpp_add<0x4E>(s);                        // lanes 2, 3, 0, 1
+    if (LANES >= 8) s = dpp_add<0x141>(s);       // the row's halves mirrored
+    if (LANES >= 16) s = dpp_add<0x140>(s);      // the row mirrored
+    if (LANES >= 32) s += __shfl_xor(s, 16);
+    return s;
 }
 
 // STAGE 0: out = h[slot][F] bf16 = silu(gate) * up.   STAGE 1: out = yd[split][slot][H] fp32.
@@ -89,26 +148,27 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
                                                          const int32_t* __restrict__ row_token,
                                                          const int32_t* __restrict__ tile_e,
                                                          const int32_t* __restrict__ tile_row0,
-                                                         const int32_t* __restrict__ offsets,
+                                                         const int32_t* __restrict__ tile_rows,
                                                          const int32_t* __restrict__ ctrl,
-                                                         const float* __restrict__ tpart, int n_slices, int na_tiles,
+                                                         const uint16_t* __restrict__ t_in,
                                                          void* __restrict__ out, int32_t* __restrict__ pair_cnt,
                                                          int units_per_split, int RB, int red_off, int xs_off, int mb_off,
-                                                         const int32_t* __restrict__ row_src, int nsplit,
-                                                         const int32_t* __restrict__ tile_rows)
+                                                         const int32_t* __restrict__ row_src, int nsplit)
 {
     constexpr int UNIT_K = (GS * 16 < 64) ? 64 : GS * 16;
     constexpr int UC = UNIT_K / 64;
-    constexpr int US = UNIT_K / 16;
-    constexpr int NG = US / GS;
+    constexpr int US = UNIT_K / 32;    // 32-deep MFMA steps per unit
+    constexpr int NG = UNIT_K / (GS * 16);
+    constexpr int GT = GS / 2;         // steps per group
     constexpr int UPW = WK / UNIT_K;   // units per wave
     using WT = std::conditional_t<CW == 4, u32x4, uint32_t>;      // register type of the packed codes
     constexpr int WN = CW == 4 ? UC : UC * CW;                    // and how many of them one tile of a unit takes
+    // dense codes in units of two chunks: a 32-deep step takes step w of both chunks, so that the rows of the raw words can be exchanged
+    constexpr bool PAIRED = CW != 4 && UC > 1;
 
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     float* red = reinterpret_cast<float*>(lds + red_off);
     float* xs = reinterpret_cast<float*>(lds + xs_off);
-    uint16_t* tbuf = reinterpret_cast<uint16_t*>(lds + red_off);   // [16][NA] bf16; lives only before the pair loop
 
     // Which (row tile, split) this workgroup works on, its number `part` among the g_wg workgroups on it:
     //  * 3-D grid (layers of few experts, where the host knows how many tiles will exist): blockIdx itself;
@@ -139,8 +199,9 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
         rt = vt % n_t;
         split = vt / n_t;
     }
-    const int e = tile_e[rt], slot0 = tile_row0[rt];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 31, hf = lane >> 5;
+    const int e = tile_e[rt], slot0 = tile_row0[rt], rows = tile_rows[rt];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, col = lane & 31;
+    const int l16 = lane & 15, lrow = lane >> 4;      // MFMA: row of A / column of B and D; quarter of the contraction step / of the rows of D
     const int K = sec.K, NU = K / UNIT_K;
     const int NA = STAGE == 0 ? 2 * G.r16 : G.r16;
     const int n_lr = (G.r > 0) ? NA / 16 : 0;       // low-rank MFMA steps; step j is applied by wave j
@@ -149,53 +210,60 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
     const int range_k = (ue - ub) * UNIT_K;
     int nuw = min(UPW, ue - (ub + wave * UPW));     // units of this wave (0 for idle waves)
     if (nuw < 0) nuw = 0;
-    const int wk0 = wave * UPW * US;                // first MFMA step of this wave inside the workgroup's range
     // Column-tile pairs are dealt out dynamically among the g_wg workgroups of this (tile, split): the first one is the
     // workgroup's number among them, every further one comes from a counter (cleared by the permutation), fetched one pair
-    // ahead of its use so that the weight prefetch knows where to go.  Workgroups that get a better share of the
+    // before its weights are requested.  Workgroups that get a better share of the
     // memory system take more pairs, and all of them finish together.
     const int npairs = sec.pairs;
-    const int p0 = part;
     int32_t* cnt = pair_cnt + (size_t)rt * TQ_MAX_SPLIT + split;
-    int* pq = reinterpret_cast<int*>(lds + mb_off);            // two mailbox words
+    int* pq = reinterpret_cast<int*>(lds + mb_off);            // two mailbox words, in turn
     int got_v = 0;
     if (tid == 0) got_v = g_wg + atomicAdd(cnt, 1);
 
     const uint8_t* rec = blob + TQ_HEADER_BYTES + (size_t)e * G.expert_stride;
-    const u32x4* codes = reinterpret_cast<const u32x4*>(rec + sec.codes) + lane;
-    const uint32_t* szp = reinterpret_cast<const uint32_t*>(rec + sec.sz) + col;
-    const u32x4* bfr = reinterpret_cast<const u32x4*>(G.r > 0 ? tq_bfrag_base(blob, G.expert_stride, sec, G.fm, STAGE, e)
-                                                               : rec + sec.bfrag);
     const bool fp8 = G.fm.fp8 != 0;
     // fragment f of the right factors: 64 lanes x 16 bytes (fp16), or 64 x 8 bytes (fp8: lanes 2j, 2j + 1 share a word)
-    const int b_per = fp8 ? 32 : 64, b_lane = fp8 ? (lane >> 1) : lane;
+    const int b_per = fp8 ? 512 : 1024, b_lane = (fp8 ? (lane >> 1) : lane) * 16;
+    const uint8_t* bfr = G.r > 0 ? tq_bfrag_base(blob, G.expert_stride, sec, G.fm, STAGE, e) : rec;
+    const uint32_t codes_bytes = (uint32_t)sec.pairs * sec.chunks * (512 * CW), sz_bytes = (uint32_t)sec.pairs * sec.groups * 256;
+    const int steps_per_tile = G.r16 / 16;
+    const uint32_t b_bytes = wave < n_lr ? (uint32_t)sec.pairs * steps_per_tile * 2 * b_per : 0u;
 
-    // Unit and pair indices are clamped into the valid range instead of guarding the loads: a load under a
-    // condition makes the compiler wait for ALL outstanding loads at every later use, which would drain the
-    // one-pair-ahead prefetch at every unit.  Clamped loads repeat a neighbour's line (cache hit) and are unused.
-    const uint32_t* codes32 = reinterpret_cast<const uint32_t*>(rec + sec.codes) + lane;      // dense layouts
     auto load_w = [&](WT (&dst)[2][WN], int pair, int u) {       // unit u of this wave, both tiles
-        const int chunk0 = min(ub + wave * UPW + u, ue - 1) * UC;
+        const __amdgpu_buffer_rsrc_t rs = buffer(rec + sec.codes, pair < npairs && u < nuw ? codes_bytes : 0u);
+        const int so = (pair * sec.chunks + (ub + wave * UPW + u) * UC) * (512 * CW);
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int c = 0; c < UC; ++c) {    // read once, never again: the non-temporal hint keeps the stream out of the caches
+            for (int c = 0; c < UC; ++c) {
                 if constexpr (CW == 4) {
-                    dst[t][c] = __builtin_nontemporal_load(&codes[(((size_t)pair * sec.chunks + chunk0 + c) * 2 + t) * 64]);
+                    dst[t][c] = __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16 + (c * 2 + t) * 1024, so, BUF_NT);
                 } else {
 #pragma unroll
                     for (int d = 0; d < CW; ++d)
-                        dst[t][c * CW + d] = __builtin_nontemporal_load(
-                            &codes32[((((size_t)pair * sec.chunks + chunk0 + c) * 2 + t) * CW + d) * 64]);
+                        dst[t][c * CW + d] = __builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4 + ((c * 2 + t) * CW + d) * 256, so, BUF_NT);
                 }
             }
     };
     auto load_sz = [&](uint32_t (&dst)[NG][2], int pair, int u) {
-        const int g0 = min(ub + wave * UPW + u, ue - 1) * NG;
+        const __amdgpu_buffer_rsrc_t rs = buffer(rec + sec.sz, pair < npairs && u < nuw ? sz_bytes : 0u);
+        const int so = (pair * sec.groups + (ub + wave * UPW + u) * NG) * 256;
 #pragma unroll
         for (int gi = 0; gi < NG; ++gi)
 #pragma unroll
-            for (int t = 0; t < 2; ++t) dst[gi][t] = szp[(((size_t)pair * sec.groups + g0 + gi) * 2 + t) * 32];
+            for (int t = 0; t < 2; ++t) dst[gi][t] = __builtin_amdgcn_raw_buffer_load_b32(rs, col * 4 + (gi * 2 + t) * 128, so, 0);
+    };
+    // low-rank B fragments ride in the same prefetch: step `wave` (stage 0: steps below r16 / 16 feed the gate tile, the others the up tile)
+    const int lr_t = (STAGE == 0 && wave >= steps_per_tile) ? 1 : 0;
+    const int lr_step = wave - lr_t * steps_per_tile;
+    constexpr int NBQ = STAGE == 0 ? 1 : 2;
+    auto load_b = [&](u32x4 (&dst)[NBQ], int pair) {
+        const __amdgpu_buffer_rsrc_t rs = buffer(bfr, pair < npairs ? b_bytes : 0u);
+        const int so = (pair * steps_per_tile + lr_step) * 2 * b_per;
+        if (STAGE == 0) dst[0] = __builtin_amdgcn_raw_buffer_load_b128(rs, b_lane, so + lr_t * b_per, 0);
+        else
+#pragma unroll
+            for (int t = 0; t < NBQ; ++t) dst[t] = __builtin_amdgcn_raw_buffer_load_b128(rs, b_lane, so + t * b_per, 0);
     };
 
     // the or-operand of the unpack in a vector register (see unpack_word): opaque move, not folded to a literal
@@ -203,175 +271,89 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
     asm volatile("v_mov_b32 %0, %1" : "=v"(magic_v) : "s"(G.unpack_magic));
 
     // ---- 1. activations of the tile for the workgroup's contraction range -> LDS (row stride RB = 2*range + 16 bytes:
-    //         the rows read by one ds_read_b128 fall into different bank groups).  Only the rows that exist are
+    //         the rows read by one ds_read_b128 fall into different bank groups), their group sums beside them.  Only the rows that exist are
     //         staged; the MFMA rows beyond them re-read the last one and their results are never stored.
-    //         Everything the set-up needs (these rows, the low-rank slices) is requested and awaited BEFORE the first
-    //         weights are asked for: at kernel start every workgroup asks for its first pair at once, and small
-    //         loads queued behind that burst would arrive only after it.
-    // (DEAL reads the tile's row count from the tile table: its tile index already waited for a load, and offsets
-    // would be one more in the chain)
-    const int rows = DEAL ? tile_rows[rt] : min(16, offsets[e + 1] - slot0);
+    //         Up to eight rows of 4096 are requested at once, and before the first weights: at kernel start every workgroup asks for its
+    //         first pair at once, and small loads queued behind that burst would arrive only after it.  What the set-up waits for is kept
+    //         short (the intermediate comes summed up, the group sums cost no loads): it is 6 us of a kernel in which nothing streams.
     const int gran = range_k / 8;                 // 16-byte chunks per row
     const int total = rows * gran;
-    auto stage_load = [&](int c0, u32x4 (&v)[4], int (&dst)[4]) {
+    auto stage_load = [&](int c0, u32x4 (&v)[4]) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int c = min(c0 + j * 512 + tid, total - 1);
             const int row = c / gran, kg = c - row * gran;
             const size_t src_row = STAGE == 0 ? (size_t)row_token[slot0 + row] : (size_t)(slot0 + row);
             v[j] = *reinterpret_cast<const u32x4*>(xin + src_row * K + (size_t)ub * UNIT_K + (size_t)kg * 8);
-            dst[j] = row * RB + kg * 16;
         }
     };
-    u32x4 xv0[4];
-    int xd0[4];
-    stage_load(0, xv0, xd0);
-
-    // ---- the slices of the low-rank intermediate: up to 16 per workgroup range and column tile of t.  Requested
-    //         before the weights as well, and unconditionally (layers without factors read a valid dummy word with
-    //         weight zero).
-    // Sigma of fp8 factors for this lane's columns of t (requested with the slices; 1 otherwise, from a valid dummy word)
-    float sgv[4];
-    {
-        const float* sp = fp8 ? tq_sig_base(blob, G.expert_stride, sec, G.fm, STAGE, e) : reinterpret_cast<const float*>(ctrl);
+    auto stage_store = [&](int c0, const u32x4 (&v)[4]) {
 #pragma unroll
-        for (int ta = 0; ta < 4; ++ta) sgv[ta] = sp[fp8 ? min(32 * ta + col, NA - 1) : 0];
-    }
-    float tv[4][16];
-    {
-        const int sl0 = (ub * UNIT_K) / SK_PRE_K;
-        const int nsl = (range_k + SK_PRE_K - 1) / SK_PRE_K;
-        const float* tp = n_lr > 0 ? tpart : reinterpret_cast<const float*>(ctrl);
-        const size_t live = n_lr > 0 ? 1 : 0;
-        if (STAGE == 0 && row_src) {
-            // slices stored per assignment (they came with the permutation's launch): this lane's value of step
-            // `wave` belongs to row row_of_v(wave, hf) of the tile; padding rows repeat the last one
-            const int m = min(row_of_v(wave, hf), rows - 1);
-            const size_t v = (size_t)row_src[slot0 + m];
-#pragma unroll
-            for (int ta = 0; ta < 4; ++ta)
-#pragma unroll
-                for (int sl = 0; sl < 16; ++sl) {
-                    const size_t idx = ((v * n_slices + sl0 + min(sl, nsl - 1)) * na_tiles + min(ta, max(na_tiles, 1) - 1)) * 32 + col;
-                    tv[ta][sl] = tp[idx * live];
-                }
-        } else {
-#pragma unroll
-            for (int ta = 0; ta < 4; ++ta)
-#pragma unroll
-                for (int sl = 0; sl < 16; ++sl) {
-                    const size_t idx = (((size_t)rt * n_slices + sl0 + min(sl, nsl - 1)) * na_tiles + min(ta, max(na_tiles, 1) - 1)) * 512 + wave * 64 + lane;
-                    tv[ta][sl] = tp[idx * live];
-                }
-        }
-    }
-
-#pragma unroll
-    for (int j = 0; j < 4; ++j) *reinterpret_cast<u32x4*>(lds + xd0[j]) = xv0[j];
-    for (int c0 = 4 * 512; c0 < total; c0 += 4 * 512) {      // more than four chunks per thread: the rare tall tiles
-        u32x4 v[4];
-        int dst[4];
-        stage_load(c0, v, dst);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) *reinterpret_cast<u32x4*>(lds + dst[j]) = v[j];
-    }
-    float tsum[4] = {0.f, 0.f, 0.f, 0.f};
-    {
-        const int nsl = (range_k + SK_PRE_K - 1) / SK_PRE_K;
-#pragma unroll
-        for (int ta = 0; ta < 4; ++ta)
-#pragma unroll
-            for (int sl = 0; sl < 16; ++sl) tsum[ta] += sl < nsl ? tv[ta][sl] : 0.f;
-    }
-    // the first pair's codes: their latency hides behind the rest of the set-up (group sums, t fragments)
-    WT wq[UPW][2][WN];
-    uint32_t szq[UPW][NG][2];
-#pragma unroll
-    for (int u = 0; u < UPW; ++u) { load_w(wq[u], p0, u); load_sz(szq[u], p0, u); }
-    // low-rank B fragments ride in the same prefetch (one pair ahead); waves without a low-rank step, and layers
-    // without factors, read a valid dummy location
-    const int steps_per_tile = G.r16 / 16;
-    const int lr_t = (STAGE == 0 && wave >= steps_per_tile) ? 1 : 0;
-    const int lr_step = (G.r > 0) ? min(wave - lr_t * steps_per_tile, steps_per_tile - 1) : 0;
-    const u32x4* bsrc = (G.r > 0) ? bfr + b_lane : codes;
-    const size_t bstride = (G.r > 0) ? (size_t)steps_per_tile * 2 * b_per : (size_t)0;      // dummy reads stay in the first 2 KB of the codes
-    auto load_b = [&](u32x4 (&dst)[2], int pair) {
-        if (STAGE == 0) {
-            dst[0] = bsrc[(size_t)pair * bstride + ((size_t)lr_step * 2 + lr_t) * b_per];
-            dst[1] = dst[0];
-        } else {
-            dst[0] = bsrc[(size_t)pair * bstride + ((size_t)lr_step * 2 + 0) * b_per];
-            dst[1] = bsrc[(size_t)pair * bstride + ((size_t)lr_step * 2 + 1) * b_per];
-        }
-    };
-    auto b_operand = [&](const u32x4& raw) -> bf16x8 { return fp8 ? fp8_frag_to_bf8(raw, lane) : half8_to_bf8(raw); };
-    u32x4 bq[2];
-    load_b(bq, p0);
-
-    if (tid == 0) pq[0] = got_v;
-    lds_barrier();
-    const int xrow_off = min(col & 15, rows - 1) * RB;
-    auto lds_x = [&](int kl) -> bf16x8 {       // fragment of MFMA step kl (relative to the workgroup's range)
-        Frag f;
-        f.q = *reinterpret_cast<const u32x4*>(lds + xrow_off + (kl * 16 + 8 * hf) * 2);
-        return f.v;
-    };
-
-    // ---- 2. group sums of the activations (MFMA against ones: every column of the result holds the row sums)
-    {
-        Frag ones;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) ones.u[j] = 0x3F803F80u;
-#pragma unroll
-        for (int u = 0; u < UPW; ++u) {
-            if (u < nuw) {
-#pragma unroll
-                for (int gi = 0; gi < NG; ++gi) {
-                    f32x16 sD;
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) sD[v] = 0.f;
-#pragma unroll
-                    for (int ks = 0; ks < GS; ++ks)
-                        sD = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_x(wk0 + u * US + gi * GS + ks), ones.v, sD, 0, 0, 0);
-                    if (col == 0) {
-                        const int gl = (wave * UPW + u) * NG + gi;      // group index inside the workgroup's range
-#pragma unroll
-                        for (int v = 0; v < 8; ++v) xs[gl * 16 + row_of_v(v, hf)] = sD[v];
-                    }
-                }
+        for (int j = 0; j < 4; ++j) {
+            // a group is a run of 2 GS chunks (4 to 32, a divisor of 64) and `total` a whole number of them: its lanes are all in range or all not
+            const float s = run_sum<2 * GS>(v[j]);
+            const int c = c0 + j * 512 + tid;
+            if (c < total) {
+                const int row = c / gran, kg = c - row * gran;
+                *reinterpret_cast<u32x4*>(lds + row * RB + kg * 16) = v[j];
+                if ((kg & (2 * GS - 1)) == 0) xs[kg / (2 * GS) * 16 + row] = s;
             }
         }
-    }
-    // ---- 3. low-rank intermediate: add the slices of this range, round to bf16, keep it as MFMA fragments
+    };
+    u32x4 xa0[4], xa1[4];
+    const bool two = total > 4 * 512;
+    stage_load(0, xa0);
+    if (two) stage_load(4 * 512, xa1);
+    // ---- low-rank intermediate: the A operand of the 16-deep step `wave`, rows of a step at lane rows 0 and 2 (the others meet zeros)
     Frag tf;
 #pragma unroll
     for (int j = 0; j < 4; ++j) tf.u[j] = 0;
-    if (n_lr > 0) {
-        const int m = row_of_v(wave, hf);          // wave w owns result rows row_of_v(w, hf)
-#pragma unroll
-        for (int ta = 0; ta < 4; ++ta) {
-            const int c = 32 * ta + col;
-            if (ta < na_tiles && c < NA) tbuf[m * NA + c] = (uint16_t)f2bf_bits(fp8 ? tsum[ta] * sgv[ta] : tsum[ta]);
-        }
-        lds_barrier();
-        if (wave < n_lr) tf.q = *reinterpret_cast<const u32x4*>(tbuf + (col & 15) * NA + 16 * wave + 8 * hf);
+    if (wave < n_lr) {
+        const uint16_t* tr;
+        if (STAGE == 0 && row_src) tr = t_in + (size_t)row_src[slot0 + min(l16, rows - 1)] * NA;      // stored per assignment
+        else tr = t_in + (((size_t)rt * nsplit + split) * 16 + l16) * NA;
+        if ((lrow & 1) == 0) tf.q = *reinterpret_cast<const u32x4*>(tr + 16 * wave + 4 * lrow);
     }
-    lds_barrier();     // xs is complete; tbuf has been read: the reduction buffer may be reused
+    WT wq[UPW][2][WN];
+    uint32_t szq[UPW][NG][2];
+    u32x4 bq[NBQ];
+#pragma unroll
+    for (int u = 0; u < UPW; ++u) { load_w(wq[u], part, u); load_sz(szq[u], part, u); }
+    load_b(bq, part);
+    stage_store(0, xa0);
+    if (two) {
+        stage_store(4 * 512, xa1);
+        for (int c0 = 8 * 512; c0 < total; c0 += 4 * 512) {      // the rare tall tiles
+            stage_load(c0, xa0);
+            stage_store(c0, xa0);
+        }
+    }
+    if (tid == 0) pq[0] = got_v;
+    lds_barrier();
+    const int xrow_off = min(l16, rows - 1) * RB + (PAIRED ? 64 * (lrow & 1) + 8 * (lrow >> 1) : 16 * (lrow & 1) + 8 * (lrow >> 1)) * 2 +
+                         wave * WK * 2;
+    auto lds_x = [&](int s) -> bf16x8 {       // A operand of step s of this wave (a constant at every call)
+        const int k = PAIRED ? 128 * (s / 4) + 16 * (s % 4) : 32 * s;
+        Frag f;
+        f.q = *reinterpret_cast<const u32x4*>(lds + xrow_off + k * 2);
+        return f.v;
+    };
+    auto b_operand = [&](const u32x4& raw, Frag& lo, Frag& hi) {
+        lo.v = fp8 ? fp8_frag_to_bf8(raw, lane) : half8_to_bf8(raw);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { hi.u[j] = 0; swap_rows(lo.u[j], hi.u[j]); }
+    };
 
-    // ---- 4. the stream over this workgroup's column-tile pairs
-    int pnext_raw = pq[0];
-    int it = 0;
-    for (int pair = p0; pair < npairs;) {
-        const int pnext = pnext_raw < npairs ? pnext_raw : pair;     // nothing left: re-request this pair (its scales and
-                                                                     // factors hit the cache; the codes are fetched again, once
-                                                                     // per workgroup: measured cheaper than a guarded prefetch)
+    // ---- 2. the stream over this workgroup's column-tile pairs
+    int pnext = __builtin_amdgcn_readfirstlane(pq[0]), it = 0;
+    for (int pair = part; pair < npairs;) {
         int fetched = 0;
         if (tid == 0) fetched = g_wg + atomicAdd(cnt, 1);       // the pair after the next one
-        float acc8[2][8];
+        f32x4 acc[2][2];
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int v = 0; v < 8; ++v) acc8[t][v] = 0.f;
+            for (int n = 0; n < 2; ++n) acc[t][n] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int u = 0; u < UPW; ++u) {
             WT wc[2][WN];
@@ -387,72 +369,93 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
             load_w(wq[u], pnext, u);
             load_sz(szq[u], pnext, u);
             if (u < nuw) {
+                if constexpr (PAIRED) {
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+#pragma unroll
+                        for (int c = 0; c < UC; c += 2)
+#pragma unroll
+                            for (int i = 0; i < CW; ++i) swap_rows(wc[t][c * CW + i], wc[t][(c + 1) * CW + i]);
+                }
                 bf16x8 xq[2];
-                xq[0] = lds_x(wk0 + u * US);
+                xq[0] = lds_x(u * US);
 #pragma unroll
                 for (int gi = 0; gi < NG; ++gi) {
-                    f32x16 part[2];
+                    f32x4 pt[2][2];
 #pragma unroll
-                    for (int ks = 0; ks < GS; ++ks) {
-                        const int kidx = gi * GS + ks;
-                        if (kidx + 1 < US) xq[(kidx + 1) & 1] = lds_x(wk0 + u * US + kidx + 1);   // next step's fragment
-                        const bf16x8 xa = xq[kidx & 1];
+                    for (int ks = 0; ks < GT; ++ks) {
+                        const int s = gi * GT + ks;
+                        if (s + 1 < US) xq[(s + 1) & 1] = lds_x(u * US + s + 1);   // next step's operand
+                        const bf16x8 xa = xq[s & 1];
 #pragma unroll
                         for (int t = 0; t < 2; ++t) {
-                            bf16x8 bw;
-                            if constexpr (CW == 4) bw = unpack_word(word_of(wc[t][kidx / 4], kidx % 4), G.unpack_mask, magic_v);
-                            else bw = unpack_dense<CW>(&wc[t][(kidx / 4) * CW], kidx % 4, G.unpack_mask, magic_v);
-                            if (ks == 0) {
-                                f32x16 zero;
+                            Frag bw[2];      // columns 0..15 and 16..31 of the tile
+                            if constexpr (CW == 4) {
+                                uint32_t w0 = word_of(wc[t][s / 2], 2 * s % 4), w1 = word_of(wc[t][s / 2], 2 * s % 4 + 1);
+                                swap_rows(w0, w1);
+                                bw[0].v = unpack_word(w0, G.unpack_mask, magic_v);
+                                bw[1].v = unpack_word(w1, G.unpack_mask, magic_v);
+                            } else if constexpr (PAIRED) {
 #pragma unroll
-                                for (int v = 0; v < 16; ++v) zero[v] = 0.f;
-                                part[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa, bw, zero, 0, 0, 0);
+                                for (int n = 0; n < 2; ++n)
+                                    bw[n].v = unpack_dense<CW>(&wc[t][(s / 4 * 2 + n) * CW], s % 4, G.unpack_mask, magic_v);
                             } else {
-                                part[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa, bw, part[t], 0, 0, 0);
+#pragma unroll
+                                for (int n = 0; n < 2; ++n)
+                                    bw[n].v = unpack_dense<CW>(&wc[t][s / 2 * CW], 2 * (s % 2) + n, G.unpack_mask, magic_v);
+#pragma unroll
+                                for (int j = 0; j < 4; ++j) swap_rows(bw[0].u[j], bw[1].u[j]);
                             }
+#pragma unroll
+                            for (int n = 0; n < 2; ++n)
+                                pt[t][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, bw[n].v, ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : pt[t][n],
+                                                                                   0, 0, 0);
                         }
                     }
                     // fold the group: acc += s * part + c * xsum, c = -s (128 + z)
                     const int gl = (wave * UPW + u) * NG + gi;
-                    const float4 x0 = *reinterpret_cast<const float4*>(xs + gl * 16 + 4 * hf);
-                    const float4 x1 = *reinterpret_cast<const float4*>(xs + gl * 16 + 8 + 4 * hf);
-                    const float xv[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+                    const f32x4 xv = *reinterpret_cast<const f32x4*>(xs + gl * 16 + 4 * lrow);
 #pragma unroll
                     for (int t = 0; t < 2; ++t) {
                         const float s = tq_half_bits_to_float((uint16_t)(szc[gi][t] & 0xFFFF));
                         const float z = tq_half_bits_to_float((uint16_t)(szc[gi][t] >> 16));
                         const float c = -s * (128.0f + z);
+                        // this lane's column is lane % 32; what the two halves of the tile need is that of lane % 16 and of lane % 16 + 16
+                        uint32_t sn[2], cn[2];
+                        sn[0] = sn[1] = __float_as_uint(s);
+                        cn[0] = cn[1] = __float_as_uint(c);
+                        swap_rows(sn[0], sn[1]);
+                        swap_rows(cn[0], cn[1]);
 #pragma unroll
-                        for (int v = 0; v < 8; ++v) acc8[t][v] = fmaf(c, xv[v], fmaf(s, part[t][v], acc8[t][v]));
+                        for (int n = 0; n < 2; ++n)
+#pragma unroll
+                            for (int v = 0; v < 4; ++v)
+                                acc[t][n][v] = fmaf(__uint_as_float(cn[n]), xv[v], fmaf(__uint_as_float(sn[n]), pt[t][n][v], acc[t][n][v]));
                     }
                 }
             }
         }
-        // low-rank step `wave` (stage 0: steps below r16/16 feed the gate tile, the others the up tile)
         {
-            u32x4 bc[2] = {bq[0], bq[1]};
+            u32x4 bc[NBQ];
+#pragma unroll
+            for (int t = 0; t < NBQ; ++t) bc[t] = bq[t];
             load_b(bq, pnext);
             if (wave < n_lr) {
-                f32x16 zero;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) zero[v] = 0.f;
-                if (STAGE == 0) {
-                    const f32x16 lr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tf.v, b_operand(bc[0]), zero, 0, 0, 0);
-#pragma unroll
-                    for (int v = 0; v < 8; ++v) {
-                        if (lr_t == 0) acc8[0][v] += lr[v]; else acc8[1][v] += lr[v];
-                    }
-                } else {
-#pragma unroll
-                    for (int t = 0; t < 2; ++t) {
-                        const f32x16 lr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tf.v, b_operand(bc[t]), zero, 0, 0, 0);
-#pragma unroll
-                        for (int v = 0; v < 8; ++v) acc8[t][v] += lr[v];
+                for (int t = 0; t < NBQ; ++t) {
+                    Frag lo, hi;
+                    b_operand(bc[t], lo, hi);
+                    if (STAGE == 0 && lr_t == 1) {
+                        acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tf.v, lo.v, acc[1][0], 0, 0, 0);
+                        acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tf.v, hi.v, acc[1][1], 0, 0, 0);
+                    } else {
+                        acc[t][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tf.v, lo.v, acc[t][0], 0, 0, 0);
+                        acc[t][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tf.v, hi.v, acc[t][1], 0, 0, 0);
                     }
                 }
             }
         }
-        // ---- wavefront reduction: wave w keeps row group v = w and publishes its other seven
+        // ---- wavefront reduction: wave w keeps result w (half w / 4 of the tile's columns, row w % 4 of each four) and publishes its other seven
         {
             float* mine = red + wave * (7 * 2 * 64);
 #pragma unroll
@@ -461,7 +464,7 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
                 for (int v = 0; v < 8; ++v) {
                     if (v != wave) {
                         const int slot = v < wave ? v : v - 1;
-                        mine[(t * 7 + slot) * 64 + lane] = acc8[t][v];
+                        mine[(t * 7 + slot) * 64 + lane] = acc[t][v >> 2][v & 3];
                     }
                 }
             if (tid == 0) pq[(it + 1) & 1] = fetched;
@@ -473,8 +476,9 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
             for (int t = 0; t < 2; ++t)
 #pragma unroll
                 for (int v = 0; v < 8; ++v)
-                    if (v == wave) own[t] = acc8[t][v];
+                    if (v == wave) own[t] = acc[t][v >> 2][v & 3];
             float tot[2] = {0.f, 0.f};
+#pragma unroll
             for (int ww = 0; ww < SK_NW; ++ww) {           // fixed order: run-to-run identical sums
                 if (ww == wave) {
                     tot[0] += own[0];
@@ -486,21 +490,21 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
                     tot[1] += src[(1 * 7 + slot) * 64 + lane];
                 }
             }
-            const int m = row_of_v(wave, hf);
+            const int m = 4 * lrow + (wave & 3), n = 16 * (wave >> 2) + l16;
             if (m < rows) {
                 if (STAGE == 0) {
                     const float hv = silu_mul(tot[0], tot[1]);
-                    reinterpret_cast<uint16_t*>(out)[(size_t)(slot0 + m) * G.F + 32 * pair + col] = (uint16_t)f2bf_bits(hv);
+                    reinterpret_cast<uint16_t*>(out)[(size_t)(slot0 + m) * G.F + 32 * pair + n] = (uint16_t)f2bf_bits(hv);
                 } else {
-                    float* yd = reinterpret_cast<float*>(out) + (size_t)split * G.a_tot * G.H + (size_t)(slot0 + m) * G.H + 64 * pair + col;
+                    float* yd = reinterpret_cast<float*>(out) + (size_t)split * G.a_tot * G.H + (size_t)(slot0 + m) * G.H + 64 * pair + n;
                     yd[0] = tot[0];
                     yd[32] = tot[1];
                 }
             }
         }
         lds_barrier();
-        pair = pnext_raw;
-        pnext_raw = pq[(it + 1) & 1];
+        pair = pnext;
+        pnext = __builtin_amdgcn_readfirstlane(pq[(it + 1) & 1]);
         ++it;
     }
 }
@@ -508,9 +512,9 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
 template <int STAGE, int GS, int CW, int WK>
 tq_status launch_skinny(const MGeom& G, const TqSection& sec, const uint8_t* blob, const uint16_t* xin,
                         const int32_t* row_token, const int32_t* tile_e, const int32_t* tile_row0,
-                        const int32_t* offsets, const int32_t* ctrl, float* tpart, int n_slices, int na_tiles,
+                        const int32_t* tile_rows, const int32_t* ctrl, const uint16_t* t_in,
                         void* out, int32_t* pair_cnt, int row_tiles, int nsplit, int units_per_split,
-                        hipStream_t st, const int32_t* row_src, const int32_t* tile_rows)
+                        hipStream_t st, const int32_t* row_src)
 {
     constexpr int UNIT_K = (GS * 16 < 64) ? 64 : GS * 16;
     const int range_k = units_per_split * UNIT_K;
@@ -525,7 +529,7 @@ tq_status launch_skinny(const MGeom& G, const TqSection& sec, const uint8_t* blo
     const TqDeviceState* ds = nullptr;
     if (tqi_device_state(&ds) != TQ_OK) return TQ_ERR_HIP;
     dim3 grid;
-    int deal_nsplit = 0;
+    bool deal = false;
     if (G.ne <= 32) {
         // few experts: nearly all of them receive rows, the host's count of the tiles is good
         const int tiles_est = (int)std::min<int64_t>(G.a_tot, std::min(G.ne, row_tiles));
@@ -540,17 +544,15 @@ tq_status launch_skinny(const MGeom& G, const TqSection& sec, const uint8_t* blo
         const long n_wg = std::max<long>(ds->n_cu, (long)row_tiles * nsplit);
         if (n_wg > 0x7FFFFFFF) return TQ_ERR_UNSUPPORTED;
         grid = dim3((unsigned)n_wg);
-        deal_nsplit = nsplit;
+        deal = true;
     }
     // (dynamic-LDS limit of both instantiations: raised once per device by tqi_setup_skinny)
-    if (deal_nsplit == 0)
+    if (!deal)
         hipLaunchKernelGGL((moe_skinny_kernel<STAGE, GS, CW, false, WK>), grid, dim3(512), smem, st, G, sec, blob, xin, row_token, tile_e,
-                           tile_row0, offsets, ctrl, (const float*)tpart, n_slices, na_tiles, out, pair_cnt, units_per_split,
-                           RB, red_off, xs_off, mb_off, row_src, deal_nsplit, tile_rows);
+                           tile_row0, tile_rows, ctrl, t_in, out, pair_cnt, units_per_split, RB, red_off, xs_off, mb_off, row_src, nsplit);
     else
         hipLaunchKernelGGL((moe_skinny_kernel<STAGE, GS, CW, true, WK>), grid, dim3(512), smem, st, G, sec, blob, xin, row_token, tile_e,
-                           tile_row0, offsets, ctrl, (const float*)tpart, n_slices, na_tiles, out, pair_cnt, units_per_split,
-                           RB, red_off, xs_off, mb_off, row_src, deal_nsplit, tile_rows);
+                           tile_row0, tile_rows, ctrl, t_in, out, pair_cnt, units_per_split, RB, red_off, xs_off, mb_off, row_src, nsplit);
     TQ_CHECK_LAUNCH();
     return TQ_OK;
 }
@@ -558,19 +560,18 @@ tq_status launch_skinny(const MGeom& G, const TqSection& sec, const uint8_t* blo
 template <int STAGE>
 tq_status launch_skinny_gs(int gs, int cw, const MGeom& G, const TqSection& sec, const uint8_t* blob, const uint16_t* xin,
                            const int32_t* row_token, const int32_t* tile_e, const int32_t* tile_row0,
-                           const int32_t* offsets, const int32_t* ctrl, float* tpart, int n_slices, int na_tiles,
+                           const int32_t* tile_rows, const int32_t* ctrl, const uint16_t* t_in,
                            void* out, int32_t* pair_cnt, int row_tiles, int nsplit, int units_per_split,
-                           hipStream_t st, const int32_t* row_src, const int32_t* tile_rows, int wave_k)
+                           hipStream_t st, const int32_t* row_src, int wave_k)
 {
 #define TQ_SK(GSV, CWV)                                                                                                   \
     do {                                                                                                                  \
         if (wave_k == 256 && GSV * 16 <= 256)                                                                             \
             return launch_skinny<STAGE, GSV, CWV, (GSV * 16 <= 256 ? 256 : 512)>(                                         \
-                G, sec, blob, xin, row_token, tile_e, tile_row0, offsets, ctrl, tpart, n_slices, na_tiles, out, pair_cnt, \
-                row_tiles, nsplit, units_per_split, st, row_src, tile_rows);                                              \
-        return launch_skinny<STAGE, GSV, CWV, 512>(G, sec, blob, xin, row_token, tile_e, tile_row0, offsets, ctrl, tpart,  \
-                                                   n_slices, na_tiles, out, pair_cnt, row_tiles, nsplit, units_per_split, \
-                                                   st, row_src, tile_rows);                                               \
+                G, sec, blob, xin, row_token, tile_e, tile_row0, tile_rows, ctrl, t_in, out, pair_cnt, row_tiles, nsplit, \
+                units_per_split, st, row_src);                                                                            \
+        return launch_skinny<STAGE, GSV, CWV, 512>(G, sec, blob, xin, row_token, tile_e, tile_row0, tile_rows, ctrl, t_in, \
+                                                   out, pair_cnt, row_tiles, nsplit, units_per_split, st, row_src);       \
     } while (0)
     if (cw == 4) {
         switch (gs) {
@@ -657,53 +658,49 @@ tq_status tqi_forward_skinny(const TqLayout& L, const TqWorkspace& W, const uint
     G.unpack_magic = 0x43004300u;
     G.zc_ws = nullptr; G.zc_stride = 0; G.zc_d_off = 0;
     const int32_t* ctrl = reinterpret_cast<const int32_t*>(ws + W.ctrl);
-    const int32_t* offsets = reinterpret_cast<const int32_t*>(ws + W.offsets);
     const int32_t* row_token = reinterpret_cast<const int32_t*>(ws + W.row_token);
     const int32_t* tile_e = reinterpret_cast<const int32_t*>(ws + W.tile_e) + 2 * (size_t)W.rt_max;      // 16-row tiling
     const int32_t* tile_row0 = reinterpret_cast<const int32_t*>(ws + W.tile_row0) + 2 * (size_t)W.rt_max;
     const int32_t* tile_rows = tile_row0 + (size_t)TQ_N_TILINGS * W.rt_max;      // row counts of the same tiling
     uint16_t* h = reinterpret_cast<uint16_t*>(ws + W.h);
     float* yd = reinterpret_cast<float*>(ws + W.yd);
-    float* tpart = reinterpret_cast<float*>(ws + W.tpart);
+    uint16_t* t_bf = reinterpret_cast<uint16_t*>(ws + W.tpart);
     const int gs = L.g / 16;
     const int rt16 = W.a_tot / 16 + L.E + L.S;
 
     int ns, ups;
     plan_split(L.H, L.g, &ns, &ups);
-    const int sl_gu = (L.H + SK_PRE_K - 1) / SK_PRE_K, sl_d = (L.F + SK_PRE_K - 1) / SK_PRE_K;
-    const int nat_gu = L.r > 0 ? L.gu.na_tiles : 0, nat_d = L.r > 0 ? L.d.na_tiles : 0;
-    // decode batches proper: the gate/up slices were computed per assignment in the permutation's launch
+    const int unit_k = L.g < 64 ? 64 : L.g;
+    // the pre-pass of one stage: a wave per 256-wide slice of a split's range (at most 4096)
+    auto pre = [&](auto kernel, const TqSection& sec, const uint16_t* xin) {
+        const int range_k = std::min(ups * unit_k, sec.K), nsl = (range_k + SK_PRE_K - 1) / SK_PRE_K;
+        hipLaunchKernelGGL(kernel, dim3(rt16, ns, sec.na_tiles), dim3(64 * nsl), 0, stream, G, sec, blob, xin, row_token, tile_e, tile_row0,
+                           tile_rows, ctrl, t_bf, range_k);
+    };
+    // decode batches proper: that of gate/up was computed per assignment in the permutation's launch
     const bool by_assign = tqi_pre_by_assign(L, W);
     const int32_t* row_src = by_assign ? reinterpret_cast<const int32_t*>(ws + W.row_src) : nullptr;
     if (L.r > 0 && !by_assign) {
-        if (L.fm.fp8)
-            hipLaunchKernelGGL((skinny_pre_kernel<0, true>), dim3(rt16, sl_gu, nat_gu), dim3(64), 0, stream, G, L.gu, blob, x, row_token,
-                               tile_e, tile_row0, offsets, ctrl, tpart, sl_gu, nat_gu);
-        else
-            hipLaunchKernelGGL((skinny_pre_kernel<0, false>), dim3(rt16, sl_gu, nat_gu), dim3(64), 0, stream, G, L.gu, blob, x, row_token,
-                               tile_e, tile_row0, offsets, ctrl, tpart, sl_gu, nat_gu);
+        if (L.fm.fp8) pre(skinny_pre_kernel<0, true>, L.gu, x);
+        else pre(skinny_pre_kernel<0, false>, L.gu, x);
         TQ_CHECK_LAUNCH();
     }
     tqi_record_stage(2, stream);
     int32_t* pair_cnt = reinterpret_cast<int32_t*>(ws + W.sk_cnt);
     if (W.sk_cnt_n < 2 * W.rt_max * TQ_MAX_SPLIT) return TQ_ERR_UNSUPPORTED;
-    tq_status rc = launch_skinny_gs<0>(gs, L.cw, G, L.gu, blob, x, row_token, tile_e, tile_row0, offsets, ctrl, tpart, sl_gu, nat_gu,
-                                       h, pair_cnt, rt16, 1, ups, stream, row_src, tile_rows, wave_k_of(L.H, L.g));
+    tq_status rc = launch_skinny_gs<0>(gs, L.cw, G, L.gu, blob, x, row_token, tile_e, tile_row0, tile_rows, ctrl, t_bf, h, pair_cnt, rt16, 1,
+                                       ups, stream, row_src, wave_k_of(L.H, L.g));
     if (rc != TQ_OK) return rc;
     tqi_record_stage(3, stream);
+    plan_split(L.F, L.g, &ns, &ups);
     if (L.r > 0) {
-        if (L.fm.fp8)
-            hipLaunchKernelGGL((skinny_pre_kernel<1, true>), dim3(rt16, sl_d, nat_d), dim3(64), 0, stream, G, L.d, blob, h, row_token,
-                               tile_e, tile_row0, offsets, ctrl, tpart, sl_d, nat_d);
-        else
-            hipLaunchKernelGGL((skinny_pre_kernel<1, false>), dim3(rt16, sl_d, nat_d), dim3(64), 0, stream, G, L.d, blob, h, row_token,
-                               tile_e, tile_row0, offsets, ctrl, tpart, sl_d, nat_d);
+        if (L.fm.fp8) pre(skinny_pre_kernel<1, true>, L.d, h);
+        else pre(skinny_pre_kernel<1, false>, L.d, h);
         TQ_CHECK_LAUNCH();
     }
     tqi_record_stage(4, stream);
-    plan_split(L.F, L.g, &ns, &ups);
-    rc = launch_skinny_gs<1>(gs, L.cw, G, L.d, blob, h, row_token, tile_e, tile_row0, offsets, ctrl, tpart, sl_d, nat_d, yd,
-                             pair_cnt + (size_t)W.rt_max * TQ_MAX_SPLIT, rt16, ns, ups, stream, nullptr, tile_rows, wave_k_of(L.F, L.g));
+    rc = launch_skinny_gs<1>(gs, L.cw, G, L.d, blob, h, row_token, tile_e, tile_row0, tile_rows, ctrl, t_bf, yd,
+                             pair_cnt + (size_t)W.rt_max * TQ_MAX_SPLIT, rt16, ns, ups, stream, nullptr, wave_k_of(L.F, L.g));
     if (rc != TQ_OK) return rc;
     *nsplit_out = ns;
     return TQ_OK;
