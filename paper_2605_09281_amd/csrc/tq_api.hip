@@ -234,8 +234,8 @@ tq_status forward_impl(const tq_layer_desc* desc, const void* packed, const void
     const bool with_pre = desc->act_dtype == TQ_ACT_BF16 && tqi_bf16_takes_skinny(L, W, desc->flags) && tqi_pre_by_assign(L, W);
     if (with_pre) {
         pre.x = (const uint16_t*)x; pre.blob = (const uint8_t*)packed; pre.expert_stride = L.expert_stride;
-        pre.sec = L.gu; pre.fm = L.fm; pre.t = (uint16_t*)(ws + W.tpart); pre.H = L.H;
-        pre.n_slices = (L.H + 255) / 256; pre.na_tiles = L.gu.na_tiles; pre.na = 2 * L.r16; pre.a_tot = W.a_tot;
+        pre.sec = L.gu; pre.fm = L.fm; pre.t = (float*)(ws + W.tpart); pre.H = L.H;
+        pre.n_parts = (L.H + 256 * TQ_PRE_PART_SLICES - 1) / (256 * TQ_PRE_PART_SLICES); pre.na_tiles = L.gu.na_tiles; pre.na = 2 * L.r16; pre.a_tot = W.a_tot;
     }
     // routing asked for as well: inside the permutation's launch where that is one wave's work, else by its own kernel
     if (route && !tqi_route_fusable(T, L.E, L.S, L.k, W.nblk)) {

@@ -335,18 +335,22 @@ __device__ inline int tq_find_expert(const int32_t* __restrict__ offsets, int n,
 
 // Decode batches: the low-rank intermediate of gate/up, t = x A_e, computed per ASSIGNMENT (it needs the routing
 // table only, not the permutation) so that it can share the permutation's launch:
-//   t[v][c] = bf16(sigma_c * sum over kk of x[token(v)][kk] * A_e(v)[kk][c])      (summed in fp32, 256-wide slices in order)
+//   t[v][part][c] = sigma_c * sum over the kk of the part of x[token(v)][kk] * A_e(v)[kk][c]      (fp32)
 // v = t * k + j for routed assignments, T * k + s * T + t for shared expert s.
 #define TQ_PRE_ASSIGN_MAX_ROWS 256    // assignment rows up to which the decode path takes this form (A_e is read per row;
                                       // measured: saves 7 % of the step at 96 rows, 5 % at 160, 1-2 % at 256)
+// The decode path's low-rank intermediates are left in parts of this many 256-wide slices of the contraction, a workgroup each (a decode
+// workgroup's range is at most 4096 wide)
+#define TQ_PRE_PART_SLICES 4
+#define TQ_PRE_MAX_PARTS (16 / TQ_PRE_PART_SLICES)
 struct TqPreByAssign {
     const uint16_t* x;       // [T][H] bf16
     const uint8_t* blob;
     size_t expert_stride;
     TqSection sec;           // section GU
     TqFactorMap fm;
-    uint16_t* t;             // [a_tot][na]
-    int32_t H, n_slices, na_tiles, na, a_tot;      // (at most 16 slices: the decode kernels take a hidden size of at most 4096)
+    float* t;                // [a_tot][n_parts][na]
+    int32_t H, n_parts, na_tiles, na, a_tot;
 };
 
 // Routing inputs of tq_route_moe_forward: when the single-wave permutation runs (one chunk of assignments) and the

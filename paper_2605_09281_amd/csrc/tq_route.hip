@@ -690,18 +690,18 @@ __device__ inline void permute_small_body(const int32_t* __restrict__ idx, const
     if ((flags & TQ_FLAG_BIT_BLOB) && ctrl && lane == 0) { ctrl[1] = 0; ctrl[2] = 0; ctrl[3] = 0; ctrl[4] = 0; ctrl[5] = 0; }
 }
 
-// One workgroup per (assignment v, 32-column tile of t), a wave per 256-wide slice of the contraction: see TqPreByAssign.  Plain fp32 FMAs on
+// One workgroup per (assignment v, part, 32-column tile of t), a wave per 256-wide slice of the contraction: see TqPreByAssign.  Plain fp32 FMAs on
 // the exact values of x (bf16) and A (fp16, or fp8 with FP8), the two halves of a 16-wide step in the two halves of a wave; the slices are
 // added in order through LDS.
 template <bool FP8>
 __device__ inline void pre_by_assign_block(const TqPreByAssign& P, const int32_t* __restrict__ idx, int T, int E, int k,
                                            int b, const TqRouteIn* route = nullptr)
 {
-    __shared__ float red[16][32];
-    __shared__ __attribute__((aligned(16))) uint2 xl[16][64];      // each wave's slice of the row
-    const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6;
-    const int ta = b % P.na_tiles;
-    const int v = b / P.na_tiles;
+    __shared__ float red[TQ_PRE_PART_SLICES][32];
+    __shared__ __attribute__((aligned(16))) uint2 xl[TQ_PRE_PART_SLICES][64];      // each wave's slice of the row
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int ta = b % P.na_tiles, part = b / P.na_tiles % P.n_parts;
+    const int v = b / (P.na_tiles * P.n_parts), slice = part * TQ_PRE_PART_SLICES + w;
     if (v >= P.a_tot) return;
     int e, t;
     if (v < T * k) {
@@ -723,13 +723,13 @@ __device__ inline void pre_by_assign_block(const TqPreByAssign& P, const int32_t
         const size_t f = (size_t)ta * ksteps + min(s0 + u, ksteps - 1);       // fragment; fp8 fragments: 8 bytes per lane, two lanes per word
         aq[u] = af[FP8 ? f * 32 + (lane >> 1) : f * 64 + lane];
     }
-    xl[slice][lane] = xv;
+    xl[w][lane] = xv;
     wave_fence();
     float acc = 0.f;
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
         if (s0 + u < ksteps) {
-            const uint4 xa = *reinterpret_cast<const uint4*>(&xl[slice][4 * u + 2 * hf]);
+            const uint4 xa = *reinterpret_cast<const uint4*>(&xl[w][4 * u + 2 * hf]);
             const uint32_t xw[4] = {xa.x, xa.y, xa.z, xa.w};
             const uint32_t aw[4] = {aq[u].x, aq[u].y, aq[u].z, aq[u].w};
             if (FP8) {
@@ -751,14 +751,15 @@ __device__ inline void pre_by_assign_block(const TqPreByAssign& P, const int32_t
         }
     }
     acc += __shfl_xor(acc, 32);
-    if (hf == 0) red[slice][col] = acc;
+    if (hf == 0) red[w][col] = acc;
     __syncthreads();
     const int c = 32 * ta + (int)threadIdx.x;
     if (threadIdx.x < 32 && c < P.na) {
-        float s = 0.f;
-        for (int i = 0; i < P.n_slices; ++i) s += red[i][threadIdx.x];
+        float s = red[0][threadIdx.x];
+#pragma unroll
+        for (int i = 1; i < TQ_PRE_PART_SLICES; ++i) s += red[i][threadIdx.x];
         if (FP8) s *= tq_sig_base(P.blob, P.expert_stride, P.sec, P.fm, 0, e)[c];
-        P.t[(size_t)v * P.na + c] = (uint16_t)tqdev::f2bf_bits(s);
+        P.t[((size_t)v * P.n_parts + part) * P.na + c] = s;
     }
 }
 
@@ -766,9 +767,9 @@ __device__ inline void pre_by_assign_block(const TqPreByAssign& P, const int32_t
 // PRE != 0 the other workgroups of the launch compute the gate/up low-rank intermediate by assignment (1: fp16
 // factors, 2: fp8 factors) or derive what the tiled kernels read beside the blob (3).
 // With ROUTE the launch also does the routing (route_small; idx and w are then unused).
-// (Workgroups of as many waves as the pre-pass has slices; the permutation's is one wave, the others end at once.)
+// (Workgroups of as many waves as a part of the pre-pass has slices; the permutation's is one wave, the others end at once.)
 template <int PRE, bool ROUTE>
-__global__ void __launch_bounds__(PRE == 1 || PRE == 2 ? 1024 : 64) permute_small_kernel(const int32_t* __restrict__ idx, const float* __restrict__ w,
+__global__ void __launch_bounds__(PRE == 1 || PRE == 2 ? 64 * TQ_PRE_PART_SLICES : 64) permute_small_kernel(const int32_t* __restrict__ idx, const float* __restrict__ w,
                                                            int n_assign, int E, int S, int T, int k,
                                                            int32_t* __restrict__ offsets, int32_t* __restrict__ slot_of,
                                                            int slot_stride, int32_t* __restrict__ src_of,
@@ -818,7 +819,7 @@ tq_status tqi_launch_permute(const int32_t* topk_idx, const float* topk_w, int32
 {
     const int64_t n_assign = (int64_t)T * k;
     const unsigned n_prep = prep ? prep->n_waves : 0;
-    const int64_t n_pre = pre ? (int64_t)pre->a_tot * pre->na_tiles : 0;
+    const int64_t n_pre = pre ? (int64_t)pre->a_tot * pre->n_parts * pre->na_tiles : 0;
     if (n_pre > 0x3FFFFFFF) return TQ_ERR_UNSUPPORTED;
     TqBlobHeader expect = {};
     int check = 0;
@@ -839,7 +840,7 @@ tq_status tqi_launch_permute(const int32_t* topk_idx, const float* topk_w, int32
         const TqRouteIn R = fused ? *route : TqRouteIn{};
         const TqPreByAssign P = n_pre > 0 ? *pre : TqPreByAssign{};
 #define TQ_PS(PREV, ROUTEV, P, NV)                                                                                        \
-        hipLaunchKernelGGL((permute_small_kernel<PREV, ROUTEV>), dim3(1 + (unsigned)(NV)), dim3(pre_kind ? 64 * pre->n_slices : 64), sm, stream, topk_idx,  \
+        hipLaunchKernelGGL((permute_small_kernel<PREV, ROUTEV>), dim3(1 + (unsigned)(NV)), dim3(pre_kind ? 64 * TQ_PRE_PART_SLICES : 64), sm, stream, topk_idx,  \
                            topk_w, (int)n_assign, E, S, T, k, offsets, slot_of, slot_stride, src_of, row_token, row_w,     \
                            tile_e, tile_row0, rt_max, ctrl, err_flag, (const TqBlobHeader*)blob, expect, check, zero_buf,  \
                            (int)zero_n, P, tilings, R, sm_words)

@@ -12,11 +12,11 @@
 //     two steps makes the 16-column fragments of a 32-deep step of them, so no MFMA row is padding.
 //   * The 8 partial results of a pair are summed across the waves through LDS in a fixed order (the
 //     "wavefront reduction"), then SwiGLU (stage 0) or the store of the split-K plane (stage 1).
-//   * The low-rank intermediate t = x A of a workgroup's range comes ready as bf16 from skinny_pre_kernel (for decode batches
+//   * The low-rank intermediate t = x A of a workgroup's range comes as up to four fp32 parts from skinny_pre_kernel (for decode batches
 //     proper that of gate/up per assignment from the permutation's launch); a split contraction needs no global reduction: the
 //     partial t of a split times B lands in that split's output plane, and the planes are summed by the combine.
 // Measured on 8 experts of 4096 x 14336, 16 tokens: gate/up 84.4 us for 514 MB, down 50.5 for 257 MB (with 32x32 MFMAs half of whose rows were padding,
-// the intermediate added up from fp32 slices in the set-up and group sums by MFMAs against ones: 91.9 and 56.9); whole call 163 -> 149 us.
+// the intermediate added up from fp32 slices in the set-up and group sums by MFMAs against ones: 91.9 and 56.9); whole call 163 -> 147 us.
 // The same call with codes of 3 bits and fp8 factors 162 -> 145 (there the MFMAs and their operands counted); 128 experts of 4096 x 1536: 112 -> 104.
 // Tried: two pairs in flight (spills at 512 indices a wave; at 256 the deal gets coarser: 44.6 -> 52.2 us on 60 experts of 2048 x 1408, 4
 // tokens); touching every workgroup's first pair in the launch before (down 2 us shorter, that launch 2 us longer).
@@ -34,12 +34,14 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int SK_NW = 8;        // waves per workgroup
 constexpr int SK_RED_BYTES = SK_NW * 7 * 2 * 64 * 4;   // per wave: 7 of its 8 row groups, 2 tiles, 64 lanes
 
-// Low-rank intermediate of one 16-row tile over the contraction range of one split, ready for the low-rank step:
-//   t[tile][split][m][c] = bf16(sigma_c * sum_{kk in range} x[row m][kk] * A[kk][c])
-// One workgroup per (tile, split, 32 columns of t); wave w takes the 256-wide slice w of the range, with all of its loads in flight
-// at once, and the slices are added in order through LDS.  (Left as fp32 slices for the kernel that reads them, they were 64 loads a lane of its
-// set-up.)
+// Low-rank intermediate of one 16-row tile over 1024 contraction indices (a part of the range of a split):
+//   t[tile][split][part][m][c] = sigma_c * sum_{kk in part} x[row m][kk] * A[kk][c]      (fp32)
+// One workgroup per (tile, split, part, 32 columns of t); each of its four waves takes a 256-wide slice, with all of its loads in flight
+// at once, and the slices are added in order through LDS.  (Left as 256-wide slices for the kernel that reads them, they were 64 loads a lane of its
+// set-up.  A whole range of 4096 in one workgroup is 340 KB through one CU, which takes 33 to 50 bytes a ns: 8 experts of 4096 x 14336, 16 tokens
+// 7.5 us that way, 5.3 in parts of 1024.)
 constexpr int SK_PRE_K = 256;
+constexpr int SK_PART_K = TQ_PRE_PART_SLICES * SK_PRE_K;
 
 // Exchanges 16-lane rows: a keeps its even rows and takes b's in its odd ones, b the other way round.  On the words of two 16-deep steps
 // (lane = column + 32 * k-half) a becomes the word of a 32-deep step's columns 0..15, b that of columns 16..31; the four rows of either hold
@@ -52,16 +54,19 @@ __device__ inline void swap_rows(uint32_t& a, uint32_t& b)
 }
 
 template <int STAGE, bool FP8>
-__global__ void __launch_bounds__(1024) skinny_pre_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob,
+__global__ void __launch_bounds__(64 * TQ_PRE_PART_SLICES) skinny_pre_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob,
                                                           const uint16_t* __restrict__ xin,
                                                           const int32_t* __restrict__ row_token,
                                                           const int32_t* __restrict__ tile_e,
                                                           const int32_t* __restrict__ tile_row0,
                                                           const int32_t* __restrict__ tile_rows,
-                                                          const int32_t* __restrict__ ctrl, uint16_t* __restrict__ t_out, int range_k)
+                                                          const int32_t* __restrict__ ctrl, float* __restrict__ t_out, int range_k,
+                                                          int n_parts)
 {
-    __shared__ float red[16][8][64];
-    const int tile = blockIdx.x, split = blockIdx.y, ta = blockIdx.z, lane = threadIdx.x & 63, slice = threadIdx.x >> 6;
+    constexpr int NW = TQ_PRE_PART_SLICES;
+    __shared__ float red[NW][8][64];
+    const int tile = blockIdx.x, split = blockIdx.y / n_parts, part = blockIdx.y % n_parts, ta = blockIdx.z, lane = threadIdx.x & 63,
+              slice = threadIdx.x >> 6;
     if (tile >= ctrl[4]) return;
     const int e = tile_e[tile], slot0 = tile_row0[tile], rows = tile_rows[tile];
     const int K = sec.K, ksteps = K / 16;
@@ -69,7 +74,7 @@ __global__ void __launch_bounds__(1024) skinny_pre_kernel(MGeom G, TqSection sec
     const uint16_t* xrow = (STAGE == 0 ? xin + (size_t)row_token[slot0 + r] * K : xin + (size_t)(slot0 + r) * K) + 16 * (lrow & 1) + 8 * (lrow >> 1);
     const u32x4* af = reinterpret_cast<const u32x4*>(tq_afrag_base(blob, G.expert_stride, sec, G.fm, STAGE, e)) + (FP8 ? lane >> 1 : lane);
     constexpr int NS = SK_PRE_K / 16;
-    const int s0 = split * (range_k / 16) + slice * NS;
+    const int s0 = split * (range_k / 16) + (part * NW + slice) * NS;
     const int n = min(NS, min(ksteps, (split + 1) * (range_k / 16)) - s0);      // (<= 0: past the end of the last split); even: ranges are whole chunks of 64
     Frag xa[NS / 2];
     u32x4 aq[NS];
@@ -95,14 +100,15 @@ __global__ void __launch_bounds__(1024) skinny_pre_kernel(MGeom G, TqSection sec
 #pragma unroll
     for (int v = 0; v < 8; ++v) red[slice][v][lane] = acc[v >> 2][v & 3];
     __syncthreads();
-    const int nsl = blockDim.x >> 6, NA = STAGE == 0 ? 2 * G.r16 : G.r16;
-    for (int i = threadIdx.x; i < 512; i += blockDim.x) {
+    const int NA = STAGE == 0 ? 2 * G.r16 : G.r16;
+    for (int i = threadIdx.x; i < 512; i += 64 * NW) {
         const int v = i >> 6, l = i & 63, c = 32 * ta + 16 * (v >> 2) + (l & 15), m = 4 * (l >> 4) + (v & 3);
         if (c >= NA) continue;
-        float t = 0.f;
-        for (int sl = 0; sl < nsl; ++sl) t += red[sl][v][l];
+        float t = red[0][v][l];
+#pragma unroll
+        for (int sl = 1; sl < NW; ++sl) t += red[sl][v][l];
         if (FP8) t *= tq_sig_base(blob, G.expert_stride, sec, G.fm, STAGE, e)[c];
-        t_out[(((size_t)tile * gridDim.y + split) * 16 + m) * NA + c] = (uint16_t)f2bf_bits(t);
+        t_out[(((size_t)tile * gridDim.y + blockIdx.y) * 16 + m) * NA + c] = t;
     }
 }
 
@@ -150,7 +156,7 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
                                                          const int32_t* __restrict__ tile_row0,
                                                          const int32_t* __restrict__ tile_rows,
                                                          const int32_t* __restrict__ ctrl,
-                                                         const uint16_t* __restrict__ t_in,
+                                                         const float* __restrict__ t_in, int n_parts,
                                                          void* __restrict__ out, int32_t* __restrict__ pair_cnt,
                                                          int units_per_split, int RB, int red_off, int xs_off, int mb_off,
                                                          const int32_t* __restrict__ row_src, int nsplit)
@@ -304,15 +310,20 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
     const bool two = total > 4 * 512;
     stage_load(0, xa0);
     if (two) stage_load(4 * 512, xa1);
-    // ---- low-rank intermediate: the A operand of the 16-deep step `wave`, rows of a step at lane rows 0 and 2 (the others meet zeros)
-    Frag tf;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) tf.u[j] = 0;
+    // ---- low-rank intermediate: the parts of the A operand of the 16-deep step `wave`, rows of a step at lane rows 0 and 2 (the others
+    //      meet zeros).  Only what exists, by the waves that have a step: requests in front of the weights are what the set-up waits for
+    f32x4 tp[TQ_PRE_MAX_PARTS][2];
     if (wave < n_lr) {
-        const uint16_t* tr;
-        if (STAGE == 0 && row_src) tr = t_in + (size_t)row_src[slot0 + min(l16, rows - 1)] * NA;      // stored per assignment
-        else tr = t_in + (((size_t)rt * nsplit + split) * 16 + l16) * NA;
-        if ((lrow & 1) == 0) tf.q = *reinterpret_cast<const u32x4*>(tr + 16 * wave + 4 * lrow);
+        const bool by_assign = STAGE == 0 && row_src;
+        const size_t row = by_assign ? (size_t)row_src[slot0 + min(l16, rows - 1)] * n_parts * NA : (((size_t)rt * nsplit + split) * n_parts * 16 + l16) * NA;
+        const float* tr = t_in + row + 16 * wave + 4 * (lrow & 2);
+#pragma unroll
+        for (int p = 0; p < TQ_PRE_MAX_PARTS; ++p)
+            if (p < n_parts) {
+                const f32x4* q = reinterpret_cast<const f32x4*>(tr + (size_t)p * (by_assign ? NA : 16 * NA));
+                tp[p][0] = q[0];
+                tp[p][1] = q[1];
+            }
     }
     WT wq[UPW][2][WN];
     uint32_t szq[UPW][NG][2];
@@ -330,6 +341,22 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
     }
     if (tid == 0) pq[0] = got_v;
     lds_barrier();
+    Frag tf;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) tf.u[j] = 0;
+    if (wave < n_lr) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            f32x4 t = tp[0][i];
+#pragma unroll
+            for (int p = 1; p < TQ_PRE_MAX_PARTS; ++p)
+                if (p < n_parts) t += tp[p][i];
+            if ((lrow & 1) == 0) {
+                tf.u[2 * i] = pack_bf2(t[0], t[1]);
+                tf.u[2 * i + 1] = pack_bf2(t[2], t[3]);
+            }
+        }
+    }
     const int xrow_off = min(l16, rows - 1) * RB + (PAIRED ? 64 * (lrow & 1) + 8 * (lrow >> 1) : 16 * (lrow & 1) + 8 * (lrow >> 1)) * 2 +
                          wave * WK * 2;
     auto lds_x = [&](int s) -> bf16x8 {       // A operand of step s of this wave (a constant at every call)
@@ -512,7 +539,7 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
 template <int STAGE, int GS, int CW, int WK>
 tq_status launch_skinny(const MGeom& G, const TqSection& sec, const uint8_t* blob, const uint16_t* xin,
                         const int32_t* row_token, const int32_t* tile_e, const int32_t* tile_row0,
-                        const int32_t* tile_rows, const int32_t* ctrl, const uint16_t* t_in,
+                        const int32_t* tile_rows, const int32_t* ctrl, const float* t_in, int n_parts,
                         void* out, int32_t* pair_cnt, int row_tiles, int nsplit, int units_per_split,
                         hipStream_t st, const int32_t* row_src)
 {
@@ -549,10 +576,10 @@ tq_status launch_skinny(const MGeom& G, const TqSection& sec, const uint8_t* blo
     // (dynamic-LDS limit of both instantiations: raised once per device by tqi_setup_skinny)
     if (!deal)
         hipLaunchKernelGGL((moe_skinny_kernel<STAGE, GS, CW, false, WK>), grid, dim3(512), smem, st, G, sec, blob, xin, row_token, tile_e,
-                           tile_row0, tile_rows, ctrl, t_in, out, pair_cnt, units_per_split, RB, red_off, xs_off, mb_off, row_src, nsplit);
+                           tile_row0, tile_rows, ctrl, t_in, n_parts, out, pair_cnt, units_per_split, RB, red_off, xs_off, mb_off, row_src, nsplit);
     else
         hipLaunchKernelGGL((moe_skinny_kernel<STAGE, GS, CW, true, WK>), grid, dim3(512), smem, st, G, sec, blob, xin, row_token, tile_e,
-                           tile_row0, tile_rows, ctrl, t_in, out, pair_cnt, units_per_split, RB, red_off, xs_off, mb_off, row_src, nsplit);
+                           tile_row0, tile_rows, ctrl, t_in, n_parts, out, pair_cnt, units_per_split, RB, red_off, xs_off, mb_off, row_src, nsplit);
     TQ_CHECK_LAUNCH();
     return TQ_OK;
 }
@@ -560,7 +587,7 @@ tq_status launch_skinny(const MGeom& G, const TqSection& sec, const uint8_t* blo
 template <int STAGE>
 tq_status launch_skinny_gs(int gs, int cw, const MGeom& G, const TqSection& sec, const uint8_t* blob, const uint16_t* xin,
                            const int32_t* row_token, const int32_t* tile_e, const int32_t* tile_row0,
-                           const int32_t* tile_rows, const int32_t* ctrl, const uint16_t* t_in,
+                           const int32_t* tile_rows, const int32_t* ctrl, const float* t_in, int n_parts,
                            void* out, int32_t* pair_cnt, int row_tiles, int nsplit, int units_per_split,
                            hipStream_t st, const int32_t* row_src, int wave_k)
 {
@@ -568,10 +595,10 @@ tq_status launch_skinny_gs(int gs, int cw, const MGeom& G, const TqSection& sec,
     do {                                                                                                                  \
         if (wave_k == 256 && GSV * 16 <= 256)                                                                             \
             return launch_skinny<STAGE, GSV, CWV, (GSV * 16 <= 256 ? 256 : 512)>(                                         \
-                G, sec, blob, xin, row_token, tile_e, tile_row0, tile_rows, ctrl, t_in, out, pair_cnt, row_tiles, nsplit, \
+                G, sec, blob, xin, row_token, tile_e, tile_row0, tile_rows, ctrl, t_in, n_parts, out, pair_cnt, row_tiles, nsplit, \
                 units_per_split, st, row_src);                                                                            \
         return launch_skinny<STAGE, GSV, CWV, 512>(G, sec, blob, xin, row_token, tile_e, tile_row0, tile_rows, ctrl, t_in, \
-                                                   out, pair_cnt, row_tiles, nsplit, units_per_split, st, row_src);       \
+                                                   n_parts, out, pair_cnt, row_tiles, nsplit, units_per_split, st, row_src);       \
     } while (0)
     if (cw == 4) {
         switch (gs) {
@@ -664,18 +691,18 @@ tq_status tqi_forward_skinny(const TqLayout& L, const TqWorkspace& W, const uint
     const int32_t* tile_rows = tile_row0 + (size_t)TQ_N_TILINGS * W.rt_max;      // row counts of the same tiling
     uint16_t* h = reinterpret_cast<uint16_t*>(ws + W.h);
     float* yd = reinterpret_cast<float*>(ws + W.yd);
-    uint16_t* t_bf = reinterpret_cast<uint16_t*>(ws + W.tpart);
+    float* tpart = reinterpret_cast<float*>(ws + W.tpart);
     const int gs = L.g / 16;
     const int rt16 = W.a_tot / 16 + L.E + L.S;
 
     int ns, ups;
     plan_split(L.H, L.g, &ns, &ups);
     const int unit_k = L.g < 64 ? 64 : L.g;
-    // the pre-pass of one stage: a wave per 256-wide slice of a split's range (at most 4096)
+    // parts of the intermediate in a split's range
+    auto parts = [&](const TqSection& sec) { return (std::min(ups * unit_k, sec.K) + SK_PART_K - 1) / SK_PART_K; };
     auto pre = [&](auto kernel, const TqSection& sec, const uint16_t* xin) {
-        const int range_k = std::min(ups * unit_k, sec.K), nsl = (range_k + SK_PRE_K - 1) / SK_PRE_K;
-        hipLaunchKernelGGL(kernel, dim3(rt16, ns, sec.na_tiles), dim3(64 * nsl), 0, stream, G, sec, blob, xin, row_token, tile_e, tile_row0,
-                           tile_rows, ctrl, t_bf, range_k);
+        hipLaunchKernelGGL(kernel, dim3(rt16, ns * parts(sec), sec.na_tiles), dim3(64 * TQ_PRE_PART_SLICES), 0, stream, G, sec, blob, xin,
+                           row_token, tile_e, tile_row0, tile_rows, ctrl, tpart, ups * unit_k, parts(sec));
     };
     // decode batches proper: that of gate/up was computed per assignment in the permutation's launch
     const bool by_assign = tqi_pre_by_assign(L, W);
@@ -688,7 +715,7 @@ tq_status tqi_forward_skinny(const TqLayout& L, const TqWorkspace& W, const uint
     tqi_record_stage(2, stream);
     int32_t* pair_cnt = reinterpret_cast<int32_t*>(ws + W.sk_cnt);
     if (W.sk_cnt_n < 2 * W.rt_max * TQ_MAX_SPLIT) return TQ_ERR_UNSUPPORTED;
-    tq_status rc = launch_skinny_gs<0>(gs, L.cw, G, L.gu, blob, x, row_token, tile_e, tile_row0, tile_rows, ctrl, t_bf, h, pair_cnt, rt16, 1,
+    tq_status rc = launch_skinny_gs<0>(gs, L.cw, G, L.gu, blob, x, row_token, tile_e, tile_row0, tile_rows, ctrl, tpart, parts(L.gu), h, pair_cnt, rt16, 1,
                                        ups, stream, row_src, wave_k_of(L.H, L.g));
     if (rc != TQ_OK) return rc;
     tqi_record_stage(3, stream);
@@ -699,7 +726,7 @@ tq_status tqi_forward_skinny(const TqLayout& L, const TqWorkspace& W, const uint
         TQ_CHECK_LAUNCH();
     }
     tqi_record_stage(4, stream);
-    rc = launch_skinny_gs<1>(gs, L.cw, G, L.d, blob, h, row_token, tile_e, tile_row0, tile_rows, ctrl, t_bf, yd,
+    rc = launch_skinny_gs<1>(gs, L.cw, G, L.d, blob, h, row_token, tile_e, tile_row0, tile_rows, ctrl, tpart, parts(L.d), yd,
                              pair_cnt + (size_t)W.rt_max * TQ_MAX_SPLIT, rt16, ns, ups, stream, nullptr, wave_k_of(L.F, L.g));
     if (rc != TQ_OK) return rc;
     *nsplit_out = ns;
