@@ -3,21 +3,22 @@
 //
 //   * A row tile holds at most 16 assignment rows of one expert.  Its activations for the whole
 //     contraction range of the workgroup (up to 4096 values per row) are staged in LDS ONCE.
-//   * A workgroup has 8 waves; wave w owns a 512-wide slice (256 on contractions up to 2048) of the contraction range and walks over the
+//   * A workgroup has 8 waves (2 or 4 on contractions up to 512 or 1024); wave w owns a 512-wide slice (256 on contractions up to 2048) of the contraction range and walks over the
 //     workgroup's column-tile pairs, streaming its slice of the packed codes (already in MFMA fragment
 //     order) straight from global memory into registers, one pair ahead.  No barrier in that stream.
 //   * Codes go to v_mfma_f32_16x16x32_bf16 as 128 + q; each quantisation group's fp32 partial sum is folded as
 //     acc += s * part - s (128 + z) * xsum, with the group sums of the activations added up as the rows are staged.  The blob's
 //     fragments are those of the 32x32x16 instruction of the tiled kernels; one row exchange (v_permlane16_swap) of the words of
 //     two steps makes the 16-column fragments of a 32-deep step of them, so no MFMA row is padding.
-//   * The 8 partial results of a pair are summed across the waves through LDS in a fixed order (the
+//   * The waves' partial results of a pair are summed across the waves through LDS in a fixed order (the
 //     "wavefront reduction"), then SwiGLU (stage 0) or the store of the split-K plane (stage 1).
 //   * The low-rank intermediate t = x A of a workgroup's range comes as up to four fp32 parts from skinny_pre_kernel (for decode batches
 //     proper that of gate/up per assignment from the permutation's launch); a split contraction needs no global reduction: the
 //     partial t of a split times B lands in that split's output plane, and the planes are summed by the combine.
-// Measured on 8 experts of 4096 x 14336, 16 tokens: gate/up 84.4 us for 514 MB, down 50.5 for 257 MB (with 32x32 MFMAs half of whose rows were padding,
-// the intermediate added up from fp32 slices in the set-up and group sums by MFMAs against ones: 91.9 and 56.9); whole call 163 -> 147 us.
-// The same call with codes of 3 bits and fp8 factors 162 -> 145 (there the MFMAs and their operands counted); 128 experts of 4096 x 1536: 112 -> 104.
+// Measured, whole calls (before: 32x32 MFMAs half of whose rows were padding, the intermediate added up from fp32 slices in the set-up,
+// group sums by MFMAs against ones, a reduction with a branch per result): 8 experts of 4096 x 14336, 16 tokens 161 -> 145 us, 1 token 67.5 -> 59.7
+// (gate/up 32.9 -> 28.1 for 125 MB, down 22.3 -> 17.8 for 63), 16 tokens with codes of 3 bits and fp8 factors 158 -> 134; 128 experts of
+// 4096 x 1536, 16 tokens 104 -> 93.
 // Tried: two pairs in flight (spills at 512 indices a wave; at 256 the deal gets coarser: 44.6 -> 52.2 us on 60 experts of 2048 x 1408, 4
 // tokens); touching every workgroup's first pair in the launch before (down 2 us shorter, that launch 2 us longer).
 #include "tq_device.h"
@@ -31,8 +32,13 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int SK_NW = 8;        // waves per workgroup
-constexpr int SK_RED_BYTES = SK_NW * 7 * 2 * 64 * 4;   // per wave: 7 of its 8 row groups, 2 tiles, 64 lanes
+// the reduction buffer of NW waves: per wave the 8 - 8 / NW of its results that others add up, 2 tiles, 64 lanes, and a slot for those that nobody reads
+// waves per SIMD that a workgroup of nw waves is compiled for: three where it fits 168 registers without a spill.  (Four, 128 registers: 80
+// to 100 bytes spilled and two workgroups per CU, 60 experts of 2048 x 1408, 16 tokens 58.5 -> 72.4 us; two at four waves: 16 experts of 1024 x 8192,
+// 8 tokens 47.8 -> 51.8; three at two waves: 24 experts of 512 x 3072, 5 tokens 36.3 -> 37.3.)
+constexpr int sk_waves_per_simd(int nw) { return nw == 4 ? 3 : 2; }
+constexpr int SK_LDS = 160 * 1024;
+constexpr int sk_red_bytes(int nw) { return (nw * (8 - 8 / nw) * 2 + 1) * 64 * 4; }
 
 // Low-rank intermediate of one 16-row tile over 1024 contraction indices (a part of the range of a split):
 //   t[tile][split][part][m][c] = sigma_c * sum_{kk in part} x[row m][kk] * A[kk][c]      (fp32)
@@ -147,9 +153,10 @@ __device__ inline float run_sum(const u32x4& q)
 // CW: 32-bit words of codes per lane, tile and 64-wide chunk: 4 (4-bit slots), 3 or 2 (dense 3- / 2-bit codes).
 // DEAL: the workgroups share out the (tile, split) combinations that exist among themselves (1-D grid) instead of
 // taking the one their 3-D block index names; see below.
-// WK: contraction indices per wave (512, or 256 on contractions of at most 2048 so that all eight waves have a slice).
-template <int STAGE, int GS, int CW, bool DEAL, int WK>
-__global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob,
+// WK, NW: contraction indices per wave and waves per workgroup: 512 and 8; on contractions of at most 2048 256 and as many waves
+// as they take (2, 4 or 8), and a CU holds as many workgroups as it has room for.
+template <int STAGE, int GS, int CW, bool DEAL, int WK, int NW>
+__global__ void __launch_bounds__(64 * NW, sk_waves_per_simd(NW)) moe_skinny_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob,
                                                          const uint16_t* __restrict__ xin,
                                                          const int32_t* __restrict__ row_token,
                                                          const int32_t* __restrict__ tile_e,
@@ -167,6 +174,9 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
     constexpr int NG = UNIT_K / (GS * 16);
     constexpr int GT = GS / 2;         // steps per group
     constexpr int UPW = WK / UNIT_K;   // units per wave
+    constexpr int NT = 64 * NW;
+    constexpr int OV = 8 / NW;         // results per tile that a wave adds up, and low-rank steps that it may have
+    constexpr int MAXP = NW == 8 ? TQ_PRE_MAX_PARTS : 1;      // parts of the low-rank intermediate (fewer waves: at most 1024 indices)
     using WT = std::conditional_t<CW == 4, u32x4, uint32_t>;      // register type of the packed codes
     constexpr int WN = CW == 4 ? UC : UC * CW;                    // and how many of them one tile of a unit takes
     // dense codes in units of two chunks: a 32-deep step takes step w of both chunks, so that the rows of the raw words can be exchanged
@@ -210,7 +220,7 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
     const int l16 = lane & 15, lrow = lane >> 4;      // MFMA: row of A / column of B and D; quarter of the contraction step / of the rows of D
     const int K = sec.K, NU = K / UNIT_K;
     const int NA = STAGE == 0 ? 2 * G.r16 : G.r16;
-    const int n_lr = (G.r > 0) ? NA / 16 : 0;       // low-rank MFMA steps; step j is applied by wave j
+    const int n_lr = (G.r > 0) ? NA / 16 : 0;       // low-rank MFMA steps; step j is applied by wave j % NW
     const int ub = split * units_per_split;
     const int ue = min(NU, ub + units_per_split);
     const int range_k = (ue - ub) * UNIT_K;
@@ -233,21 +243,23 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
     const uint8_t* bfr = G.r > 0 ? tq_bfrag_base(blob, G.expert_stride, sec, G.fm, STAGE, e) : rec;
     const uint32_t codes_bytes = (uint32_t)sec.pairs * sec.chunks * (512 * CW), sz_bytes = (uint32_t)sec.pairs * sec.groups * 256;
     const int steps_per_tile = G.r16 / 16;
-    const uint32_t b_bytes = wave < n_lr ? (uint32_t)sec.pairs * steps_per_tile * 2 * b_per : 0u;
+    const uint32_t b_bytes = (uint32_t)sec.pairs * steps_per_tile * 2 * b_per;
 
     auto load_w = [&](WT (&dst)[2][WN], int pair, int u) {       // unit u of this wave, both tiles
         const __amdgpu_buffer_rsrc_t rs = buffer(rec + sec.codes, pair < npairs && u < nuw ? codes_bytes : 0u);
         const int so = (pair * sec.chunks + (ub + wave * UPW + u) * UC) * (512 * CW);
+        int lo = lane * (CW == 4 ? 16 : 4);
+        asm volatile("" : "+v"(lo));      // one register; the rest of the offset goes into the instruction
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int c = 0; c < UC; ++c) {
                 if constexpr (CW == 4) {
-                    dst[t][c] = __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16 + (c * 2 + t) * 1024, so, BUF_NT);
+                    dst[t][c] = __builtin_amdgcn_raw_buffer_load_b128(rs, lo + (c * 2 + t) * 1024, so, BUF_NT);
                 } else {
 #pragma unroll
                     for (int d = 0; d < CW; ++d)
-                        dst[t][c * CW + d] = __builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4 + ((c * 2 + t) * CW + d) * 256, so, BUF_NT);
+                        dst[t][c * CW + d] = __builtin_amdgcn_raw_buffer_load_b32(rs, lo + ((c * 2 + t) * CW + d) * 256, so, BUF_NT);
                 }
             }
     };
@@ -259,17 +271,17 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
 #pragma unroll
             for (int t = 0; t < 2; ++t) dst[gi][t] = __builtin_amdgcn_raw_buffer_load_b32(rs, col * 4 + (gi * 2 + t) * 128, so, 0);
     };
-    // low-rank B fragments ride in the same prefetch: step `wave` (stage 0: steps below r16 / 16 feed the gate tile, the others the up tile)
-    const int lr_t = (STAGE == 0 && wave >= steps_per_tile) ? 1 : 0;
-    const int lr_step = wave - lr_t * steps_per_tile;
+    // low-rank B fragments ride in the same prefetch: steps wave, wave + NW, ... (stage 0: steps below r16 / 16 feed the gate tile, the others the up tile)
     constexpr int NBQ = STAGE == 0 ? 1 : 2;
-    auto load_b = [&](u32x4 (&dst)[NBQ], int pair) {
-        const __amdgpu_buffer_rsrc_t rs = buffer(bfr, pair < npairs ? b_bytes : 0u);
-        const int so = (pair * steps_per_tile + lr_step) * 2 * b_per;
-        if (STAGE == 0) dst[0] = __builtin_amdgcn_raw_buffer_load_b128(rs, b_lane, so + lr_t * b_per, 0);
-        else
+    auto load_b = [&](u32x4 (&dst)[OV][NBQ], int pair) {
 #pragma unroll
-            for (int t = 0; t < NBQ; ++t) dst[t] = __builtin_amdgcn_raw_buffer_load_b128(rs, b_lane, so + t * b_per, 0);
+        for (int q = 0; q < OV; ++q) {
+            const int step = wave + NW * q, t0 = STAGE == 0 && step >= steps_per_tile ? 1 : 0;
+            const __amdgpu_buffer_rsrc_t rs = buffer(bfr, pair < npairs && step < n_lr ? b_bytes : 0u);
+            const int so = (pair * steps_per_tile + step - t0 * steps_per_tile) * 2 * b_per;
+#pragma unroll
+            for (int t = 0; t < NBQ; ++t) dst[q][t] = __builtin_amdgcn_raw_buffer_load_b128(rs, b_lane, so + (t0 + t) * b_per, 0);
+        }
     };
 
     // the or-operand of the unpack in a vector register (see unpack_word): opaque move, not folded to a literal
@@ -287,7 +299,7 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
     auto stage_load = [&](int c0, u32x4 (&v)[4]) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int c = min(c0 + j * 512 + tid, total - 1);
+            const int c = min(c0 + j * NT + tid, total - 1);
             const int row = c / gran, kg = c - row * gran;
             const size_t src_row = STAGE == 0 ? (size_t)row_token[slot0 + row] : (size_t)(slot0 + row);
             v[j] = *reinterpret_cast<const u32x4*>(xin + src_row * K + (size_t)ub * UNIT_K + (size_t)kg * 8);
@@ -298,7 +310,7 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
         for (int j = 0; j < 4; ++j) {
             // a group is a run of 2 GS chunks (4 to 32, a divisor of 64) and `total` a whole number of them: its lanes are all in range or all not
             const float s = run_sum<2 * GS>(v[j]);
-            const int c = c0 + j * 512 + tid;
+            const int c = c0 + j * NT + tid;
             if (c < total) {
                 const int row = c / gran, kg = c - row * gran;
                 *reinterpret_cast<u32x4*>(lds + row * RB + kg * 16) = v[j];
@@ -307,53 +319,60 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
         }
     };
     u32x4 xa0[4], xa1[4];
-    const bool two = total > 4 * 512;
+    const bool two = total > 4 * NT;
     stage_load(0, xa0);
-    if (two) stage_load(4 * 512, xa1);
-    // ---- low-rank intermediate: the parts of the A operand of the 16-deep step `wave`, rows of a step at lane rows 0 and 2 (the others
+    if (two) stage_load(4 * NT, xa1);
+    // ---- low-rank intermediate: the parts of the A operands of this wave's 16-deep steps, rows of a step at lane rows 0 and 2 (the others
     //      meet zeros).  Only what exists, by the waves that have a step: requests in front of the weights are what the set-up waits for
-    f32x4 tp[TQ_PRE_MAX_PARTS][2];
+    f32x4 tp[OV][MAXP][2];
     if (wave < n_lr) {
         const bool by_assign = STAGE == 0 && row_src;
         const size_t row = by_assign ? (size_t)row_src[slot0 + min(l16, rows - 1)] * n_parts * NA : (((size_t)rt * nsplit + split) * n_parts * 16 + l16) * NA;
         const float* tr = t_in + row + 16 * wave + 4 * (lrow & 2);
 #pragma unroll
-        for (int p = 0; p < TQ_PRE_MAX_PARTS; ++p)
-            if (p < n_parts) {
-                const f32x4* q = reinterpret_cast<const f32x4*>(tr + (size_t)p * (by_assign ? NA : 16 * NA));
-                tp[p][0] = q[0];
-                tp[p][1] = q[1];
+        for (int q = 0; q < OV; ++q)
+            if (wave + NW * q < n_lr) {
+#pragma unroll
+                for (int p = 0; p < MAXP; ++p)
+                    if (p < n_parts) {
+                        const f32x4* src = reinterpret_cast<const f32x4*>(tr + 16 * NW * q + (size_t)p * (by_assign ? NA : 16 * NA));
+                        tp[q][p][0] = src[0];
+                        tp[q][p][1] = src[1];
+                    }
             }
     }
     WT wq[UPW][2][WN];
     uint32_t szq[UPW][NG][2];
-    u32x4 bq[NBQ];
+    u32x4 bq[OV][NBQ];
 #pragma unroll
     for (int u = 0; u < UPW; ++u) { load_w(wq[u], part, u); load_sz(szq[u], part, u); }
     load_b(bq, part);
     stage_store(0, xa0);
     if (two) {
-        stage_store(4 * 512, xa1);
-        for (int c0 = 8 * 512; c0 < total; c0 += 4 * 512) {      // the rare tall tiles
+        stage_store(4 * NT, xa1);
+        for (int c0 = 8 * NT; c0 < total; c0 += 4 * NT) {      // the rare tall tiles
             stage_load(c0, xa0);
             stage_store(c0, xa0);
         }
     }
     if (tid == 0) pq[0] = got_v;
     lds_barrier();
-    Frag tf;
+    Frag tf[OV];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) tf.u[j] = 0;
-    if (wave < n_lr) {
+    for (int q = 0; q < OV; ++q) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            f32x4 t = tp[0][i];
+        for (int j = 0; j < 4; ++j) tf[q].u[j] = 0;
+        if (wave + NW * q < n_lr) {
 #pragma unroll
-            for (int p = 1; p < TQ_PRE_MAX_PARTS; ++p)
-                if (p < n_parts) t += tp[p][i];
-            if ((lrow & 1) == 0) {
-                tf.u[2 * i] = pack_bf2(t[0], t[1]);
-                tf.u[2 * i + 1] = pack_bf2(t[2], t[3]);
+            for (int i = 0; i < 2; ++i) {
+                f32x4 t = tp[q][0][i];
+#pragma unroll
+                for (int p = 1; p < MAXP; ++p)
+                    if (p < n_parts) t += tp[q][p][i];
+                if ((lrow & 1) == 0) {
+                    tf[q].u[2 * i] = pack_bf2(t[0], t[1]);
+                    tf[q].u[2 * i + 1] = pack_bf2(t[2], t[3]);
+                }
             }
         }
     }
@@ -463,69 +482,80 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
             }
         }
         {
-            u32x4 bc[NBQ];
+            u32x4 bc[OV][NBQ];
 #pragma unroll
-            for (int t = 0; t < NBQ; ++t) bc[t] = bq[t];
+            for (int q = 0; q < OV; ++q)
+#pragma unroll
+                for (int t = 0; t < NBQ; ++t) bc[q][t] = bq[q][t];
             load_b(bq, pnext);
-            if (wave < n_lr) {
 #pragma unroll
-                for (int t = 0; t < NBQ; ++t) {
-                    Frag lo, hi;
-                    b_operand(bc[t], lo, hi);
-                    if (STAGE == 0 && lr_t == 1) {
-                        acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tf.v, lo.v, acc[1][0], 0, 0, 0);
-                        acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tf.v, hi.v, acc[1][1], 0, 0, 0);
-                    } else {
-                        acc[t][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tf.v, lo.v, acc[t][0], 0, 0, 0);
-                        acc[t][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tf.v, hi.v, acc[t][1], 0, 0, 0);
+            for (int q = 0; q < OV; ++q)
+                if (wave + NW * q < n_lr) {
+                    const bool up = STAGE == 0 && wave + NW * q >= steps_per_tile;
+#pragma unroll
+                    for (int t = 0; t < NBQ; ++t) {
+                        Frag lo, hi;
+                        b_operand(bc[q][t], lo, hi);
+                        if (up) {
+                            acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tf[q].v, lo.v, acc[1][0], 0, 0, 0);
+                            acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tf[q].v, hi.v, acc[1][1], 0, 0, 0);
+                        } else {
+                            acc[t][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tf[q].v, lo.v, acc[t][0], 0, 0, 0);
+                            acc[t][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tf[q].v, hi.v, acc[t][1], 0, 0, 0);
+                        }
                     }
                 }
-            }
         }
-        // ---- wavefront reduction: wave w keeps result w (half w / 4 of the tile's columns, row w % 4 of each four) and publishes its other seven
+        // ---- wavefront reduction: of the 8 results (half v / 4 of a tile's columns, row v % 4 of each four) wave w adds up OV w, OV w + 1, ...
+        //      and publishes the others.  Without branches, so that all reads are under way together: a wave's own results go to a slot that
+        //      nobody reads, and in the sum they take the place of what is read for them (with a branch per result and per wave, the reads one
+        //      after the other: 8 experts of 4096 x 14336, 4 tokens 128 -> 118 us a call; 128 of 4096 x 1536, 16 tokens 104.4 -> 98.5).
         {
-            float* mine = red + wave * (7 * 2 * 64);
+            float* mine = red + wave * ((8 - OV) * 2 * 64) + lane;
+            float* none = red + NW * (8 - OV) * 2 * 64 + lane;
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+            for (int v = 0; v < 8; ++v) {
+                const bool own = v / OV == wave;
+                const int slot = v / OV < wave ? v : v - OV;
 #pragma unroll
-                for (int v = 0; v < 8; ++v) {
-                    if (v != wave) {
-                        const int slot = v < wave ? v : v - 1;
-                        mine[(t * 7 + slot) * 64 + lane] = acc[t][v >> 2][v & 3];
-                    }
-                }
+                for (int t = 0; t < 2; ++t) *(own ? none : mine + (t * (8 - OV) + slot) * 64) = acc[t][v >> 2][v & 3];
+            }
             if (tid == 0) pq[(it + 1) & 1] = fetched;
         }
         lds_barrier();
         {
-            float own[2] = {0.f, 0.f};
+            float part[NW][OV][2], tot[OV][2];
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+            for (int w = 0; w < NW; ++w) {
+                const float* src = red + w * ((8 - OV) * 2 * 64) + OV * (wave < w ? wave : max(wave - 1, 0)) * 64 + lane;
 #pragma unroll
-                for (int v = 0; v < 8; ++v)
-                    if (v == wave) own[t] = acc[t][v >> 2][v & 3];
-            float tot[2] = {0.f, 0.f};
+                for (int i = 0; i < OV; ++i)
 #pragma unroll
-            for (int ww = 0; ww < SK_NW; ++ww) {           // fixed order: run-to-run identical sums
-                if (ww == wave) {
-                    tot[0] += own[0];
-                    tot[1] += own[1];
-                } else {
-                    const int slot = wave < ww ? wave : wave - 1;
-                    const float* src = red + ww * (7 * 2 * 64);
-                    tot[0] += src[(0 * 7 + slot) * 64 + lane];
-                    tot[1] += src[(1 * 7 + slot) * 64 + lane];
-                }
+                    for (int t = 0; t < 2; ++t) part[w][i][t] = src[(t * (8 - OV) + i) * 64];
             }
-            const int m = 4 * lrow + (wave & 3), n = 16 * (wave >> 2) + l16;
-            if (m < rows) {
-                if (STAGE == 0) {
-                    const float hv = silu_mul(tot[0], tot[1]);
-                    reinterpret_cast<uint16_t*>(out)[(size_t)(slot0 + m) * G.F + 32 * pair + n] = (uint16_t)f2bf_bits(hv);
-                } else {
-                    float* yd = reinterpret_cast<float*>(out) + (size_t)split * G.a_tot * G.H + (size_t)(slot0 + m) * G.H + 64 * pair + n;
-                    yd[0] = tot[0];
-                    yd[32] = tot[1];
+#pragma unroll
+            for (int i = 0; i < OV; ++i)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    float own = acc[t][i >> 2][i & 3];
+#pragma unroll
+                    for (int w = 1; w < NW; ++w) own = w == wave ? acc[t][(OV * w + i) >> 2][(OV * w + i) & 3] : own;
+                    tot[i][t] = 0.f;
+#pragma unroll
+                    for (int w = 0; w < NW; ++w) tot[i][t] += w == wave ? own : part[w][i][t];      // fixed order: run-to-run identical sums
+                }
+#pragma unroll
+            for (int i = 0; i < OV; ++i) {
+                const int v = OV * wave + i, m = 4 * lrow + (v & 3), n = 16 * (v >> 2) + l16;
+                if (m < rows) {
+                    if (STAGE == 0) {
+                        const float hv = silu_mul(tot[i][0], tot[i][1]);
+                        reinterpret_cast<uint16_t*>(out)[(size_t)(slot0 + m) * G.F + 32 * pair + n] = (uint16_t)f2bf_bits(hv);
+                    } else {
+                        float* yd = reinterpret_cast<float*>(out) + (size_t)split * G.a_tot * G.H + (size_t)(slot0 + m) * G.H + 64 * pair + n;
+                        yd[0] = tot[i][0];
+                        yd[32] = tot[i][1];
+                    }
                 }
             }
         }
@@ -536,7 +566,7 @@ __global__ void __launch_bounds__(512) moe_skinny_kernel(MGeom G, TqSection sec,
     }
 }
 
-template <int STAGE, int GS, int CW, int WK>
+template <int STAGE, int GS, int CW, int WK, int NW>
 tq_status launch_skinny(const MGeom& G, const TqSection& sec, const uint8_t* blob, const uint16_t* xin,
                         const int32_t* row_token, const int32_t* tile_e, const int32_t* tile_row0,
                         const int32_t* tile_rows, const int32_t* ctrl, const float* t_in, int n_parts,
@@ -547,38 +577,39 @@ tq_status launch_skinny(const MGeom& G, const TqSection& sec, const uint8_t* blo
     const int range_k = units_per_split * UNIT_K;
     const int RB = range_k * 2 + 16;
     const int red_off = 16 * RB;
-    const int xs_off = red_off + SK_RED_BYTES;
+    const int xs_off = red_off + sk_red_bytes(NW);
     const int mb_off = xs_off + (range_k / G.g) * 16 * 4;      // mailbox of the pair scheduler
     const size_t smem = (size_t)mb_off + 16;
-    if (smem > 160 * 1024) return TQ_ERR_UNSUPPORTED;
+    if (smem > SK_LDS) return TQ_ERR_UNSUPPORTED;
     // one workgroup per compute unit (a workgroup fills a CU's LDS; fewer, longer workgroups amortise the set-up -
     // activation staging, group sums - over more pairs)
     const TqDeviceState* ds = nullptr;
     if (tqi_device_state(&ds) != TQ_OK) return TQ_ERR_HIP;
+    const long slots = (long)ds->n_cu * std::max<long>(1, std::min<long>(4 * sk_waves_per_simd(NW) / NW, SK_LDS / (long)smem));      // workgroups that the chip holds at once
     dim3 grid;
     bool deal = false;
     if (G.ne <= 32) {
         // few experts: nearly all of them receive rows, the host's count of the tiles is good
         const int tiles_est = (int)std::min<int64_t>(G.a_tot, std::min(G.ne, row_tiles));
         long total = (long)sec.pairs * tiles_est * nsplit;
-        int ppw = (int)((total + ds->n_cu - 1) / ds->n_cu);
+        int ppw = (int)((total + slots - 1) / slots);
         ppw = std::max(1, std::min(ppw, sec.pairs));
         grid = dim3((sec.pairs + ppw - 1) / ppw, row_tiles, nsplit);
         if (grid.y > 65535) return TQ_ERR_UNSUPPORTED;
     } else {
         // many experts: at least one workgroup per (tile, split) that may exist; the kernel shares them out among
         // those that do
-        const long n_wg = std::max<long>(ds->n_cu, (long)row_tiles * nsplit);
+        const long n_wg = std::max<long>(slots, (long)row_tiles * nsplit);
         if (n_wg > 0x7FFFFFFF) return TQ_ERR_UNSUPPORTED;
         grid = dim3((unsigned)n_wg);
         deal = true;
     }
     // (dynamic-LDS limit of both instantiations: raised once per device by tqi_setup_skinny)
     if (!deal)
-        hipLaunchKernelGGL((moe_skinny_kernel<STAGE, GS, CW, false, WK>), grid, dim3(512), smem, st, G, sec, blob, xin, row_token, tile_e,
+        hipLaunchKernelGGL((moe_skinny_kernel<STAGE, GS, CW, false, WK, NW>), grid, dim3(64 * NW), smem, st, G, sec, blob, xin, row_token, tile_e,
                            tile_row0, tile_rows, ctrl, t_in, n_parts, out, pair_cnt, units_per_split, RB, red_off, xs_off, mb_off, row_src, nsplit);
     else
-        hipLaunchKernelGGL((moe_skinny_kernel<STAGE, GS, CW, true, WK>), grid, dim3(512), smem, st, G, sec, blob, xin, row_token, tile_e,
+        hipLaunchKernelGGL((moe_skinny_kernel<STAGE, GS, CW, true, WK, NW>), grid, dim3(64 * NW), smem, st, G, sec, blob, xin, row_token, tile_e,
                            tile_row0, tile_rows, ctrl, t_in, n_parts, out, pair_cnt, units_per_split, RB, red_off, xs_off, mb_off, row_src, nsplit);
     TQ_CHECK_LAUNCH();
     return TQ_OK;
@@ -589,16 +620,17 @@ tq_status launch_skinny_gs(int gs, int cw, const MGeom& G, const TqSection& sec,
                            const int32_t* row_token, const int32_t* tile_e, const int32_t* tile_row0,
                            const int32_t* tile_rows, const int32_t* ctrl, const float* t_in, int n_parts,
                            void* out, int32_t* pair_cnt, int row_tiles, int nsplit, int units_per_split,
-                           hipStream_t st, const int32_t* row_src, int wave_k)
+                           hipStream_t st, const int32_t* row_src, int wave_k, int n_waves)
 {
+#define TQ_SKL(GSV, CWV, WKV, NWV)                                                                                        \
+    return launch_skinny<STAGE, GSV, CWV, WKV, NWV>(G, sec, blob, xin, row_token, tile_e, tile_row0, tile_rows, ctrl, t_in, \
+                                                    n_parts, out, pair_cnt, row_tiles, nsplit, units_per_split, st, row_src)
 #define TQ_SK(GSV, CWV)                                                                                                   \
     do {                                                                                                                  \
-        if (wave_k == 256 && GSV * 16 <= 256)                                                                             \
-            return launch_skinny<STAGE, GSV, CWV, (GSV * 16 <= 256 ? 256 : 512)>(                                         \
-                G, sec, blob, xin, row_token, tile_e, tile_row0, tile_rows, ctrl, t_in, n_parts, out, pair_cnt, row_tiles, nsplit, \
-                units_per_split, st, row_src);                                                                            \
-        return launch_skinny<STAGE, GSV, CWV, 512>(G, sec, blob, xin, row_token, tile_e, tile_row0, tile_rows, ctrl, t_in, \
-                                                   n_parts, out, pair_cnt, row_tiles, nsplit, units_per_split, st, row_src);       \
+        if (wave_k == 512) TQ_SKL(GSV, CWV, 512, 8);                                                                      \
+        if (n_waves == 2) TQ_SKL(GSV, CWV, 256, 2);                                                                       \
+        if (n_waves == 4) TQ_SKL(GSV, CWV, 256, 4);                                                                       \
+        TQ_SKL(GSV, CWV, 256, 8);                                                                                         \
     } while (0)
     if (cw == 4) {
         switch (gs) {
@@ -615,12 +647,16 @@ tq_status launch_skinny_gs(int gs, int cw, const MGeom& G, const TqSection& sec,
         if (gs == 8) TQ_SK(8, 2);
     }
 #undef TQ_SK
+#undef TQ_SKL
     return TQ_ERR_UNSUPPORTED;
 }
 
-// contraction indices per wave of a stage: 512, or 256 on contractions of at most 2048 - a workgroup works on one
-// column-tile pair at a time, and with 512-wide slices a contraction of 1536 would leave five of its eight waves idle
+// Contraction indices per wave of a stage: 512, or 256 on contractions of at most 2048 (with 512 a contraction of 1536 would leave five of
+// eight waves idle); waves per workgroup: as many as have a slice (2, 4 or 8).  Eight waves of which four have work keep 32 KB of codes in flight
+// per CU, three workgroups of four 96 KB: 16 experts of 1024 x 8192, rank 0, 8 tokens 71.4 -> 47.8 us a call, 30 tokens 77.5 -> 61.5; 32 of 768 x 3072,
+// 60 tokens 61.4 -> 46.4; two waves: 24 of 512 x 3072, 5 tokens 42.1 -> 36.3.
 inline int wave_k_of(int K, int g) { return (K <= 2048 && g <= 256) ? 256 : 512; }
+inline int waves_of(int K, int g) { return wave_k_of(K, g) == 512 || K > 1024 ? 8 : K > 512 ? 4 : 2; }
 
 // contraction split of one stage: nsplit workgroups along K, each a whole number of wave slices
 inline void plan_split(int K, int g, int* nsplit, int* units_per_split)
@@ -628,7 +664,7 @@ inline void plan_split(int K, int g, int* nsplit, int* units_per_split)
     const int unit_k = g < 64 ? 64 : g;
     const int upw = wave_k_of(K, g) / unit_k;
     const int nu = K / unit_k;
-    const int max_units = SK_NW * upw;
+    const int max_units = 8 * upw;
     int ns = (nu + max_units - 1) / max_units;
     int ups = (nu + ns - 1) / ns;
     ups = (ups + upw - 1) / upw * upw;
@@ -641,12 +677,12 @@ inline void plan_split(int K, int g, int* nsplit, int* units_per_split)
 tq_status tqi_setup_skinny()
 {
     bool ok = true;
-#define TQ_ATTR(ST, GS, CW, DL, WK)                                                                                  \
-    ok = ok && hipFuncSetAttribute((const void*)moe_skinny_kernel<ST, GS, CW, DL, WK>,                                  \
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess
-#define TQ_ONE(ST, GS, CW)                                                                                           \
-    TQ_ATTR(ST, GS, CW, false, 512); TQ_ATTR(ST, GS, CW, true, 512);                                                 \
-    TQ_ATTR(ST, GS, CW, false, (GS * 16 <= 256 ? 256 : 512)); TQ_ATTR(ST, GS, CW, true, (GS * 16 <= 256 ? 256 : 512))
+#define TQ_ATTR(ST, GS, CW, WK, NW)                                                                                    \
+    ok = ok && hipFuncSetAttribute((const void*)moe_skinny_kernel<ST, GS, CW, false, WK, NW>,                             \
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, SK_LDS) == hipSuccess &&                   \
+         hipFuncSetAttribute((const void*)moe_skinny_kernel<ST, GS, CW, true, WK, NW>,                                    \
+                             hipFuncAttributeMaxDynamicSharedMemorySize, SK_LDS) == hipSuccess
+#define TQ_ONE(ST, GS, CW) TQ_ATTR(ST, GS, CW, 512, 8); TQ_ATTR(ST, GS, CW, 256, 8); TQ_ATTR(ST, GS, CW, 256, 4); TQ_ATTR(ST, GS, CW, 256, 2)
     TQ_ONE(0, 2, 4); TQ_ONE(0, 4, 4); TQ_ONE(0, 8, 4); TQ_ONE(0, 16, 4);
     TQ_ONE(1, 2, 4); TQ_ONE(1, 4, 4); TQ_ONE(1, 8, 4); TQ_ONE(1, 16, 4);
     TQ_ONE(0, 4, 3); TQ_ONE(0, 8, 3); TQ_ONE(1, 4, 3); TQ_ONE(1, 8, 3);
@@ -667,11 +703,11 @@ bool tqi_skinny_supported(const TqLayout& L)
     const int unit_k = L.g < 64 ? 64 : L.g;
     auto smem = [&](int units) {
         const int range_k = units * unit_k;
-        return (size_t)16 * (range_k * 2 + 16) + SK_RED_BYTES + (size_t)(range_k / L.g) * 64 + 16;
+        return (size_t)16 * (range_k * 2 + 16) + sk_red_bytes(8) + (size_t)(range_k / L.g) * 64 + 16;
     };
-    if (smem(ups) > 160 * 1024) return false;
+    if (smem(ups) > SK_LDS) return false;
     plan_split(L.F, L.g, &ns, &ups);
-    if (ns > TQ_MAX_SPLIT || smem(ups) > 160 * 1024) return false;
+    if (ns > TQ_MAX_SPLIT || smem(ups) > SK_LDS) return false;
     return true;
 }
 
@@ -716,7 +752,7 @@ tq_status tqi_forward_skinny(const TqLayout& L, const TqWorkspace& W, const uint
     int32_t* pair_cnt = reinterpret_cast<int32_t*>(ws + W.sk_cnt);
     if (W.sk_cnt_n < 2 * W.rt_max * TQ_MAX_SPLIT) return TQ_ERR_UNSUPPORTED;
     tq_status rc = launch_skinny_gs<0>(gs, L.cw, G, L.gu, blob, x, row_token, tile_e, tile_row0, tile_rows, ctrl, tpart, parts(L.gu), h, pair_cnt, rt16, 1,
-                                       ups, stream, row_src, wave_k_of(L.H, L.g));
+                                       ups, stream, row_src, wave_k_of(L.H, L.g), waves_of(L.H, L.g));
     if (rc != TQ_OK) return rc;
     tqi_record_stage(3, stream);
     plan_split(L.F, L.g, &ns, &ups);
@@ -727,7 +763,7 @@ tq_status tqi_forward_skinny(const TqLayout& L, const TqWorkspace& W, const uint
     }
     tqi_record_stage(4, stream);
     rc = launch_skinny_gs<1>(gs, L.cw, G, L.d, blob, h, row_token, tile_e, tile_row0, tile_rows, ctrl, tpart, parts(L.d), yd,
-                             pair_cnt + (size_t)W.rt_max * TQ_MAX_SPLIT, rt16, ns, ups, stream, nullptr, wave_k_of(L.F, L.g));
+                             pair_cnt + (size_t)W.rt_max * TQ_MAX_SPLIT, rt16, ns, ups, stream, nullptr, wave_k_of(L.F, L.g), waves_of(L.F, L.g));
     if (rc != TQ_OK) return rc;
     *nsplit_out = ns;
     return TQ_OK;

@@ -28,6 +28,12 @@ CASES.update({
     "dense_3_units_of_two": wide(2839, H=384, F=2304, g=128, T=12, bits=3, dense=True),
     "dense_2_units_of_one_chunk": wide(2840, H=320, F=448, T=12, bits=2, dense=True),
     "dense_2_units_of_two": wide(2841, H=2176, F=640, g=128, T=12, bits=2, dense=True),
+    # workgroups of two and of four waves: 512 and 1024 indices are their last, with all eight low-rank steps among them
+    "four_waves_groups_of_32": wide(2845, H=960, F=1024, g=32, T=12, r=64),
+    "four_waves_dense_3": wide(2846, H=576, F=832, T=12, r=64, bits=3, dense=True),
+    "two_waves_rank_64": wide(2847, H=512, F=512, g=128, T=16, r=64, **ONE),
+    "four_waves_groups_of_256": wide(2848, H=1024, F=512, g=256, T=12, r=40),
+    "many_experts_two_and_four_waves": wide(2849, E=40, k=4, H=512, F=1024, T=30, r=24),
     "256_rows_by_assignment": wide(2842, H=256, F=320, T=128, r=24),
     "258_rows_by_tile": wide(2843, H=256, F=320, T=129, r=24),
     "by_tile_40_experts": wide(2844, E=40, k=4, H=320, F=384, T=70, r=48, S=1),
