@@ -151,11 +151,9 @@ __device__ inline float run_sum(const u32x4& q)
 
 // STAGE 0: out = h[slot][F] bf16 = silu(gate) * up.   STAGE 1: out = yd[split][slot][H] fp32.
 // CW: 32-bit words of codes per lane, tile and 64-wide chunk: 4 (4-bit slots), 3 or 2 (dense 3- / 2-bit codes).
-// DEAL: the workgroups share out the (tile, split) combinations that exist among themselves (1-D grid) instead of
-// taking the one their 3-D block index names; see below.
 // WK, NW: contraction indices per wave and waves per workgroup: 512 and 8; on contractions of at most 2048 256 and as many waves
 // as they take (2, 4 or 8), and a CU holds as many workgroups as it has room for.
-template <int STAGE, int GS, int CW, bool DEAL, int WK, int NW>
+template <int STAGE, int GS, int CW, int WK, int NW>
 __global__ void __launch_bounds__(64 * NW, sk_waves_per_simd(NW)) moe_skinny_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob,
                                                          const uint16_t* __restrict__ xin,
                                                          const int32_t* __restrict__ row_token,
@@ -186,34 +184,30 @@ __global__ void __launch_bounds__(64 * NW, sk_waves_per_simd(NW)) moe_skinny_ker
     float* red = reinterpret_cast<float*>(lds + red_off);
     float* xs = reinterpret_cast<float*>(lds + xs_off);
 
-    // Which (row tile, split) this workgroup works on, its number `part` among the g_wg workgroups on it:
-    //  * 3-D grid (layers of few experts, where the host knows how many tiles will exist): blockIdx itself;
-    //  * DEAL, 1-D grid (many small experts, most of the tiles the host has to allow for are empty): the
-    //    workgroups are shared out among the combinations that EXIST, a number only the device knows.  Each of the
-    //    n_v combinations gets G = grid / n_v consecutive workgroups (consecutive ids sit on different XCDs, so a
-    //    combination's weight stream is spread over all of them), the first grid mod n_v one more from the end.
-    //    (A template argument, not a run-time switch or the only form: the kernel is short of scalar registers, and
-    //    the second form measured 1-2 % slower per stage on the 8-expert decode layer in every spelling tried; its
-    //    surplus workgroups leave inside the block below because the same test further down cost the down stage 70
-    //    more spilled scalar registers.)
+    // Which (row tile, split) this workgroup works on, its number `part` among the g_wg workgroups on it: the workgroups are shared out among the
+    // combinations that EXIST, a number only the device knows (most experts of a large layer receive no row, hot ones fill several tiles).  Each
+    // of the n_v combinations gets G_lo = grid / n_v consecutive workgroups, the first grid mod n_v one more from the end: consecutive ids
+    // sit on different XCDs, so a combination's weight stream is spread over all of them.  (A grid sized by the host for one tile
+    // an expert runs the tiles beyond in a second round and leaves the experts without rows idle: 8 experts of 4096 x 14336, 48 tokens 237 us against 183 here,
+    // 4 tokens 118 against 102; 32 of 2048 x 2048, top-4, 80 tokens 100 against 73; where every expert has one tile the two are level, up to 2 % apart
+    // either way.  With combination b mod n_v for workgroup b, 16 tokens of the first layer take 3 % longer: each XCD then streams one expert.)
     int rt, split, part, g_wg;
-    if constexpr (!DEAL) {
-        rt = blockIdx.y;
-        if (rt >= ctrl[4]) return;
-        split = blockIdx.z;
-        part = blockIdx.x;
-        g_wg = gridDim.x;
-    } else {
+    {
         const int n_t = ctrl[4], n_v = n_t * nsplit;
         if (n_v == 0) return;
-        const int G_lo = (int)gridDim.x / n_v, n_full = G_lo * n_v;      // the grid has at least n_v workgroups
-        const bool extra = (int)blockIdx.x >= n_full;
-        const int vt = extra ? (int)blockIdx.x - n_full : (int)blockIdx.x / G_lo;
-        part = extra ? G_lo : (int)blockIdx.x % G_lo;
+        const unsigned gx = gridDim.x, b = blockIdx.x, G_lo = gx / (unsigned)n_v, n_full = G_lo * (unsigned)n_v;      // the grid has at least n_v workgroups
+        const bool extra = b >= n_full;
+        const unsigned vq = b / G_lo;
+        const int vt = (int)(extra ? b - n_full : vq);
+        part = (int)(extra ? G_lo : b - vq * G_lo);
         if (part >= sec.pairs) return;      // more workgroups on this combination than it has pairs
-        g_wg = G_lo + (vt < (int)gridDim.x - n_full ? 1 : 0);
-        rt = vt % n_t;
-        split = vt / n_t;
+        g_wg = (int)G_lo + (vt < (int)(gx - n_full) ? 1 : 0);
+        rt = vt;
+        split = 0;
+        if (nsplit > 1) {
+            split = (int)((unsigned)vt / (unsigned)n_t);
+            rt = vt - split * n_t;
+        }
     }
     const int e = tile_e[rt], slot0 = tile_row0[rt], rows = tile_rows[rt];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, col = lane & 31;
@@ -581,36 +575,20 @@ tq_status launch_skinny(const MGeom& G, const TqSection& sec, const uint8_t* blo
     const int mb_off = xs_off + (range_k / G.g) * 16 * 4;      // mailbox of the pair scheduler
     const size_t smem = (size_t)mb_off + 16;
     if (smem > SK_LDS) return TQ_ERR_UNSUPPORTED;
-    // one workgroup per compute unit (a workgroup fills a CU's LDS; fewer, longer workgroups amortise the set-up -
-    // activation staging, group sums - over more pairs)
+    // as many workgroups as the chip holds at once (more, shorter ones would spend more of their time on the set-up: activation staging,
+    // group sums)
     const TqDeviceState* ds = nullptr;
     if (tqi_device_state(&ds) != TQ_OK) return TQ_ERR_HIP;
     const long slots = (long)ds->n_cu * std::max<long>(1, std::min<long>(4 * sk_waves_per_simd(NW) / NW, SK_LDS / (long)smem));      // workgroups that the chip holds at once
-    dim3 grid;
-    bool deal = false;
-    if (G.ne <= 32) {
-        // few experts: nearly all of them receive rows, the host's count of the tiles is good
-        const int tiles_est = (int)std::min<int64_t>(G.a_tot, std::min(G.ne, row_tiles));
-        long total = (long)sec.pairs * tiles_est * nsplit;
-        int ppw = (int)((total + slots - 1) / slots);
-        ppw = std::max(1, std::min(ppw, sec.pairs));
-        grid = dim3((sec.pairs + ppw - 1) / ppw, row_tiles, nsplit);
-        if (grid.y > 65535) return TQ_ERR_UNSUPPORTED;
-    } else {
-        // many experts: at least one workgroup per (tile, split) that may exist; the kernel shares them out among
-        // those that do
-        const long n_wg = std::max<long>(slots, (long)row_tiles * nsplit);
-        if (n_wg > 0x7FFFFFFF) return TQ_ERR_UNSUPPORTED;
-        grid = dim3((unsigned)n_wg);
-        deal = true;
-    }
-    // (dynamic-LDS limit of both instantiations: raised once per device by tqi_setup_skinny)
-    if (!deal)
-        hipLaunchKernelGGL((moe_skinny_kernel<STAGE, GS, CW, false, WK, NW>), grid, dim3(64 * NW), smem, st, G, sec, blob, xin, row_token, tile_e,
-                           tile_row0, tile_rows, ctrl, t_in, n_parts, out, pair_cnt, units_per_split, RB, red_off, xs_off, mb_off, row_src, nsplit);
-    else
-        hipLaunchKernelGGL((moe_skinny_kernel<STAGE, GS, CW, true, WK, NW>), grid, dim3(64 * NW), smem, st, G, sec, blob, xin, row_token, tile_e,
-                           tile_row0, tile_rows, ctrl, t_in, n_parts, out, pair_cnt, units_per_split, RB, red_off, xs_off, mb_off, row_src, nsplit);
+    // at least one workgroup per (tile, split) that may exist; the kernel shares them out among those that do.  (The dynamic-LDS limit is raised once
+    // per device by tqi_setup_skinny.)
+    // A combination has work for at most `pairs` of them: small layers launch no more (1024 instead of 160, most of which end at once, cost 8 experts
+    // of 256 x 512, 16 tokens, 2 us of 27).
+    const long combos = (long)std::min<int64_t>(row_tiles, G.a_tot) * nsplit;
+    const long n_wg = std::max<long>(std::min<long>(slots, combos * sec.pairs), (long)row_tiles * nsplit);
+    if (n_wg > 0x7FFFFFFF) return TQ_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL((moe_skinny_kernel<STAGE, GS, CW, WK, NW>), dim3((unsigned)n_wg), dim3(64 * NW), smem, st, G, sec, blob, xin, row_token, tile_e,
+                       tile_row0, tile_rows, ctrl, t_in, n_parts, out, pair_cnt, units_per_split, RB, red_off, xs_off, mb_off, row_src, nsplit);
     TQ_CHECK_LAUNCH();
     return TQ_OK;
 }
@@ -678,10 +656,8 @@ tq_status tqi_setup_skinny()
 {
     bool ok = true;
 #define TQ_ATTR(ST, GS, CW, WK, NW)                                                                                    \
-    ok = ok && hipFuncSetAttribute((const void*)moe_skinny_kernel<ST, GS, CW, false, WK, NW>,                             \
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, SK_LDS) == hipSuccess &&                   \
-         hipFuncSetAttribute((const void*)moe_skinny_kernel<ST, GS, CW, true, WK, NW>,                                    \
-                             hipFuncAttributeMaxDynamicSharedMemorySize, SK_LDS) == hipSuccess
+    ok = ok && hipFuncSetAttribute((const void*)moe_skinny_kernel<ST, GS, CW, WK, NW>,                                    \
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, SK_LDS) == hipSuccess
 #define TQ_ONE(ST, GS, CW) TQ_ATTR(ST, GS, CW, 512, 8); TQ_ATTR(ST, GS, CW, 256, 8); TQ_ATTR(ST, GS, CW, 256, 4); TQ_ATTR(ST, GS, CW, 256, 2)
     TQ_ONE(0, 2, 4); TQ_ONE(0, 4, 4); TQ_ONE(0, 8, 4); TQ_ONE(0, 16, 4);
     TQ_ONE(1, 2, 4); TQ_ONE(1, 4, 4); TQ_ONE(1, 8, 4); TQ_ONE(1, 16, 4);
