@@ -1070,7 +1070,16 @@ bool tqi_bf16_rows_take_skinny(const TqLayout& L, int64_t a_tot, int flags)
     // sums as bf16 pairs and multiplies by left factors rounded to bf16 where these kernels have fp32 sums and, up to 256
     // assignments, the fp16 factors themselves (error against 64 bits 2.35e-3 -> up to 2.54e-3), and 60 experts of 2048x1408 were
     // slower for it (404 assignments: 111 against 130 us).
-    bool skinny = !bf16_large_tiles_rows(L, a_tot, flags) && few_rows && !(flags & TQ_FLAG_FORCE_SMALL_TILE);
+    // Fewer than 16 experts: further, the further the less there is to stream ((E+S) H F codes a matrix).  A tile more costs the decode kernels
+    // a second pass over an expert's weights and the tiled ones next to nothing; where the weights are small the launches count, of which the
+    // decode kernels have one less, without the tiled pre-passes.  7600 batches of up to 1024 assignments of random layers, both paths forced: the 598
+    // that these lines move take 0.81 of the time on average (0.54 to 1.02); past them one batch in four is slower by more than 3 %.  8
+    // experts of 256x512, 16 rows 34.5 -> 29.0 us, 32 rows 36.8 -> 31.2; 8 of 4096x14336, 10 rows 196 -> 166, but 16 rows 197 -> 217.  (Layers of 16
+    // experts and more keep their lines: popular experts of theirs fill several tiles at the same average.)
+    const int64_t codes = (int64_t)ne * L.H * L.F;
+    const int rows_small = codes <= 10000000 ? 32 : codes <= 30000000 ? 20 : codes <= 100000000 ? 16 : 12;
+    const bool few_small = ne < 16 && a_tot <= (int64_t)rows_small * ne;
+    bool skinny = (few_small || (few_rows && !bf16_large_tiles_rows(L, a_tot, flags))) && !(flags & (TQ_FLAG_FORCE_SMALL_TILE | TQ_FLAG_FORCE_LARGE_TILE));
     if (flags & TQ_FLAG_FORCE_SKINNY) skinny = true;
     // (the parts that the tiled kernels derive per call from dense codes and fp8 factors are laid out in the workspace
     // exactly when this returns false)
