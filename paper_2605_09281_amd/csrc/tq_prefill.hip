@@ -10,10 +10,10 @@
 // fetched an item earlier.
 //
 // Items are dealt out statically.  Workgroup ids go round-robin over the 8 XCDs (each with its own L2);
-// XCD x takes the x-th eighth of the row tiles, a contiguous range, and its workgroups walk (row tile, column
-// block) in row-tile-major order, so the workgroups of one XCD are on a few neighbouring row tiles at any time:
-// they share their activations in that L2, and neighbouring tiles mostly share an expert's weights there too.
-// (With few row tiles the XCDs share out the column blocks of every tile instead: see by_cols.)
+// XCD x takes either the x-th eighth of the row tiles, a contiguous range, or every eighth column block of all
+// row tiles (by_cols), and its workgroups walk these items strip by strip of column blocks, in row-tile-major order within a
+// strip (strip_w): at any time the workgroups of an XCD are on a few neighbouring row tiles, which share an expert's weights, and a
+// few column blocks, which share activations, in that XCD's L2.
 #include "tq_device.h"
 
 #include <type_traits>
@@ -71,9 +71,13 @@ moe_prefill_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob, con
     const int tiles_x = min(max(ntiles - xcd * per_x, 0), per_x);
     // With few row tiles an eighth of them per XCD is a poor deal (12 tiles: six XCDs with two each, two with
     // none).  Then XCD x takes the column blocks x, x + 8, ... of EVERY row tile instead, whenever that leaves the
-    // busiest XCD at least a tenth fewer items; still row-tile-major, so its workgroups stay on neighbouring tiles.
+    // busiest XCD at least a tenth fewer items.  It also does where the column blocks are many enough for a strip in each XCD (four) and the
+    // busiest has no more items than under the deal by rows: full and remainder tiles, which take half the time, are then spread evenly (8 experts of
+    // 4096 x 14336: 300 tokens 415 -> 409 us against strips alone, 800 tokens 753 -> 735; with two or one column blocks in each
+    // XCD, 8 to 16 in all, 64 experts of 2048 x 1408 with 4096 tokens take 3 % longer).
     const int nbx_max = (nb_count + 7) >> 3;
-    const bool by_cols = (long long)ntiles * nbx_max * 10 <= (long long)per_x * nb_count * 9;
+    const bool by_cols = (long long)ntiles * nbx_max * 10 <= (long long)per_x * nb_count * 9 ||
+                         (nbx_max >= 4 && (long long)ntiles * nbx_max <= (long long)per_x * nb_count);
     const int nbx = xcd < nb_count ? (nb_count - xcd + 7) >> 3 : 0;
     const int items_x = by_cols ? ntiles * nbx : tiles_x * nb_count;
     int q = blockIdx.x >> 3;
@@ -94,8 +98,30 @@ moe_prefill_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob, con
     const int ZT = tq_zero_terms(K, G.g);
 
     // ---- item bookkeeping (everything wave-uniform) ---------------------------------------------------
-    auto tile_of = [&](int qq) { return by_cols ? qq / nbx : xcd * per_x + qq / nb_count; };
-    auto nb_of = [&](int qq) { return by_cols ? xcd + 8 * (qq % nbx) : qq % nb_count; };
+    // Strips.  What the workgroups of an XCD are on at one time is about R row tiles x C column blocks with R C = their number; a
+    // row tile costs its L2 64 rows of 2 bytes per contraction index, a column block 256 columns of half a byte, the same 128 bytes, so R = C
+    // fetches least as long as the R tiles are of one expert (tiles of another bring their own weights).  Hence C = workgroups / R with R the
+    // tiles an expert has on average, at most 8.  Row-tile-major over all of many column blocks is R = 1 and had every XCD stream
+    // all weights once per row tile: 8 experts of 4096 x 14336 (112 column blocks) on 600 tokens 648 -> 597 us, 1500 1385 -> 1218, 4096
+    // 3420 -> 2945; 12 of 2048 x 5632 (44) on 5000 tokens 788 -> 761; with the 12 of 128 experts of 4096 x 1536 R is 5 anyway: level.
+    const int rows_x = by_cols ? ntiles : tiles_x, cols_x = by_cols ? nbx : nb_count;
+    int strip_w;
+    {
+        const int width = max(1, wgx / min(8, max(1, ntiles / G.ne)));
+        const int n_strips = max(1, (cols_x + width / 2) / width);
+        strip_w = (cols_x + n_strips - 1) / n_strips;
+    }
+    // (row tile, column block) of item qq
+    auto place = [&](int qq, int& rt, int& nb) {
+        int r = qq / cols_x, c = qq - r * cols_x;
+        if (strip_w < cols_x) {
+            const int strip = qq / (rows_x * strip_w), in = qq - strip * (rows_x * strip_w), w = min(strip_w, cols_x - strip * strip_w);
+            r = in / w;
+            c = strip * strip_w + in - r * w;
+        }
+        rt = by_cols ? r : xcd * per_x + r;
+        nb = by_cols ? xcd + 8 * c : c;
+    };
     auto make_src = [&](int e, int nb, bool& active) {
         const int pair_raw = nb * 4 + wn;
         active = pair_raw < sec.pairs;
@@ -201,14 +227,14 @@ moe_prefill_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob, con
 
     // ---- start-up: the only place where the chain of dependent loads is exposed -------------------------
     int cur_e, cur_slot0, cur_nb, cur_rows;
-    int nxt_e, nxt_slot0;
+    int nxt_e, nxt_slot0, nxt_nb;
     {
-        const int rt = tile_of(q);
+        int rt, rtn;
+        place(q, rt, cur_nb);
+        place(min(q + wgx, items_x - 1), rtn, nxt_nb);
         cur_e = __builtin_amdgcn_readfirstlane(tile_e[rt]);
         cur_slot0 = __builtin_amdgcn_readfirstlane(tile_row0[rt]);
-        cur_nb = nb_of(q);
         cur_rows = min(BM, __builtin_amdgcn_readfirstlane(offsets[cur_e + 1]) - cur_slot0);
-        const int rtn = tile_of(min(q + wgx, items_x - 1));
         nxt_e = __builtin_amdgcn_readfirstlane(tile_e[rtn]);
         nxt_slot0 = __builtin_amdgcn_readfirstlane(tile_row0[rtn]);
         int tx, ta;
@@ -235,13 +261,13 @@ moe_prefill_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob, con
         const bool has_next = qn < items_x;
         // next item: its tile header was fetched one item ago, its row ids are requested now and written to
         // LDS after the augmented units; the header of the item after it is requested now as well
-        const int nxt_nb = has_next ? nb_of(qn) : cur_nb;
         bool nxt_active;
         const WSrc nxt = make_src(nxt_e, nxt_nb, nxt_active);
         int ntx, nta;
         row_ids(nxt_slot0, ntx, nta);
         const int noffs_v = offsets[nxt_e + 1];
-        const int rtnn = tile_of(min(qn + wgx, items_x - 1));
+        int rtnn, nn_nb;
+        place(min(qn + wgx, items_x - 1), rtnn, nn_nb);
         const int nn_e_v = tile_e[rtnn], nn_slot0_v = tile_row0[rtnn];
 
         // ---- augmented units: zero-point correction and the low-rank term ------------------------------
@@ -463,6 +489,7 @@ moe_prefill_kernel(MGeom G, TqSection sec, const uint8_t* __restrict__ blob, con
         cur_e = nxt_e; cur_slot0 = nxt_slot0; cur_rows = nxt_rows;
         nxt_e = nn_e;
         nxt_slot0 = nn_slot0;
+        nxt_nb = nn_nb;
         par ^= 1;
     }
 }
