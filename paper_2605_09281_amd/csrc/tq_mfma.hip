@@ -963,7 +963,9 @@ tq_status launch_aug(const MGeom& G, const TqSection& sec, const uint8_t* blob, 
         // neighbouring tiles on one XCD: from more row tiles on than the chip holds at once (two or three a CU).  65536 rows of 4096, 2048 tiles:
         // 152 -> 141.5 us, the factors of an expert then come once or twice from memory instead of eight times; below that nothing
         // is shared and the next kernel finds the tiles in another L2: 16 experts of 256x512, 600 rows 37.6 -> 38.4 us a call.
-        const bool runs = rt32 >= 768;
+        // Four column tiles of t are twice the factors or more, and pay from 96 tiles on: 60 experts of 2048 x 1408, rank 64, 500 tokens (122
+        // tiles) 165.1 -> 164.4 us a call, 1024 211.7 -> 211.0, 2048 (316) 321.9 -> 312.4; 200 tokens (85) level.
+        const bool runs = rt32 >= 768 || (nat > 2 && rt32 >= 96);
 #define TQ_AUGS(NATV, GSV)                                                                                          \
     hipLaunchKernelGGL((aug_staged_kernel<STAGE, NATV, GSV>), dim3(runs ? (rt32 + 7) / 8 * 8 : rt32, nsl), dim3(256), \
                        aug_stage_bytes(GSV) + 2 * 32 * 16,                                                                \
