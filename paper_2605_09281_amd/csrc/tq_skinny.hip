@@ -32,12 +32,12 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// the reduction buffer of NW waves: per wave the 8 - 8 / NW of its results that others add up, 2 tiles, 64 lanes, and a slot for those that nobody reads
 // waves per SIMD that a workgroup of nw waves is compiled for: three where it fits 168 registers without a spill.  (Four, 128 registers: 80
 // to 100 bytes spilled and two workgroups per CU, 60 experts of 2048 x 1408, 16 tokens 58.5 -> 72.4 us; two at four waves: 16 experts of 1024 x 8192,
 // 8 tokens 47.8 -> 51.8; three at two waves: 24 experts of 512 x 3072, 5 tokens 36.3 -> 37.3.)
 constexpr int sk_waves_per_simd(int nw) { return nw == 4 ? 3 : 2; }
 constexpr int SK_LDS = 160 * 1024;
+// the reduction buffer of NW waves: per wave the 8 - 8 / NW of its results that others add up, 2 tiles, 64 lanes, and a slot for those that nobody reads
 constexpr int sk_red_bytes(int nw) { return (nw * (8 - 8 / nw) * 2 + 1) * 64 * 4; }
 
 // Low-rank intermediate of one 16-row tile over 1024 contraction indices (a part of the range of a split):
