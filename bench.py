@@ -27,7 +27,7 @@ MFMA_BF16_PEAK = 2.5e15    # FLOP/s dense bf16, MI355X published
 # over this same command, scaled by the streaming-copy calibration: (bytes, file under profiles/ that holds the
 # counter readings).  These are profiler runs of their own, not measurements of the present run; workloads that
 # have not been counted report null.
-TRAFFIC_FROM_PROFILES = {2: (548.1e6 + 1.0e6, "profiles/hbm_traffic_config2_skinny_kernels.txt"),
+TRAFFIC_FROM_PROFILES = {2: (515.4e6 + 1.0e6, "profiles/hbm_traffic_config2_skinny_kernels.txt"),
                          3: (757.1e6 + 92.3e6, "profiles/hbm_traffic_config3_config5_prefill_kernels.txt"),
                          5: (4928.0e6 + 201.3e6, "profiles/hbm_traffic_config3_config5_prefill_kernels.txt")}
 STAGES = ["permute", "aug_gate_up", "gate_up", "aug_down", "down", "combine"]
@@ -563,7 +563,9 @@ def bench_layer(args, cfg, dev, oracle_macs, fp8=False):
     hbm_bound = work["path_flops"] / max(work["path_bytes"], 1) < MFMA_BF16_PEAK / HBM_PEAK
     t_gu = stage_us["gate_up"] * 1e-6
     ne = cfg.E + cfg.S
-    decode_path = ((cfg.a_tot // ne <= (12 if ne <= 8 else 10)) if ne <= 32 else cfg.a_tot <= (8 if cfg.H <= 2048 else 3) * ne) and cfg.a_tot <= 1024   # the library's rule
+    codes = ne * cfg.H * cfg.F
+    few_small = ne < 16 and cfg.a_tot <= (32 if codes <= 10e6 else 20 if codes <= 30e6 else 16 if codes <= 100e6 else 12) * ne
+    decode_path = (few_small or ((cfg.a_tot // ne <= (12 if ne <= 8 else 10)) if ne <= 32 else cfg.a_tot <= (8 if cfg.H <= 2048 else 3) * ne)) and cfg.a_tot <= 1024   # the library's rule
     kname = ("gate/up stage (moe_skinny_kernel<0,.>)" if decode_path else
              "gate/up stage (moe_prefill_kernel<0,.>, or moe_mfma_kernel<.,.,0,.> where the layer does not qualify)")
     traffic, traffic_source = (None, None) if (cfg.dense or fp8) else TRAFFIC_FROM_PROFILES.get(cfg.cfg_id, (None, None))
